@@ -75,6 +75,10 @@ struct Workspace {
     int32_t* forced;        // [max_batch][k+2]
     int32_t* forced_on;     // [1]
     // split-K partial tiles of the projection kernel; attention partials per position span
+    // activation planes of the many-row projections (see pgemm.hip) and 1/rms of their rows
+    uint16_t* planes;
+    float* row_inv;
+    size_t planes_n;             // bytes of planes
     float* ws_part;
     int32_t* ws_cnt;
     size_t ws_part_n, ws_cnt_n;  // their capacities (floats, counters)
@@ -146,8 +150,9 @@ void prof_end(Engine* e);
 ProfEntry* prof_slot(Engine* e, int cls, double bytes);
 void prof_commit(Engine* e);
 
+// lean: without the buffers of the many-row projections (they then run 16 rows at a time)
 size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, ModelDev* md, int* maxm,
-             MkState* mk = nullptr);
+             MkState* mk = nullptr, bool lean = false);
 
 // ---- launchers (kernels.hip) ----
 void launch_rope_table(hipStream_t s, ModelDev& m, int cap);
@@ -208,8 +213,9 @@ struct WsPlan {
 };
 WsPlan ws_plan(int M, int N, int K, int mode);
 void launch_wsgemv(Engine* e, hipStream_t s, const WsCall& c);
-hipError_t wsgemv_setup();
-int pg_split(int M, int N, int K, int subs);  // K ranges of the many-row GEMM for a shape  // kernel attributes of the many-row GEMM (once per process and device)
+// Many-row projection; false when it does not take the call (see pgemm.hip).
+bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c);
+
 void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int rps, const float* q, int q_stride);
 int attn_nsplit(int cap);
 size_t attn_groups(int rows, int rps, int H, int Hkv);

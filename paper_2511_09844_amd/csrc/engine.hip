@@ -9,6 +9,7 @@
 #include <new>
 
 #include "engine.h"
+#include "pgemm.h"
 
 using namespace sd2;
 
@@ -111,7 +112,7 @@ void model_dims(ModelDev* m, const sd2_dims& d) {
 namespace sd2 {
 
 size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, ModelDev* md, int* maxm_out,
-             MkState* mk) {
+             MkState* mk, bool lean) {
     Carver cv{base};
     int B = c.max_batch, k = c.k, cap = c.max_seq_len, V = c.verifier.vocab;
     int maxm = max_rows(c);
@@ -192,34 +193,30 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
                     if (p.S > 1) pmax = std::max(pmax, (size_t)p.tiles * p.S * 256);
                 }
         }
-        // many-row GEMM with K ranges: [tile][m block][range][subs][4 x 256] partials.  Besides the
-        // models' projections: W_s over many rows (the training-objective forward) and the MLP
-        // steering projections at batches above 16 rows
+        // many-row projections with K ranges.  Besides the models': W_s over many rows (the
+        // training-objective forward) and the MLP steering projections of more than 16 sequences
         const int R = c.steering == SD2_STEER_MLP_COND ? c.cond_rank : 0;
-        const bool mf = mlp_form(c);
-        for (int i = 0; i < 2; ++i) {
+        const bool mf = mlp_form(c), pg = c.dtype == SD2_BF16 && !lean;
+        for (int i = 0; i < 2 && pg; ++i) {
             const sd2_dims& d = *dd[i];
             int hd = d.d_model / d.n_heads;
-            int shapes[10][3] = {{(d.n_heads + 2 * d.n_kv_heads) * hd, d.d_model, 1},
-                                 {d.d_model, d.n_heads * hd, 1},
-                                 {d.d_ff, d.d_model, 2},
-                                 {d.d_model, d.d_ff, 1},
-                                 {d.vocab, d.d_model, 1},
-                                 {c.drafter.d_model, c.verifier.d_model, 1},
-                                 {mf ? c.verifier.d_model : 0, 3 * c.verifier.d_model, 1},
-                                 {mf ? bias_len(c) : 0, c.verifier.d_model, 1},
-                                 {R, c.drafter.d_model, 1},
-                                 {R ? c.drafter.d_ff : 0, R, 1}};
-            // the split depends on the rows only through their number of 64-row blocks
-            for (int nbm = 1; nbm <= (maxm + 63) / 64; ++nbm)
+            int shapes[10][2] = {{(d.n_heads + 2 * d.n_kv_heads) * hd, d.d_model},
+                                 {d.d_model, d.n_heads * hd},
+                                 {2 * d.d_ff, d.d_model},
+                                 {d.d_model, d.d_ff},
+                                 {d.vocab, d.d_model},
+                                 {c.drafter.d_model, c.verifier.d_model},
+                                 {mf ? c.verifier.d_model : 0, 3 * c.verifier.d_model},
+                                 {mf ? bias_len(c) : 0, c.verifier.d_model},
+                                 {R, c.drafter.d_model},
+                                 {R ? c.drafter.d_ff : 0, R}};
+            // the plan depends on the rows only through their number of 16-row groups
+            for (int rows = 16; rows <= pg_rows(maxm); rows += 16)
                 for (auto& sh : shapes) {
                     if (sh[0] <= 0) continue;
-                    int S = pg_split(nbm * 64, sh[0], sh[1], sh[2]);
-                    size_t nblkm = (size_t)nbm;
-                    if (S > 1) {
-                        pmax = std::max(pmax, nblkm * (sh[0] / 16) * S * sh[2] * 1024);
-                        pg_cnt = std::max(pg_cnt, nblkm * (sh[0] / 16));
-                    }
+                    const PgPlan p = pg_plan(rows, sh[0], sh[1]);
+                    pmax = std::max(pmax, p.part);
+                    pg_cnt = std::max(pg_cnt, p.cnt);
                 }
         }
         w.ws_part = cv.take<float>(std::max<size_t>(pmax, 1));
@@ -239,7 +236,18 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
             int hd = dd[i]->d_model / dd[i]->n_heads;
             amax = std::max(amax, (size_t)maxm * dd[i]->n_heads * attn_nsplit(cap) * (hd + 2));
         }
-        w.attn_part = cv.take<float>(amax);
+        // the planes of the many-row projections share the attention partials' memory: these live
+        // within one attention launch, those from k_planes to the projection that follows it
+        size_t planes = 0;
+        if (c.dtype == SD2_BF16 && !lean) {
+            for (int i = 0; i < 2; ++i)
+                planes = std::max(planes, pg_plane_bytes(maxm, std::max(dd[i]->d_model, dd[i]->d_ff)));
+            if (mlp_form(c) && B >= 16) planes = std::max(planes, pg_plane_bytes(B, 3 * c.verifier.d_model));
+            w.row_inv = cv.take<float>(maxm);
+        }
+        w.attn_part = cv.take<float>(std::max(amax, (planes + 3) / 4));
+        w.planes = planes ? (uint16_t*)w.attn_part : nullptr;
+        w.planes_n = planes;
         // arrival counters: the largest split-free grid of any launch shape
         size_t gmax = 1;
         for (int i = 0; i < 2; ++i) {
@@ -530,6 +538,9 @@ static sd2_status create_impl(const sd2_config* cfg, const sd2_weights* verifier
     if (!unsteered && !aligned16(w_steer)) return SD2_ERR_INVALID_ARG;
     if (!workspace || ((uintptr_t)workspace % kAlign) != 0) return SD2_ERR_INVALID_ARG;
     size_t need = sd2_workspace_bytes(cfg);
+    // the static workspace may hold a configuration only without the many-row projections' buffers
+    const bool lean = slot && need > workspace_bytes;
+    if (lean) need = carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, true);
     if (workspace_bytes < need) return SD2_ERR_INVALID_ARG;
     // the kernels are built for gfx950 with XNACK (page-fault replay) off, MI355X's default mode
     {
@@ -579,7 +590,7 @@ static sd2_status create_impl(const sd2_config* cfg, const sd2_weights* verifier
     }
     // Graph replay needs a capturable (non-null) stream; SD2_NO_GRAPH=1 forces eager launches.
     e->use_graph = hip_stream != nullptr && getenv("SD2_NO_GRAPH") == nullptr;
-    carve(*cfg, (char*)workspace, &e->ws, &e->mv, &e->md, &e->maxm, &e->mk);
+    carve(*cfg, (char*)workspace, &e->ws, &e->mv, &e->md, &e->maxm, &e->mk, lean);
     const sd2_weights* src[2] = {verifier, drafter};
     ModelDev* dst[2] = {&e->mv, &e->md};
     for (int i = 0; i < 2; ++i) {
@@ -588,12 +599,7 @@ static sd2_status create_impl(const sd2_config* cfg, const sd2_weights* verifier
         dst[i]->lm_head = src[i]->lm_head;
         for (int j = 0; j < dst[i]->dm.n_layers * 9; ++j) dst[i]->layer[j] = src[i]->layers[j];
     }
-    hipError_t err = wsgemv_setup();
-    if (err != hipSuccess) {
-        sd2_status st = hip_fail(e, err, "hipFuncSetAttribute");
-        if (!slot) delete e;
-        return st;
-    }
+    hipError_t err;
     if (slot) {
         // the static workspace keeps the previous handle's contents: clear it with a kernel
         const size_t n16 = (need + 15) / 16;
@@ -677,8 +683,8 @@ sd2_status sd2_create_noalloc(const sd2_config* cfg, const sd2_weights* verifier
     if (!out) return SD2_ERR_INVALID_ARG;
     *out = nullptr;
     if (!config_ok(cfg) || mlp_form(*cfg)) return SD2_ERR_INVALID_ARG;
-    const size_t need = sd2_workspace_bytes(cfg);
-    if (need > kStaticWorkspaceBytes) return SD2_ERR_CAPACITY;
+    if (carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, true) > kStaticWorkspaceBytes)
+        return SD2_ERR_CAPACITY;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return SD2_ERR_HIP;
     if (dev < 0 || dev >= kStaticMaxDevices) return SD2_ERR_UNSUPPORTED;

@@ -1,0 +1,417 @@
+// Projections of more than 16 activation rows with bf16 weights (prefill chunks, verify passes of
+// several sequences, the training-objective forward):
+//
+//   Y[m][n] (op)= sum_k W[n][k] * xn[m][k],   xn = x (optionally RMS-normalised and scaled by gamma)
+//
+// The activations enter as "planes": k_planes splits each value (times the gain) once into a bf16
+// hi/lo pair and stores it as [K / 64][row][64 hi | 64 lo], the order in which a workgroup stages
+// it, so staging is a linear copy (16-byte loads, 16-byte LDS stores) with no arithmetic.  It also
+// takes 1/rms of every row, which the epilogue applies.
+//
+// A workgroup of four waves owns 16 MG rows and 64 NG weight rows: each wave holds 16 NG weight
+// rows of its own, whose fragments it loads straight into registers (a weight is read by one wave
+// only, so LDS would add traffic), against all the rows, whose planes all four waves read from
+// LDS.  K goes in steps of KB blocks of 64 columns with two LDS buffers: while step i multiplies,
+// the planes of step i + 1 are on their way into registers, and each weight fragment is
+// requested again for a later step as soon as it has been used.  A row of a block is 256 bytes
+// in LDS, its sixteen 16-byte chunks permuted by chunk ^ (row & 15), so that the sixteen rows of
+// an operand read fall into different banks.
+//
+// The weights are the A operand of v_mfma_f32_16x16x32_bf16 and the activations the B operand, so
+// a lane ends with four consecutive output columns of one row: the epilogues (store, residual add
+// with the next norm's sums of squares, SwiGLU, Q|K|V with RoPE and the cache append) run on
+// registers with 16-byte accesses.  Weight rows are dealt in pairs of 16-row sub-tiles so that
+// what an epilogue combines sits in one lane: gate and up of the same features, or the two
+// rotate-half partners of a head.
+#include <hip/hip_ext.h>
+
+#include <algorithm>
+
+#include "device_common.h"
+#include "engine.h"
+#include "pgemm.h"
+
+namespace sd2 {
+
+typedef __bf16 pg_bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 pg_bf2 __attribute__((ext_vector_type(2)));
+typedef float pg_f4 __attribute__((ext_vector_type(4)));
+typedef float pg_f2 __attribute__((ext_vector_type(2)));
+typedef unsigned int pg_u4 __attribute__((ext_vector_type(4)));
+typedef int pg_i4 __attribute__((ext_vector_type(4)));
+
+// hi/lo bf16 split of two fp32 values, packed (hi = x rounded to nearest even, lo = (x - hi)
+// rounded likewise)
+__device__ __forceinline__ void pg_split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+    const pg_f2 v = {x0, x1};
+    const pg_bf2 h = __builtin_convertvector(v, pg_bf2);
+    const pg_bf2 l = __builtin_convertvector(v - __builtin_convertvector(h, pg_f2), pg_bf2);
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+
+struct PlaneArgs {
+    const float* X;
+    int ldx;
+    const int32_t* in_map;  // source row of each row (negative: zeros), or null
+    int M, Mp, K;           // rows, rows of the planes, columns
+    const uint16_t* gamma;  // bf16 gain, or null
+    const float* ss;        // [rows][nss] sums of squares (with gamma)
+    int nss;
+    float eps;
+    uint16_t* planes;
+    float* inv;             // [M] 1/rms (1 without gamma)
+};
+
+constexpr int kPlaneCols = 1024;  // columns per workgroup of k_planes: one float4 per thread
+
+__global__ __launch_bounds__(256) void k_planes(PlaneArgs a) {
+    const int row = blockIdx.x, tid = threadIdx.x;
+    const int src = a.in_map ? a.in_map[row] : row;
+    const int c = blockIdx.y * kPlaneCols + 4 * tid;
+    if (c < a.K) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (src >= 0) v = *(const float4*)(a.X + (size_t)src * a.ldx + c);
+        if (a.gamma) {
+            const uint2 w = *(const uint2*)(a.gamma + c);
+            v.x *= bf16_lo(w.x); v.y *= bf16_hi(w.x); v.z *= bf16_lo(w.y); v.w *= bf16_hi(w.y);
+        }
+        uint2 h, l;
+        pg_split2(v.x, v.y, h.x, l.x);
+        pg_split2(v.z, v.w, h.y, l.y);
+        uint16_t* p = a.planes + ((size_t)(c / kPgBlk) * a.Mp + row) * kPgBlkWords + c % kPgBlk;
+        *(uint2*)p = h;
+        *(uint2*)(p + kPgBlk) = l;
+    }
+    if (blockIdx.y == 0 && tid < 64) {
+        float sm = 0.f;
+        if (a.gamma && src >= 0)
+            for (int i = tid; i < a.nss; i += 64) sm += a.ss[(size_t)src * a.nss + i];
+        sm = wave_sum(sm);
+        if (tid == 0) a.inv[row] = a.gamma ? rsqrtf(sm / (float)a.K + a.eps) : 1.0f;
+    }
+}
+
+struct PgArgs {
+    const uint16_t* planes;
+    const float* inv;
+    int M, Mp, K, S, nblk_m, nblk_n, nbs;
+    const uint16_t* W[3];
+    int pairs;          // pairs of 16-row sub-tiles
+    int tiles;          // 16-column tiles of the output (store, add, SwiGLU)
+    int seg_pairs[2];   // Q|K|V: pairs of Q and of K
+    int mode;
+    float* Y;
+    int ldy;
+    const int32_t* out_map;
+    float* ss_out;
+    float* part;
+    int32_t* cnt;
+    int H, Hkv, hd;
+    const int32_t *row_pos, *row_seq;
+    const float *rcos, *rsin;
+    float *qout, *kc, *vc;
+    int cap, max_batch, layer;
+    const float* ubias;
+    int ub_ld;
+};
+
+// Weight row of lane row n in sub-tile `sub` of pair P.
+__device__ __forceinline__ const uint16_t* pg_row(const PgArgs& a, int P, int sub, int n) {
+    if (a.mode == kEpiSwiglu) return a.W[sub] + (size_t)(P * 16 + n) * a.K;
+    if (a.mode == kEpiQkv) {
+        int seg = 0;
+        if (P >= a.seg_pairs[0]) { P -= a.seg_pairs[0]; seg = 1; }
+        if (seg == 1 && P >= a.seg_pairs[1]) { P -= a.seg_pairs[1]; seg = 2; }
+        const int per = a.hd / 32, h = P / per, p = P % per;
+        return (seg == 0 ? a.W[0] : seg == 1 ? a.W[1] : a.W[2]) + (size_t)(h * a.hd + sub * (a.hd / 2) + 16 * p + n) * a.K;
+    }
+    // an odd number of tiles leaves the last pair half empty: its second sub-tile re-reads the first
+    return a.W[0] + (size_t)(min(2 * P + sub, a.tiles - 1) * 16 + n) * a.K;
+}
+
+__device__ __forceinline__ pg_f4 pg_ld4(const float* p) { return *(const pg_f4*)p; }
+
+// Epilogue of pair P for one row: lane (n, q) holds columns 4q .. 4q + 3 of both sub-tiles.
+// Executed by all lanes (`valid`: the row exists), since the add mode reduces across lanes.
+__device__ __forceinline__ void pg_epilogue(const PgArgs& a, int P, int row, bool valid, int q, pg_f4 v0, pg_f4 v1) {
+    if (a.mode == kEpiStore) {
+        if (!valid) return;
+        const int orow = a.out_map ? a.out_map[row] : row;
+        if (orow < 0) return;
+        float* y = a.Y + (size_t)orow * a.ldy + 32 * P + 4 * q;
+        *(pg_f4*)y = v0;
+        if (2 * P + 1 < a.tiles) *(pg_f4*)(y + 16) = v1;
+    } else if (a.mode == kEpiAdd) {
+        const bool two = 2 * P + 1 < a.tiles;
+        float s0 = 0.f, s1 = 0.f;
+        if (valid) {
+            float* y = a.Y + (size_t)row * a.ldy + 32 * P + 4 * q;
+            pg_f4 r0 = pg_ld4(y), r1 = two ? pg_ld4(y + 16) : pg_f4{0.f, 0.f, 0.f, 0.f};
+            r0 += v0;
+            r1 += v1;
+            if (a.ubias) {
+                const float* ub = a.ubias + (size_t)a.row_seq[row] * a.ub_ld + 32 * P + 4 * q;
+                r0 += pg_ld4(ub);
+                if (two) r1 += pg_ld4(ub + 16);
+            }
+            *(pg_f4*)y = r0;
+            if (two) *(pg_f4*)(y + 16) = r1;
+            s0 = (r0.x * r0.x + r0.y * r0.y) + (r0.z * r0.z + r0.w * r0.w);
+            s1 = (r1.x * r1.x + r1.y * r1.y) + (r1.z * r1.z + r1.w * r1.w);
+        }
+        s0 += __shfl_xor(s0, 16, 64);
+        s1 += __shfl_xor(s1, 16, 64);
+        s0 += __shfl_xor(s0, 32, 64);
+        s1 += __shfl_xor(s1, 32, 64);
+        if (valid && q == 0) {
+            a.ss_out[(size_t)row * a.tiles + 2 * P] = s0;
+            if (two) a.ss_out[(size_t)row * a.tiles + 2 * P + 1] = s1;
+        }
+    } else if (a.mode == kEpiSwiglu) {
+        if (!valid) return;
+        if (a.ubias) v1 += pg_ld4(a.ubias + (size_t)a.row_seq[row] * a.ub_ld + 16 * P + 4 * q);
+        pg_f4 o = {silu(v0.x) * v1.x, silu(v0.y) * v1.y, silu(v0.z) * v1.z, silu(v0.w) * v1.w};
+        *(pg_f4*)(a.Y + (size_t)row * a.ldy + 16 * P + 4 * q) = o;
+    } else {
+        if (!valid) return;
+        int seg = 0;
+        if (P >= a.seg_pairs[0]) { P -= a.seg_pairs[0]; seg = 1; }
+        if (seg == 1 && P >= a.seg_pairs[1]) { P -= a.seg_pairs[1]; seg = 2; }
+        const int per = a.hd / 32, h = P / per, i = 16 * (P % per) + 4 * q, half = a.hd / 2;
+        const int pos = a.row_pos[row];
+        if (seg < 2) {
+            const int pp = pos < 0 ? 0 : pos;
+            const pg_f4 c = pg_ld4(a.rcos + (size_t)pp * half + i), s = pg_ld4(a.rsin + (size_t)pp * half + i);
+            const pg_f4 x = v0;
+            v0 = x * c - v1 * s;
+            v1 = v1 * c + x * s;
+        }
+        float* y;
+        if (seg == 0) {
+            y = a.qout + (size_t)row * a.H * a.hd + h * a.hd + i;
+        } else {
+            if (pos < 0) return;
+            y = (seg == 1 ? a.kc : a.vc) +
+                ((((size_t)a.layer * a.max_batch + a.row_seq[row]) * a.Hkv + h) * a.cap + pos) * a.hd + i;
+        }
+        *(pg_f4*)y = v0;
+        *(pg_f4*)(y + half) = v1;
+    }
+}
+
+template <int MG, int NG, int KB>
+__global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
+    static_assert(NG % 2 == 0, "sub-tiles come in pairs");
+    constexpr int kBlkB = 16 * MG * kPgBlkWords * 2;    // bytes of one 64-column block in LDS
+    constexpr int kStageB = KB * kBlkB;
+    constexpr int NA = kStageB / (256 * 16);            // 16-byte words per thread and step
+    static_assert(NA >= 1, "stage");
+    __shared__ __attribute__((aligned(16))) char sm[2 * kStageB];
+    __shared__ int last_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 15, q = lane >> 4;
+    // workgroups are dealt to the 8 XCDs in turn, so blocks b, b + 8, ... share an XCD: they take
+    // the row blocks of one weight block, whose weights then come from that XCD's L2
+    const int s = blockIdx.x / a.nbs, bb = blockIdx.x % a.nbs;
+    const int r = bb >> 3, mb = r % a.nblk_m, nb = (bb & 7) + 8 * (r / a.nblk_m);
+    if (nb >= a.nblk_n) return;  // grid padding (uniform per workgroup)
+    const int m0 = mb * 16 * MG;
+    const int P0 = nb * 2 * NG + wave * (NG / 2);       // first pair of this wave
+    const uint16_t* wp[NG];
+#pragma unroll
+    for (int j = 0; j < NG; ++j) wp[j] = pg_row(a, min(P0 + j / 2, a.pairs - 1), j & 1, n) + 16 * q;
+    // this range's steps of 64 KB columns
+    const int nst = a.K / (kPgBlk * KB);
+    const int b0 = (int)((long)nst * s / a.S), b1 = (int)((long)nst * (s + 1) / a.S);
+
+    pg_f4 acc[MG][NG];
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+#pragma unroll
+        for (int j = 0; j < NG; ++j) acc[g][j] = pg_f4{0.f, 0.f, 0.f, 0.f};
+
+    pg_u4 w[KB][2][NG];
+    pg_u4 xa[NA];
+    auto load_w = [&](int step, int kb, int h) {
+#pragma unroll
+        for (int j = 0; j < NG; ++j) w[kb][h][j] = *(const pg_u4*)(wp[j] + (size_t)(step * KB + kb) * kPgBlk + 8 * h);
+    };
+    // planes: block kb of a step is one run of 16 MG rows of 256 bytes
+    const char* const xbase = (const char*)a.planes + (size_t)m0 * kPgBlkWords * 2 + tid * 16;
+    const size_t xstep = (size_t)a.Mp * kPgBlkWords * 2;
+    auto load_x = [&](int step) {
+#pragma unroll
+        for (int e = 0; e < NA; ++e) {
+            constexpr int per = kBlkB / 4096;
+            xa[e] = *(const pg_u4*)(xbase + (size_t)(step * KB + e / per) * xstep + (e % per) * 4096);
+        }
+    };
+    const int srow = tid >> 4, schunk = tid & 15;
+    char* const sbase = sm + srow * 256 + ((schunk ^ srow) << 4);
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int e = 0; e < NA; ++e) *(pg_u4*)(sbase + buf * kStageB + e * 4096) = xa[e];
+    };
+    load_x(b0);
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) { load_w(b0, kb, 0); load_w(b0, kb, 1); }
+    stage(0);
+    __syncthreads();
+    for (int step = b0; step < b1; ++step) {
+        const int buf = (step - b0) & 1;
+        const int nx = min(step + 1, b1 - 1);
+        load_x(nx);
+        const char* const lb = sm + buf * kStageB + n * 256;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int ch = 2 * q + h;
+                const char* const ph = lb + kb * kBlkB + ((ch ^ n) << 4);
+                const char* const pl = lb + kb * kBlkB + (((8 + ch) ^ n) << 4);
+#pragma unroll
+                for (int g = 0; g < MG; ++g) {
+                    const pg_bf8 xh = __builtin_bit_cast(pg_bf8, *(const pg_u4*)(ph + g * 4096));
+                    const pg_bf8 xl = __builtin_bit_cast(pg_bf8, *(const pg_u4*)(pl + g * 4096));
+#pragma unroll
+                    for (int j = 0; j < NG; ++j)
+                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf8, w[kb][h][j]), xh,
+                                                                           acc[g][j], 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < NG; ++j)
+                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf8, w[kb][h][j]), xl,
+                                                                           acc[g][j], 0, 0, 0);
+                }
+                load_w(nx, kb, h);
+            }
+        stage(buf ^ 1);
+        __syncthreads();
+    }
+
+    if (a.S > 1) {
+        // every range writes its sums through, lane by lane; the last to arrive adds them in range
+        // order (see arrive_last)
+        const size_t tile = (size_t)nb * a.nblk_m + mb;
+        constexpr int kTile = MG * NG * 4 * 256;  // floats
+        float* pt = a.part + tile * a.S * kTile + (size_t)wave * MG * NG * 256 + lane * 4;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(pt + (size_t)s * kTile - lane * 4, 0, MG * NG * 1024, 0x00027000);
+#pragma unroll
+        for (int g = 0; g < MG; ++g)
+#pragma unroll
+            for (int j = 0; j < NG; ++j)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(pg_u4, acc[g][j]), rs,
+                                                       (g * NG + j) * 1024 + lane * 16, 0, 16 /* sc1 */);
+        if (!arrive_last(a.cnt + tile, a.S, &last_s)) return;
+#pragma unroll
+        for (int g = 0; g < MG; ++g)
+#pragma unroll
+            for (int j = 0; j < NG; ++j) acc[g][j] = pg_f4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < a.S; ++t) {
+            const float* ps = pt + (size_t)t * kTile;
+#pragma unroll
+            for (int g = 0; g < MG; ++g)
+#pragma unroll
+                for (int j = 0; j < NG; ++j) acc[g][j] += pg_ld4(ps + (g * NG + j) * 256);
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < MG; ++g) {
+        const int row = m0 + 16 * g + n;
+        const bool valid = row < a.M;
+        const int rr = min(row, a.M - 1);
+        const float sc = a.inv[rr];
+#pragma unroll
+        for (int p = 0; p < NG / 2; ++p)
+            if (P0 + p < a.pairs) pg_epilogue(a, P0 + p, rr, valid, q, acc[g][2 * p] * sc, acc[g][2 * p + 1] * sc);
+    }
+}
+
+// Shapes from a sweep of tiles and splits over 8 to 2048 rows at the 8B, 70B and drafter widths
+// (weights cycled through more than the last-level cache).  MG: the fewest row groups that hold
+// the rows, up to 128 rows, so that the weights are read once.  NG 4 (128 x 256) halves the LDS
+// reads per product and wins wherever its grid fills the chip (512 rows of gate|up 8B: 209 us
+// against 269 with NG 2), or K is long enough to split (1024 rows of down: 225 against 252);
+// below that its few blocks and their large partials lose (512 rows of down: 176 against 135).
+// 64-row blocks take short K with few columns, where even split 128-row blocks leave workgroups
+// idle (128 rows of O 8B: 28 against 34 us).  S: up to two workgroups per CU, one with up to 32
+// rows (24 rows of gate|up: 55 us unsplit, 60 with S 2; of Q|K|V: 19 with S 4, 23 with S 8).
+PgPlan pg_plan(int M, int N, int K) {
+    PgPlan p{};
+    const int rows = pg_rows(M);
+    auto blocks = [&](int mg, int ng) { return ((rows + 16 * mg - 1) / (16 * mg)) * ((N + 64 * ng - 1) / (64 * ng)); };
+    int target = 512, min_k = 512;
+    p.NG = 2;
+    if (rows <= 32 && K % 256 == 0) {
+        p.MG = rows <= 16 ? 1 : 2;
+        target = min_k = 256;
+    } else if (rows <= 64 || blocks(8, 2) * (K / 512) < 512) {
+        p.MG = 4;
+    } else {
+        p.MG = 8;
+        if (blocks(8, 4) >= 384 || (K >= 8192 && blocks(8, 4) >= 128)) p.NG = 4;
+    }
+    p.nblk_m = (rows + 16 * p.MG - 1) / (16 * p.MG);
+    p.nblk_n = (N + 64 * p.NG - 1) / (64 * p.NG);
+    const int nb = p.nblk_m * p.nblk_n;
+    p.S = std::max(1, std::min(target / nb, K / min_k));
+    p.part = p.S > 1 ? (size_t)nb * p.S * p.MG * p.NG * 1024 : 0;
+    p.cnt = p.S > 1 ? nb : 0;
+    return p;
+}
+
+template <int MG, int NG, int KB>
+static void pg_launch(hipStream_t s, ProfEntry* pe, dim3 grid, const PgArgs& a) {
+    hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB>), grid, dim3(256), 0, s, pe ? pe->a : nullptr, pe ? pe->b : nullptr, 0, a);
+}
+
+bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
+    Workspace& ws = e->ws;
+    if (c.K % 128 || !ws.planes || pg_plane_bytes(c.M, c.K) > ws.planes_n || c.M > e->maxm) return false;
+    if (c.nseg != 1 && c.mode != kEpiQkv && c.mode != kEpiSwiglu) return false;
+    PgArgs a{};
+    int N = 0;
+    for (int i = 0; i < 3; ++i) {
+        a.W[i] = i < c.nseg ? (const uint16_t*)c.W[i] : nullptr;
+        if (i < c.nseg) N += c.seg_rows[i];
+    }
+    PgPlan p = pg_plan(c.M, N, c.K);
+    if (p.part > ws.ws_part_n || p.cnt > ws.ws_cnt_n) p.S = 1;  // partials must fit the workspace
+    PlaneArgs x{};
+    x.X = c.X; x.ldx = c.K; x.in_map = c.in_map; x.M = c.M; x.Mp = pg_rows(c.M); x.K = c.K;
+    x.gamma = (const uint16_t*)c.gamma; x.ss = c.ss; x.nss = c.nss; x.eps = c.eps;
+    x.planes = ws.planes; x.inv = ws.row_inv;
+    prof_begin(e, kProfOther, 0.0);
+    k_planes<<<dim3(c.M, (c.K + kPlaneCols - 1) / kPlaneCols), 256, 0, s>>>(x);
+    prof_end(e);
+    a.planes = ws.planes; a.inv = ws.row_inv;
+    a.M = c.M; a.Mp = x.Mp; a.K = c.K; a.S = p.S; a.nblk_m = p.nblk_m; a.nblk_n = p.nblk_n;
+    a.nbs = 8 * p.nblk_m * ((p.nblk_n + 7) / 8);
+    a.mode = c.mode;
+    if (c.mode == kEpiSwiglu) {
+        a.pairs = a.tiles = c.seg_rows[0] / 16;
+    } else {
+        a.tiles = N / 16;
+        a.pairs = (a.tiles + 1) / 2;
+    }
+    if (c.mode == kEpiQkv) {
+        a.seg_pairs[0] = c.seg_rows[0] / 32;
+        a.seg_pairs[1] = c.seg_rows[1] / 32;
+    }
+    a.Y = c.Y; a.ldy = c.ldy; a.out_map = c.out_map; a.ss_out = c.ss_out; a.part = c.part; a.cnt = c.cnt;
+    a.H = c.H; a.Hkv = c.Hkv; a.hd = c.hd; a.row_pos = c.row_pos; a.row_seq = c.row_seq;
+    a.rcos = c.rcos; a.rsin = c.rsin; a.qout = c.qout; a.kc = c.kc; a.vc = c.vc;
+    a.cap = c.cap; a.max_batch = c.max_batch; a.layer = c.layer; a.ubias = c.ubias; a.ub_ld = c.ub_ld;
+    ProfEntry* pe = prof_slot(e, kProfGemv, (double)N * c.K * 2.0 + (double)c.M * c.K * 4.0 + (double)c.M * N * 4.0);
+    const dim3 grid(a.nbs * p.S);
+    if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, grid, a);
+    else if (p.MG == 2) pg_launch<2, 2, 4>(s, pe, grid, a);
+    else if (p.MG == 4) pg_launch<4, 2, 2>(s, pe, grid, a);
+    else if (p.NG == 2) pg_launch<8, 2, 1>(s, pe, grid, a);
+    else pg_launch<8, 4, 1>(s, pe, grid, a);
+    if (pe) prof_commit(e);
+    return true;
+}
+
+}  // namespace sd2

@@ -364,296 +364,6 @@ __global__ __launch_bounds__(NW * 64) void k_wsgemv(WsArgs a) {
     }
 }
 
-// ===========================================================================
-// Many-row projections (prefill chunks, large batches, verify passes of more than 16 rows): an
-// MFMA GEMM.  A workgroup computes 64 activation rows (4 groups of 16) against 8 weight sub-tiles
-// of 16 rows (two per wave), walking K in steps of 128 columns through a two-deep pipeline: the
-// activation slice of step i + 1 sits in the second of two LDS buffers (hi/lo bf16 planes, gain
-// applied, as in k_wsgemv) and its weight fragments in a second register set while step i's
-// MFMAs run, and the loads of step i + 2 are issued as soon as step i + 1's activations have been
-// staged.  Every weight fragment meets all 4 row groups.  Epilogues are k_wsgemv's, per 16-row
-// group.
-// ===========================================================================
-constexpr int kPgRows = 64;           // activation rows per workgroup
-constexpr int kPgTW = 2;              // weight sub-tiles per wave
-constexpr int kPgKC = 128;            // K columns per step
-constexpr int kPgLdk = kPgKC + 8;     // padded LDS row stride (bf16 elements)
-constexpr int kPgX4 = kPgRows * kPgKC / 4 / 256;  // float4 of a step's activation slice per thread
-constexpr size_t kPgPlane = (size_t)kPgRows * kPgLdk;           // bf16 elements of one plane
-constexpr size_t kPgLds = 2 * 2 * kPgPlane * 2;  // two buffers of hi and lo planes (also holds the 32 KB of results)
-static_assert(kPgLds >= 4 * kPgTW * 4 * 256 * 4, "result staging must fit the activation planes");
-
-// K ranges for a many-row projection: split while the grid stays within 2 workgroups per CU and
-// every range keeps at least 1024 columns (a multiple of 256); 512 with a single 64-row block,
-// whose grid is the smallest (the 32-row first drafter step of a 16-sequence batch).  Shared by
-// the launch and the workspace sizing.
-int pg_split(int M, int N, int K, int subs) {
-    const int nt = 4 * kPgTW / subs;
-    const int nblk_m = (M + kPgRows - 1) / kPgRows;
-    const int nblk_n = (N / 16 + nt - 1) / nt;
-    const int blocks = 8 * nblk_m * ((nblk_n + 7) / 8);
-    int S = 1;
-    const int min_range = nblk_m == 1 ? 512 : 1024;
-    while (blocks * S * 2 <= 512 && (K / (S * 2)) % 256 == 0 && K / (S * 2) >= min_range && K % (S * 2) == 0) S *= 2;
-    return S;
-}
-
-template <int SUBS>
-__global__ __launch_bounds__(256, 2) void k_pgemm(WsArgs a, int nblk_m, int nbs) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ float inv_rms[kPgRows];
-    __shared__ int src_row[kPgRows];
-    constexpr int NT = 4 * kPgTW / SUBS;  // 16-row output tiles per workgroup
-    __shared__ int last_tile[NT];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, q = lane >> 4;
-    // block -> (n block, m block): workgroups are dealt to the 8 XCDs in turn, so blocks b, b + 8,
-    // ... share an XCD; they take the m blocks of one n block, whose weights then come from that
-    // XCD's L2 after the first read
-    // K range s of a.S (blocks of one range are contiguous); within it, as for S = 1
-    const int s = blockIdx.x / nbs;
-    const int bb = blockIdx.x % nbs;
-    const int xcd = bb & 7, r = bb >> 3;
-    const int mb = r % nblk_m;
-    const int nb = xcd + 8 * (r / nblk_m);
-    const int tile0 = nb * NT;
-    if (tile0 >= a.tiles) return;  // grid padding (uniform per workgroup)
-    const int m0 = mb * kPgRows;
-    const int M = a.M;
-    if (tid < kPgRows) {
-        const int row = m0 + tid;
-        int src = -1;
-        if (row < M) src = a.in_map ? a.in_map[row] : row;
-        src_row[tid] = src;
-        inv_rms[tid] = 1.0f;
-    }
-    __syncthreads();
-    // this wave's sub-tiles: SwiGLU waves 0, 1 take gate rows and waves 2, 3 the up rows of the
-    // same features; a tile past the end is read clamped and never written
-    const int sub = SUBS == 2 ? wave >> 1 : 0;
-    const uint16_t* wrow[kPgTW];
-#pragma unroll
-    for (int j = 0; j < kPgTW; ++j) {
-        const int tile = tile0 + (SUBS == 2 ? (wave & 1) * kPgTW : wave * kPgTW) + j;
-        wrow[j] = tile_row(a, min(tile, a.tiles - 1), sub, n) + 16 * q;
-    }
-    uint16_t* const planes = (uint16_t*)smem;  // [buffer][hi, lo][64][kPgLdk]
-    floatx4_t acc[kPgTW][4];
-#pragma unroll
-    for (int j = 0; j < kPgTW; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) acc[j][g] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    const int KS = a.K / a.S, kb = s * KS, nstep = KS / kPgKC;
-    typedef u32x4_t WFrag[kPgTW][2][2];
-    // weight fragments of step i: lane (n, q) holds row n of each sub-tile, columns
-    // 64 st + 16 q + 8 h + [0, 8) of the step (A is read with the same column order)
-    auto load_w = [&](int i, WFrag& w) {
-        const int k0 = kb + i * kPgKC;
-#pragma unroll
-        for (int j = 0; j < kPgTW; ++j)
-#pragma unroll
-            for (int st = 0; st < 2; ++st)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) w[j][st][h] = *(const u32x4_t*)(wrow[j] + k0 + st * 64 + 8 * h);
-    };
-    // 64 rows x 128 columns of fp32 activations: kPgX4 float4 per thread, row-major (a thread's
-    // float4 all sit at the same 4 columns, so it needs one word pair of the gain per step,
-    // requested with them)
-    const int kk_t = (tid & 31) * 4;
-    auto load_x = [&](int i, float4 (&xv)[kPgX4], uint2& gw) {
-        const int k0 = kb + i * kPgKC;
-#pragma unroll
-        for (int e = 0; e < kPgX4; ++e) {
-            const int m = (tid + e * 256) >> 5;
-            const int src = src_row[m];
-            xv[e] = src >= 0 ? *(const float4*)(a.X + (size_t)src * a.ldx + k0 + kk_t) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        gw = a.gamma ? *(const uint2*)(a.gamma + k0 + kk_t) : make_uint2(0x3f803f80u, 0x3f803f80u);
-    };
-    // gain, then the hi/lo bf16 split of step i's slice into buffer (i & 1)
-    auto stage = [&](int i, const float4 (&xv)[kPgX4], uint2 gw) {
-        uint16_t* xh = planes + (size_t)(i & 1) * 2 * kPgPlane;
-        uint16_t* xl = xh + kPgPlane;
-        const float gm[4] = {bf16_lo(gw.x), bf16_hi(gw.x), bf16_lo(gw.y), bf16_hi(gw.y)};
-#pragma unroll
-        for (int e = 0; e < kPgX4; ++e) {
-            const int m = (tid + e * 256) >> 5, kk = kk_t;
-            uint32_t h0, h1, l0, l1;
-            split_hilo(xv[e].x * gm[0], xv[e].y * gm[1], h0, l0);
-            split_hilo(xv[e].z * gm[2], xv[e].w * gm[3], h1, l1);
-            *(uint2*)(xh + m * kPgLdk + kk) = make_uint2(h0, h1);
-            *(uint2*)(xl + m * kPgLdk + kk) = make_uint2(l0, l1);
-        }
-    };
-    auto mma = [&](int i, const WFrag& w) {
-        const uint16_t* xh = planes + (size_t)(i & 1) * 2 * kPgPlane;
-        const uint16_t* xl = xh + kPgPlane;
-#pragma unroll
-        for (int st = 0; st < 2; ++st) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int kk = st * 64 + 16 * q + 8 * h;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const bf16x8_t ah = *(const bf16x8_t*)(xh + (g * 16 + n) * kPgLdk + kk);
-                    const bf16x8_t al = *(const bf16x8_t*)(xl + (g * 16 + n) * kPgLdk + kk);
-#pragma unroll
-                    for (int j = 0; j < kPgTW; ++j) {
-                        const bf16x8_t b = __builtin_bit_cast(bf16x8_t, w[j][st][h]);
-                        acc[j][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, b, acc[j][g], 0, 0, 0);
-                        acc[j][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, b, acc[j][g], 0, 0, 0);
-                    }
-                }
-            }
-        }
-    };
-    // Pipeline: step i's MFMAs (weights wa for even i, wb for odd), then step i + 1's activations
-    // staged into the other buffer, then the loads of step i + 2 into the registers just freed;
-    // one barrier per step (a buffer is rewritten only after every wave has passed the barrier
-    // that follows its last read).
-    WFrag wa, wb;
-    float4 xv[kPgX4];
-    uint2 gw;
-    load_x(0, xv, gw);
-    load_w(0, wa);
-    // RMSNorm statistics (used by the epilogue only), requested behind the first step's loads:
-    // four threads per row, each summing every fourth float4 of the row's partial sums of squares
-    if (a.gamma) {
-        const int m = tid >> 2, p = tid & 3;
-        const int src = src_row[m];
-        float sm = 0.0f;
-        // eight float4 per thread in flight at once, indexes clamped and the extra ones dropped
-        // (loads under a loop test would each wait for the previous one)
-        const float4* sp = (const float4*)(a.ss + (size_t)max(src, 0) * a.nss);
-        const int n4s = a.nss / 4;
-        for (int f0 = 0; f0 < n4s; f0 += 32) {
-            float4 v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = sp[min(f0 + p + 4 * u, n4s - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                sm += (src >= 0 && f0 + p + 4 * u < n4s) ? (v[u].x + v[u].y) + (v[u].z + v[u].w) : 0.f;
-        }
-        sm += __shfl_xor(sm, 1, 4);
-        sm += __shfl_xor(sm, 2, 4);
-        if (p == 0) inv_rms[m] = rsqrtf(sm / (float)a.K + a.eps);
-    }
-    stage(0, xv, gw);
-    if (nstep > 1) {
-        load_x(1, xv, gw);
-        load_w(1, wb);
-    }
-    __syncthreads();
-    for (int i = 0; i < nstep; i += 2) {
-        mma(i, wa);
-        if (i + 1 < nstep) stage(i + 1, xv, gw);
-        if (i + 2 < nstep) {
-            load_x(i + 2, xv, gw);
-            load_w(i + 2, wa);
-        }
-        __syncthreads();
-        if (i + 1 >= nstep) break;
-        mma(i + 1, wb);
-        if (i + 2 < nstep) stage(i + 2, xv, gw);
-        if (i + 3 < nstep) {
-            load_x(i + 3, xv, gw);
-            load_w(i + 3, wb);
-        }
-        __syncthreads();
-    }
-    __syncthreads();  // planes free: results go to LDS, slot (wave * TW + j, group g)
-    float* red = (float*)smem;
-#pragma unroll
-    for (int j = 0; j < kPgTW; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) red[((wave * kPgTW + j) * 4 + g) * 256 + (4 * q + i) * 16 + n] = acc[j][g][i];
-    __syncthreads();
-    // per output tile and row group: element (m, c) at thread 16 m + c; SwiGLU's up value of
-    // local tile lt sits 2 TW slots after its gate value.  With K ranges, each range stores its
-    // sums of every (tile, m block) it holds, waits once for all of those stores, and counts in on
-    // all of its tiles at once; the last range to arrive at a tile adds the S partials in range
-    // order.
-    if (a.S > 1) {
-        for (int lt = 0; lt < NT; ++lt) {
-            const int tile = tile0 + lt;
-            if (tile >= a.tiles) break;
-            float* pt = a.part + (size_t)(tile * nblk_m + mb) * a.S * SUBS * 1024;
-#pragma unroll
-            for (int sub = 0; sub < SUBS; ++sub)
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    store_through(pt + ((size_t)s * SUBS + sub) * 1024 + g * 256 + tid,
-                                  red[((lt + sub * 2 * kPgTW) * 4 + g) * 256 + tid]);
-        }
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's stores have completed
-        __syncthreads();
-        if (tid < NT) {
-            const int tile = tile0 + tid;
-            int last = 0;
-            if (tile < a.tiles) {
-                int32_t* c = a.cnt + tile * nblk_m + mb;
-                const int prev = __hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                last = prev == a.S - 1;
-                if (last) __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            last_tile[tid] = last;
-        }
-        __syncthreads();
-    }
-    for (int lt = 0; lt < NT; ++lt) {
-        const int tile = tile0 + lt;
-        if (tile >= a.tiles) break;
-        if (a.S > 1 && !last_tile[lt]) continue;
-        float sum[4][SUBS];
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int sub = 0; sub < SUBS; ++sub) sum[g][sub] = red[((lt + sub * 2 * kPgTW) * 4 + g) * 256 + tid];
-        if (a.S > 1) {
-            // the S ranges' partials of all 4 row groups, 8 ranges per round trip (loads past S
-            // re-read the last range and are not added)
-            const float* pt = a.part + (size_t)(tile * nblk_m + mb) * a.S * SUBS * 1024 + tid;
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int sub = 0; sub < SUBS; ++sub) sum[g][sub] = 0.f;
-            for (int s0 = 0; s0 < a.S; s0 += 8) {
-                float p[8][4][SUBS];
-#pragma unroll
-                for (int r = 0; r < 8; ++r)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-#pragma unroll
-                        for (int sub = 0; sub < SUBS; ++sub)
-                            p[r][g][sub] = pt[((size_t)min(s0 + r, a.S - 1) * SUBS + sub) * 1024 + g * 256];
-#pragma unroll
-                for (int r = 0; r < 8; ++r)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-#pragma unroll
-                        for (int sub = 0; sub < SUBS; ++sub) sum[g][sub] += s0 + r < a.S ? p[r][g][sub] : 0.f;
-            }
-        }
-        for (int g = 0; g < 4; ++g) {
-            const int row0 = m0 + g * 16;
-            if (row0 >= M) break;
-            const float sc = inv_rms[g * 16 + (tid >> 4)];
-            float v[2];
-            v[0] = sum[g][0] * sc;
-            v[1] = SUBS == 2 ? sum[g][SUBS - 1] * sc : v[0];
-            tile_epilogue<SUBS>(a, tile, v, row0, min(16, M - row0));
-        }
-    }
-}
-
-hipError_t wsgemv_setup() {
-    hipError_t e1 = hipFuncSetAttribute((const void*)k_pgemm<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPgLds);
-    hipError_t e2 = hipFuncSetAttribute((const void*)k_pgemm<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPgLds);
-    return e1 != hipSuccess ? e1 : e2;
-}
-
 constexpr int kLdsBudget = 160 * 1024 - 2048;
 // Activation bytes a workgroup stages: K is split until each workgroup's slice of the rows fits
 // this (16 rows of 2048 columns would be 128 KB read from L2 by every workgroup for one 64 KB
@@ -711,57 +421,10 @@ WsPlan ws_plan(int M, int N, int K, int mode) {
     return p;
 }
 
-static bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
-    if (c.K % kPgKC) return false;
-    WsArgs a{};
-    a.X = c.X; a.ldx = c.K; a.in_map = c.in_map; a.M = c.M; a.row0 = 0; a.K = c.K;
-    a.gamma = (const uint16_t*)c.gamma; a.eps = c.eps; a.ss = c.ss; a.nss = c.nss;
-    int tiles = 0;
-    for (int i = 0; i < 3; ++i) {
-        a.W[i] = i < c.nseg ? (const uint16_t*)c.W[i] : nullptr;
-        a.seg_tiles[i] = i < c.nseg ? c.seg_rows[i] / 16 : 0;
-        if (c.mode != kEpiSwiglu) tiles += a.seg_tiles[i];
-    }
-    if (c.mode == kEpiSwiglu) tiles = c.seg_rows[0] / 16;
-    a.nseg = c.nseg; a.mode = c.mode; a.tiles = tiles;
-    a.Y = c.Y; a.ldy = c.ldy; a.out_map = c.out_map; a.ss_out = c.ss_out;
-    const int subs0 = c.mode == kEpiSwiglu ? 2 : 1;
-    a.S = pg_split(c.M, tiles * 16, c.K, subs0);
-    {
-        // partials and counters must fit the workspace; else no K split
-        const size_t nblkm = (size_t)(c.M + kPgRows - 1) / kPgRows;
-        if (a.S > 1 && (nblkm * tiles * a.S * subs0 * 1024 > e->ws.ws_part_n || nblkm * tiles > e->ws.ws_cnt_n))
-            a.S = 1;
-    }
-    a.part = c.part;
-    a.cnt = c.cnt;
-    a.H = c.H; a.Hkv = c.Hkv; a.hd = c.hd; a.row_pos = c.row_pos; a.row_seq = c.row_seq;
-    a.rcos = c.rcos; a.rsin = c.rsin; a.qout = c.qout; a.kc = c.kc; a.vc = c.vc;
-    a.cap = c.cap; a.max_batch = c.max_batch; a.layer = c.layer;
-    a.ubias = c.ubias; a.ub_ld = c.ub_ld;
-    const int subs = c.mode == kEpiSwiglu ? 2 : 1;
-    const int nt = 4 * kPgTW / subs;
-    const int nblk_m = (c.M + kPgRows - 1) / kPgRows;
-    const int nblk_n = (tiles + nt - 1) / nt;
-    const int nbs = 8 * nblk_m * ((nblk_n + 7) / 8);
-    dim3 grid(nbs * a.S);
-    const double wbytes = (double)tiles * 16 * subs * c.K * 2.0;
-    ProfEntry* pe = prof_slot(e, kProfGemv, wbytes + (double)c.M * c.K * 4.0 + (double)c.M * tiles * 16 * 4.0);
-    if (subs == 2) {
-        if (pe) hipExtLaunchKernelGGL((k_pgemm<2>), grid, dim3(256), kPgLds, s, pe->a, pe->b, 0, a, nblk_m, nbs);
-        else k_pgemm<2><<<grid, 256, kPgLds, s>>>(a, nblk_m, nbs);
-    } else {
-        if (pe) hipExtLaunchKernelGGL((k_pgemm<1>), grid, dim3(256), kPgLds, s, pe->a, pe->b, 0, a, nblk_m, nbs);
-        else k_pgemm<1><<<grid, 256, kPgLds, s>>>(a, nblk_m, nbs);
-    }
-    if (pe) prof_commit(e);
-    return true;
-}
-
 void launch_wsgemv(Engine* e, hipStream_t s, const WsCall& c) {
-    // more than one 16-row group: the GEMM (weights read once per 64 rows, not per 16); also a
-    // full 16-row group against a vocabulary-sized weight (the batched drafter steps' LM head),
-    // which the GEMM streams faster
+    // more than one 16-row group: the many-row kernel (pgemm.hip), which reads the weights once
+    // per 32 to 128 rows and not per 16; also a full 16-row group against a vocabulary-sized
+    // weight (the batched drafter steps' LM head), which it streams faster
     int nrows = 0;
     for (int i = 0; i < c.nseg; ++i) nrows += c.seg_rows[i];
     if ((c.M > 16 || (c.M == 16 && nrows >= 32768)) && launch_pgemm(e, s, c)) return;
