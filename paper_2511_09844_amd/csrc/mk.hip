@@ -23,6 +23,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "device_common.h"
@@ -133,6 +134,8 @@ __device__ __forceinline__ float mk_wsum(float v) {
 // Row plan of the launch, one entry per activation row (position -1: inactive row).
 struct MkRows {
     int pos[kMkMaxRows], seq[kMkMaxRows], tok[kMkMaxRows];
+    int nl[kMkMaxRows];  // attention: runs the row sees
+    int spu, nrun;       // spans per unit, and runs that hold the launch's live spans
 };
 
 __device__ __forceinline__ void mk_plan(const MkArgs& a, MkRows& rp) {
@@ -401,8 +404,7 @@ __device__ __forceinline__ void mk_gemv(const MkArgs& a, const MkPhase& od, cons
         // sees, all spans' partials requested at once (up to 16 per round trip), then stages them.
         const int HD = a.hd, ns = mk_uni(od.nsplit);
         for (int m = 0; m < M; ++m) {
-            const int pos = rp.pos[m];
-            const int nl = pos >= 0 ? min(ns, pos / kMkSpan + 1) : 0;
+            const int nl = rp.nl[m];
             float sqm = 0.f;
             for (int c = tid; c < n4 && tid < kNT; c += kNT) {
                 const int kk = k0 + 4 * c, h = kk / HD, d = kk % HD;
@@ -747,58 +749,74 @@ struct MkKv {
     float4 k[F4], v[F4];
 };
 
+// A unit walks a run of `spu` neighbouring spans (all units of a launch the same number), chosen so
+// that one pass of units fills the workgroups: with one span per unit a 6000-token context was 9
+// units per workgroup and verifier layer, each paying its own load latency and hand-off, and 94
+// partials per head to merge.
 struct MkAttnUnit {
-    int sp, kvh, sq, qg, q0, nqu, p0, nvalid, nl, newpos;
+    int sp, kvh, sq, qg, q0, nqu, p0, nvalid, nl, newpos;  // sp: run; nvalid: its valid positions
 };
 
-// Spans any row of the launch sees: units are numbered over these only.
-__device__ __forceinline__ int mk_attn_spans(const MkArgs& a, const MkRows& rp, int nsplit) {
+// Spans per unit and runs per group, from the spans some row of the launch sees (one thread, once
+// per launch, after mk_plan).
+__device__ __forceinline__ void mk_attn_plan(const MkArgs& a, MkRows& rp) {
     int mx = -1;
     for (int r = 0; r < a.M; ++r) mx = max(mx, rp.pos[r]);
-    return mx >= 0 ? min(nsplit, mx / kMkSpan + 1) : 1;
+    const int nspan = mx >= 0 ? min(mx, a.cap - 1) / kMkSpan + 1 : 1;
+    const int nq = a.rps * (a.H / a.Hkv), groups = (a.M / a.rps) * a.Hkv * ((nq + kMkQG - 1) / kMkQG);
+    const int runs = max(1, a.G / groups);
+    rp.spu = (nspan + runs - 1) / runs;
+    rp.nrun = (nspan + rp.spu - 1) / rp.spu;
+    for (int r = 0; r < a.M; ++r) rp.nl[r] = rp.pos[r] >= 0 ? min(rp.nrun, rp.pos[r] / (kMkSpan * rp.spu) + 1) : 0;
 }
 
-__device__ __forceinline__ MkAttnUnit mk_attn_unit(const MkArgs& a, const MkRows& rp, int nsplit, int nspan, int u) {
+// nrun: runs that hold the launch's live spans; unit u of them.
+__device__ __forceinline__ MkAttnUnit mk_attn_unit(const MkArgs& a, const MkRows& rp, int nrun, int spu, int u) {
     MkAttnUnit t;
     const int Gq = a.H / a.Hkv, nq = a.rps * Gq, nqg = (nq + kMkQG - 1) / kMkQG;
-    t.sp = u % nspan;
-    int r = u / nspan;
+    t.sp = u % nrun;
+    int r = u / nrun;
     t.qg = r % nqg;
     r /= nqg;
     t.kvh = r % a.Hkv;
     t.sq = r / a.Hkv;
     t.q0 = t.qg * kMkQG;
     t.nqu = min(kMkQG, nq - t.q0);
-    int maxq = -1, minq = 0x7fffffff;
+    int maxq = -1, minq = 0x7fffffff, nl = 0;
     for (int i = 0; i < a.rps; ++i) {
         const int ps = rp.pos[t.sq * a.rps + i];
-        if (i >= t.q0 / Gq && i <= (t.q0 + t.nqu - 1) / Gq) maxq = max(maxq, ps);
+        if (i >= t.q0 / Gq && i <= (t.q0 + t.nqu - 1) / Gq) {
+            maxq = max(maxq, ps);
+            nl = max(nl, rp.nl[t.sq * a.rps + i]);
+        }
         if (ps >= 0) minq = min(minq, ps);
     }
-    t.p0 = t.sp * kMkSpan;
-    t.nvalid = maxq >= t.p0 ? min(kMkSpan, maxq - t.p0 + 1) : 0;
-    // live spans of the group (those holding a position one of its queries sees)
-    t.nl = maxq >= 0 ? min(nsplit, maxq / kMkSpan + 1) : 0;
+    t.p0 = t.sp * spu * kMkSpan;
+    t.nvalid = maxq >= t.p0 ? min(spu * kMkSpan, maxq - t.p0 + 1) : 0;
+    // live runs of the group (those holding a position one of its queries sees)
+    t.nl = nl;
     t.newpos = minq;  // first position this launch appends for the sequence
     return t;
 }
 
-// K and V rows of a unit's span held by this thread: rows older than the launch (fresh = false)
-// or the rows it appends (fresh = true).  Rows past the last valid one re-read it.
+// K and V rows of span c of a unit's run held by this thread: rows older than the launch (fresh =
+// false), the rows it appends (fresh = true), or with `all` both.  Rows past the last valid one
+// re-read it.
 template <int HD>
-__device__ __forceinline__ void mk_attn_kv(const MkArgs& a, const MkRows& rp, int layer, const MkAttnUnit& t, bool fresh,
-                                           MkKv<HD>& kv) {
-    if (t.nvalid == 0) return;
+__device__ __forceinline__ void mk_attn_kv(const MkArgs& a, const MkRows& rp, int layer, const MkAttnUnit& t, int c,
+                                           bool fresh, bool all, MkKv<HD>& kv) {
+    const int p0 = t.p0 + c * kMkSpan, nvalid = t.nvalid - c * kMkSpan;
+    if (nvalid <= 0) return;
     const int tid = mk_tid();
     const size_t head_base = (((size_t)layer * a.max_batch + rp.seq[t.sq * a.rps]) * a.Hkv + t.kvh) * a.cap * HD;
-    const float* kg = a.kc + head_base + (size_t)t.p0 * HD;
-    const float* vg = a.vc + head_base + (size_t)t.p0 * HD;
+    const float* kg = a.kc + head_base + (size_t)p0 * HD;
+    const float* vg = a.vc + head_base + (size_t)p0 * HD;
 #pragma unroll
     for (int i = 0; i < MkKv<HD>::F4; ++i) {
         const int e4 = tid + i * kMkThreads;
         const int j = (e4 * 4) / HD, d = (e4 * 4) % HD;
-        const int jj = j < t.nvalid ? j : t.nvalid - 1;
-        if ((t.p0 + jj >= t.newpos) == fresh) {
+        const int jj = min(j, nvalid - 1);
+        if (all || (p0 + jj >= t.newpos) == fresh) {
             kv.k[i] = mk_ldg4(kg + (size_t)jj * HD + d);
             kv.v[i] = mk_ldg4(vg + (size_t)jj * HD + d);
         }
@@ -841,18 +859,19 @@ __device__ __forceinline__ void mk_attn_t(const MkArgs& a, const MkPhase& od, co
     const int Gq = a.H / a.Hkv;
     const int nq = a.rps * Gq, nqg = (nq + kMkQG - 1) / kMkQG;
     const int nseq = a.M / a.rps;
-    const int nspan = mk_attn_spans(a, rp, o.nsplit);
-    const int nunit = nseq * a.Hkv * nqg * nspan;
+    const int spu = __builtin_amdgcn_readfirstlane(rp.spu), nrun = __builtin_amdgcn_readfirstlane(rp.nrun);
+    const int nunit = nseq * a.Hkv * nqg * nrun;
     constexpr int F4 = MkKv<HD>::F4;
     constexpr int D4 = HD / 4;
     float* qs = (float*)smem;                 // [kMkQG][HD]   pre-scaled queries
     float* ks = qs + kMkQG * HD;              // [kMkSpan][HD+4]
     float* vs = ks + kMkSpan * (HD + 4);      // [kMkSpan][HD]
     float* ps = vs + kMkSpan * HD;            // [kMkQG][kMkSpan] probabilities
-    float* mq = ps + kMkSpan * kMkQG;         // [kMkQG] span max
-    float* lq = mq + kMkQG;                   // [kMkQG] span sum
+    float* mq = ps + kMkSpan * kMkQG;         // [kMkQG] running max
+    float* lq = mq + kMkQG;                   // [kMkQG] running sum
+    float* cq = lq + kMkQG;                   // [kMkQG] rescaling of the sums before this span
     for (int u = blockIdx.x; u < nunit; u += a.G) {
-        const MkAttnUnit t = mk_attn_unit(a, rp, o.nsplit, nspan, u);
+        const MkAttnUnit t = mk_attn_unit(a, rp, nrun, spu, u);
         const int sp = t.sp, kvh = t.kvh, sq = t.sq, nl = t.nl, nvalid = t.nvalid, q0 = t.q0, nqu = t.nqu;
         if (nl == 0 && sp == 0) {
             // no live position (padding): the outputs are zero
@@ -864,11 +883,9 @@ __device__ __forceinline__ void mk_attn_t(const MkArgs& a, const MkPhase& od, co
         if (nvalid == 0) continue;  // dead span: no work and no hand-off
         {
             // rows of this launch (and, past the first unit, all rows) and the queries
-            if (u != (int)blockIdx.x) {
-                if (kv_want) mk_kv_wait(a, kvh, kv_want, spins);
-                mk_attn_kv<HD>(a, rp, o.layer, t, false, kv);
-            }
-            mk_attn_kv<HD>(a, rp, o.layer, t, true, kv);
+            const bool later = u != (int)blockIdx.x;
+            if (later && kv_want) mk_kv_wait(a, kvh, kv_want, spins);
+            mk_attn_kv<HD>(a, rp, o.layer, t, 0, true, later, kv);
             constexpr int Q4 = (kMkQG * D4 + kMkThreads - 1) / kMkThreads;  // float4 of queries per thread
             float4 qv4[Q4];
 #pragma unroll
@@ -879,88 +896,113 @@ __device__ __forceinline__ void mk_attn_t(const MkArgs& a, const MkPhase& od, co
                 const int row = sq * a.rps + qv / Gq, h = kvh * Gq + qv % Gq;
                 qv4[i] = mk_ldg4(o.qout + (size_t)row * a.H * HD + h * HD + d);
             }
-#pragma unroll
-            for (int i = 0; i < F4; ++i) {
-                const int e4 = tid + i * kMkThreads;
-                const int j = (e4 * 4) / HD, d = (e4 * 4) % HD;
-                *(float4*)(ks + j * (HD + 4) + d) = kv.k[i];
-                *(float4*)(vs + j * HD + d) = kv.v[i];
-            }
-#pragma unroll
-            for (int i = 0; i < Q4; ++i) {
-                const int e = tid + i * kMkThreads;
-                const float4 v = qv4[i];
-                if (e < kMkQG * D4) *(float4*)(qs + 4 * e) = make_float4(v.x * a.scale, v.y * a.scale, v.z * a.scale, v.w * a.scale);
-            }
-            __syncthreads();
-            // scores and probabilities: wave w takes query vector w of the group, lane = position
-            if (wave < nqu) {
-                // blocks of 32 head dims: all of a block's K and query words are requested from LDS
-                // before its products (two accumulators)
-                float sc0 = 0.f, sc1 = 0.f;
-                const float4* kr = (const float4*)(ks + lane * (HD + 4));
-                const float4* qr = (const float4*)(qs + wave * HD);
-#pragma unroll 1
-                for (int d0 = 0; d0 < D4; d0 += 8) {
-                    float4 kx[8], qx[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        kx[i] = kr[d0 + i];
-                        qx[i] = qr[d0 + i];
-                    }
-#pragma unroll
-                    for (int i = 0; i < 8; i += 2) {
-                        sc0 += qx[i].x * kx[i].x + qx[i].y * kx[i].y + qx[i].z * kx[i].z + qx[i].w * kx[i].w;
-                        sc1 += qx[i + 1].x * kx[i + 1].x + qx[i + 1].y * kx[i + 1].y + qx[i + 1].z * kx[i + 1].z +
-                               qx[i + 1].w * kx[i + 1].w;
-                    }
-                }
-                const float sc = sc0 + sc1;
-                const int qv = q0 + wave;
-                const int qp = rp.pos[sq * a.rps + qv / Gq];
-                const float v = (lane < nvalid && t.p0 + lane <= qp) ? sc : -INFINITY;
-                const float mx = mk_wmax(v);
-                const float pr = v == -INFINITY ? 0.f : expf(v - mx);
-                const float sm = mk_wsum(pr);
-                ps[wave * kMkSpan + lane] = pr;  // [query][position]
-                if (lane == 0) {
-                    mq[wave] = mx;
-                    lq[wave] = sm;
-                }
-            }
-            __syncthreads();
             // un-normalised outputs: a thread per (query vector, head dim), NI vectors kMkThreads / HD
             // apart; a position's probability is a broadcast read, its V element is read once
             constexpr int STEP = kMkThreads / HD;  // vectors between a thread's items
             constexpr int NI = (kMkQG + STEP - 1) / STEP;
             static_assert(NI == 1 || NI * STEP == kMkQG, "a thread's items stay inside the group");
             const int d = tid % HD, qi0 = tid / HD;  // qi0 < STEP
-            if (qi0 < nqu) {
-                float acc[NI];
+            float acc[NI];
 #pragma unroll
-                for (int i = 0; i < NI; ++i) acc[i] = 0.f;
-                // blocks of 16 positions: V elements and probabilities are all requested from LDS
-                // before the block's products
-#pragma unroll 1
-                for (int j0 = 0; j0 < kMkSpan; j0 += 16) {
-                    float vv[16];
-                    float4 pp[NI][4];
+            for (int i = 0; i < NI; ++i) acc[i] = 0.f;
+            float m_run = -INFINITY, l_run = 0.f;  // of query vector `wave`
+            const int nsp = (nvalid + kMkSpan - 1) / kMkSpan;
+            // One span of the run, from the registers.  The first is a copy of its own: in one loop
+            // with the others it took 1 to 2 us more per phase at short contexts.
+            auto span = [&](int c, auto first_t) {
+                constexpr bool FIRST = decltype(first_t)::value;
+                if constexpr (!FIRST) __syncthreads();  // the previous span's LDS is free
 #pragma unroll
-                    for (int jj = 0; jj < 16; ++jj) vv[jj] = vs[(j0 + jj) * HD + d];
-#pragma unroll
-                    for (int i = 0; i < NI; ++i)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) pp[i][k] = *(const float4*)(ps + (qi0 + i * STEP) * kMkSpan + j0 + 4 * k);
-#pragma unroll
-                    for (int i = 0; i < NI; ++i)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            acc[i] += pp[i][k].x * vv[4 * k];
-                            acc[i] += pp[i][k].y * vv[4 * k + 1];
-                            acc[i] += pp[i][k].z * vv[4 * k + 2];
-                            acc[i] += pp[i][k].w * vv[4 * k + 3];
-                        }
+                for (int i = 0; i < F4; ++i) {
+                    const int e4 = tid + i * kMkThreads;
+                    const int j = (e4 * 4) / HD, dd = (e4 * 4) % HD;
+                    *(float4*)(ks + j * (HD + 4) + dd) = kv.k[i];
+                    *(float4*)(vs + j * HD + dd) = kv.v[i];
                 }
+                if constexpr (FIRST) {
+#pragma unroll
+                    for (int i = 0; i < Q4; ++i) {
+                        const int e = tid + i * kMkThreads;
+                        const float4 v = qv4[i];
+                        if (e < kMkQG * D4)
+                            *(float4*)(qs + 4 * e) = make_float4(v.x * a.scale, v.y * a.scale, v.z * a.scale, v.w * a.scale);
+                    }
+                }
+                __syncthreads();
+                if (c + 1 < nsp) mk_attn_kv<HD>(a, rp, o.layer, t, c + 1, false, true, kv);
+                // scores and probabilities: wave w takes query vector w of the group, lane = position
+                if (wave < nqu) {
+                    // blocks of 32 head dims: all of a block's K and query words are requested from LDS
+                    // before its products (two accumulators)
+                    float sc0 = 0.f, sc1 = 0.f;
+                    const float4* kr = (const float4*)(ks + lane * (HD + 4));
+                    const float4* qr = (const float4*)(qs + wave * HD);
+#pragma unroll 1
+                    for (int d0 = 0; d0 < D4; d0 += 8) {
+                        float4 kx[8], qx[8];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            kx[i] = kr[d0 + i];
+                            qx[i] = qr[d0 + i];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 8; i += 2) {
+                            sc0 += qx[i].x * kx[i].x + qx[i].y * kx[i].y + qx[i].z * kx[i].z + qx[i].w * kx[i].w;
+                            sc1 += qx[i + 1].x * kx[i + 1].x + qx[i + 1].y * kx[i + 1].y + qx[i + 1].z * kx[i + 1].z +
+                                   qx[i + 1].w * kx[i + 1].w;
+                        }
+                    }
+                    const float sc = sc0 + sc1;
+                    const int qv = q0 + wave;
+                    const int qp = rp.pos[sq * a.rps + qv / Gq], pj = c * kMkSpan + lane;
+                    const float v = (pj < nvalid && t.p0 + pj <= qp) ? sc : -INFINITY;
+                    const float mx = FIRST ? mk_wmax(v) : fmaxf(m_run, mk_wmax(v));
+                    const float pr = v == -INFINITY ? 0.f : expf(v - mx);
+                    // the sums so far, at the new maximum (nothing seen yet: nothing to scale)
+                    const float cr = FIRST || m_run == -INFINITY ? 0.f : expf(m_run - mx);
+                    l_run = FIRST ? mk_wsum(pr) : l_run * cr + mk_wsum(pr);
+                    m_run = mx;
+                    ps[wave * kMkSpan + lane] = pr;  // [query][position]
+                    if (lane == 0) {
+                        mq[wave] = m_run;
+                        lq[wave] = l_run;
+                        if constexpr (!FIRST) cq[wave] = cr;
+                    }
+                }
+                __syncthreads();
+                if (qi0 < nqu) {
+                    if constexpr (!FIRST) {
+#pragma unroll
+                        for (int i = 0; i < NI; ++i) acc[i] *= qi0 + i * STEP < nqu ? cq[qi0 + i * STEP] : 0.f;
+                    }
+                    // blocks of 16 positions: V elements and probabilities are all requested from LDS
+                    // before the block's products
+#pragma unroll 1
+                    for (int j0 = 0; j0 < kMkSpan; j0 += 16) {
+                        float vv[16];
+                        float4 pp[NI][4];
+#pragma unroll
+                        for (int jj = 0; jj < 16; ++jj) vv[jj] = vs[(j0 + jj) * HD + d];
+#pragma unroll
+                        for (int i = 0; i < NI; ++i)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) pp[i][k] = *(const float4*)(ps + (qi0 + i * STEP) * kMkSpan + j0 + 4 * k);
+#pragma unroll
+                        for (int i = 0; i < NI; ++i)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                acc[i] += pp[i][k].x * vv[4 * k];
+                                acc[i] += pp[i][k].y * vv[4 * k + 1];
+                                acc[i] += pp[i][k].z * vv[4 * k + 2];
+                                acc[i] += pp[i][k].w * vv[4 * k + 3];
+                            }
+                    }
+                }
+            };
+            span(0, std::true_type{});
+#pragma unroll 1
+            for (int c = 1; c < nsp; ++c) span(c, std::false_type{});
+            if (qi0 < nqu) {
 #pragma unroll
                 for (int i = 0; i < NI; ++i) {
                     const int qi = qi0 + i * STEP;
@@ -1084,22 +1126,22 @@ template <int HD>
 __device__ __forceinline__ void mk_attn_phase(const MkArgs& a, const MkPhase& od, const MkRows& rp, char* smem,
                                               int* last_flag, int& gen, long& spins, int p) {
     MkKv<HD> kv;
-    const int nsplit = mk_uni(od.nsplit), layer = mk_uni(od.layer);
+    const int layer = mk_uni(od.layer);
     const int nq = a.rps * (a.H / a.Hkv);
-    const int nspan = mk_attn_spans(a, rp, nsplit);
-    const int nunit = (a.M / a.rps) * a.Hkv * ((nq + kMkQG - 1) / kMkQG) * nspan;
+    const int spu = __builtin_amdgcn_readfirstlane(rp.spu), nrun = __builtin_amdgcn_readfirstlane(rp.nrun);
+    const int nunit = (a.M / a.rps) * a.Hkv * ((nq + kMkQG - 1) / kMkQG) * nrun;
     const bool first = (int)blockIdx.x < nunit;
     MkAttnUnit t{};
-    if (first) t = mk_attn_unit(a, rp, nsplit, nspan, blockIdx.x);
+    if (first) t = mk_attn_unit(a, rp, nrun, spu, blockIdx.x);
     const int kvwait = mk_uni(od.kvwait);
     const unsigned want = a.qc_base + (unsigned)(layer + 1) * (unsigned)a.qc_tpk;
-    if (first && threadIdx.x >= 64) mk_attn_kv<HD>(a, rp, layer, t, false, kv);
+    if (first && threadIdx.x >= 64) mk_attn_kv<HD>(a, rp, layer, t, 0, false, false, kv);
     if (!kvwait) {
         if (p > 0) mk_barrier(a, gen, spins, nullptr, nullptr);
     } else if (first && t.nvalid > 0) {
         mk_kv_wait(a, t.kvh, want, spins);  // only this unit's KV head: no grid barrier
     }
-    if (first && threadIdx.x < 64) mk_attn_kv<HD>(a, rp, layer, t, false, kv);
+    if (first && threadIdx.x < 64) mk_attn_kv<HD>(a, rp, layer, t, 0, false, false, kv);
     mk_attn_t<HD>(a, od, rp, smem, last_flag, kv, kvwait ? want : 0u, spins);
 }
 
@@ -1120,6 +1162,8 @@ __global__ __launch_bounds__(kMkThreads) void k_mk(MkArgs a) {
     static_assert(sizeof(MkPhase) % 4 == 0 && kWords <= 64, "phase descriptor larger than one wave");
     mk_plan(a, rp);
     if (threadIdx.x < kWords) ((uint32_t*)&op_lds[0])[threadIdx.x] = mk_ldu((const uint32_t*)&a.prog[0] + threadIdx.x);
+    __syncthreads();
+    if (threadIdx.x == 0) mk_attn_plan(a, rp);
     __syncthreads();
     int gen = (int)a.bar_gen;
     long spins = 0;
@@ -1198,7 +1242,7 @@ MkPlanG mk_plan_gemv(int M, int N, int K, bool norm, int subs) {
 
 size_t mk_attn_lds(int hd) {
     return sizeof(float) * ((size_t)kMkQG * hd + (size_t)kMkSpan * (hd + 4) + (size_t)kMkSpan * hd +
-                            (size_t)kMkQG * kMkSpan + 2 * kMkQG);
+                            (size_t)kMkQG * kMkSpan + 3 * kMkQG);
 }
 
 struct Arena {
