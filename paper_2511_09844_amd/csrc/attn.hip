@@ -1,16 +1,9 @@
-// Grouped-query causal attention over the fp32 KV cache for a block of query rows.
-//
-// Split over cache positions (flash-decoding): one workgroup owns up to 32 query vectors of one
-// sequence -- either one query head for a tile of rows (small batches: more workgroups, the KV
-// head shared through L2) or all query heads of one KV head (large batches: each cached K/V
-// row read once) -- and one span of kSplit cache positions.  It walks its span in chunks of 64
-// positions with an online softmax (running max, running sum, rescaled output), keeping the
-// next chunk's K/V in flight in registers while the current chunk is scored from LDS, and
-// writes an un-normalised partial (output, max, sum); the last span to finish for a set of
-// query vectors merges all spans in span order (see arrive_last).  The causal mask is key position <= query position; rows
-// with position -1 are inactive and produce zeros.  Workgroups of one KV head are placed on
-// the same XCD (workgroup ids are dealt round-robin over the 8 XCDs), so a KV head is fetched
-// into one L2 only.
+// Grouped-query causal attention over the fp32 KV cache for a block of query rows per sequence:
+// k_vattn for few rows (decode steps, verify passes), k_pattn for many (prefill chunks, the
+// training objective).  Both split the cache positions of a group over workgroups where that fills
+// the chip (every span writes an un-normalised output, max and sum, and the last one to arrive
+// merges them in span order, see arrive_last).  The causal mask is key position <= query position;
+// rows with position -1 are inactive and produce zeros.
 #include <math.h>
 
 #include <algorithm>
@@ -19,269 +12,40 @@
 
 #include "device_common.h"
 #include "engine.h"
+#include "pgemm.h"
 
 namespace sd2 {
 
-constexpr int kAttnCL = 64;   // cache positions per chunk
-constexpr int kSplit = 128;   // cache positions per workgroup
-constexpr int kAttnQT = 32;   // query vectors per workgroup
-constexpr int kAttnT = 256;
-constexpr int kXcds = 8;
-
-typedef float f4_t __attribute__((ext_vector_type(4)));
+constexpr int kSplit = 128;   // cache positions of the smallest span: the partials have room for spans of these
 
 struct AttnArgs {
     const float* q;
     int q_stride;
     const float *kc, *vc;
     float* out;
+    uint16_t* planes;  // output as planes of Mp rows (see pgemm.hip), in place of out; or null
+    int Mp;
     const int32_t* row_pos;
     int rps, H, Hkv, hd, cap, max_batch, layer;
-    int hp;     // query heads per workgroup: 1 or H/Hkv
-    int nrt;    // row tiles per (sequence, head group)
-    int ngrp;   // number of (sequence, KV head, row tile) groups
-    int nsplit; // position spans per group
+    int nseq;   // sequences
+    int nsplit; // spans the partials have room for
     float scale;
-    float* part;     // [row][head][nsplit][HD + 2]
+    float* part;     // k_pattn: [row][head][nsplit][HD + 2]
     int32_t* cnt;    // one arrival counter per workgroup of the split-free grid
 };
 
-// Wave-wide max and sum with DPP steps (quad permutes, row mirrors, row broadcasts), every lane
-// active; the result is read from lane 63 and is uniform.  xor shuffles through LDS took six
-// dependent LDS round trips per reduction.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float at_dpp(float old, float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v),
-                                                                 CTRL, ROWS, 0xf, false));
+// One output value, or four neighbouring ones: column c of row `row`.
+__device__ __forceinline__ void attn_put1(const AttnArgs& a, size_t row, int c, float v) {
+    if (a.planes) pg_put1(a.planes, a.Mp, row, c, v);
+    else a.out[row * a.H * a.hd + c] = v;
 }
-__device__ __forceinline__ float at_wmax(float v) {
-    v = fmaxf(v, at_dpp<0xB1, 0xf>(v, v));   // quad_perm [1,0,3,2]
-    v = fmaxf(v, at_dpp<0x4E, 0xf>(v, v));   // quad_perm [2,3,0,1]
-    v = fmaxf(v, at_dpp<0x141, 0xf>(v, v));  // row_half_mirror
-    v = fmaxf(v, at_dpp<0x140, 0xf>(v, v));  // row_mirror
-    v = fmaxf(v, at_dpp<0x142, 0xa>(v, v));  // row_bcast:15 into rows 1 and 3
-    v = fmaxf(v, at_dpp<0x143, 0xc>(v, v));  // row_bcast:31 into rows 2 and 3
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-__device__ __forceinline__ float at_wsum(float v) {
-    v += at_dpp<0xB1, 0xf>(0.f, v);
-    v += at_dpp<0x4E, 0xf>(0.f, v);
-    v += at_dpp<0x141, 0xf>(0.f, v);
-    v += at_dpp<0x140, 0xf>(0.f, v);
-    v += at_dpp<0x142, 0xa>(0.f, v);
-    v += at_dpp<0x143, 0xc>(0.f, v);
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-
-// Request chunk c of K and V (positions past maxpos re-read the last valid row; they are masked).
-template <int HD, int F4>
-__device__ __forceinline__ void fetch_chunk(f4_t (&pk)[F4], f4_t (&pv)[F4], const float* kg, const float* vg,
-                                            int c, int maxpos, int tid) {
-#pragma unroll
-    for (int i = 0; i < F4; ++i) {
-        int e4 = tid + i * kAttnT;  // float4 index within the chunk
-        int pos = c * kAttnCL + (e4 * 4) / HD;
-        int pp = pos <= maxpos ? pos : maxpos;
-        pk[i] = *(const f4_t*)(kg + (size_t)pp * HD + (e4 * 4) % HD);
-        pv[i] = *(const f4_t*)(vg + (size_t)pp * HD + (e4 * 4) % HD);
-    }
-}
-
-template <int HD, int QT>
-__global__ __launch_bounds__(kAttnT) void k_attn(AttnArgs a) {
-    extern __shared__ __attribute__((aligned(16))) float sm[];
-    __shared__ int qpos[QT];
-    __shared__ int qrow[QT];
-    __shared__ int qhead[QT];
-    __shared__ float mrun[QT], lrun[QT], rescale[QT];
-    __shared__ int maxpos_s;
-    __shared__ int last_flag;
-    const int tid = threadIdx.x;
-    const int G = a.H / a.Hkv;
-    const int members = G / a.hp;  // workgroups per group
-    // XCD-aware decode: the `members` workgroups of a group share wg % 8
-    const int wg = blockIdx.x / a.nsplit;
-    const int sp = blockIdx.x % a.nsplit;
-    const int gi = (wg / (kXcds * members)) * kXcds + wg % kXcds;
-    const int mi = (wg / kXcds) % members;
-    if (gi >= a.ngrp) return;
-    const int rt = gi % a.nrt;
-    const int kvh = (gi / a.nrt) % a.Hkv;
-    const int b = gi / (a.nrt * a.Hkv);
-    const int hbase = kvh * G + mi * a.hp;
-    const int rows_per_tile = QT / a.hp;
-    const int r0 = rt * rows_per_tile;
-    const int nrows = min(rows_per_tile, a.rps - r0);
-    const int nq = nrows * a.hp;
-
-    float* qs = sm;                          // [QT][HD]   (pre-scaled queries)
-    float* ks = qs + QT * HD;           // [CL][HD+1]
-    float* vs = ks + kAttnCL * (HD + 1);     // [CL][HD]
-    float* ps = vs + kAttnCL * HD;           // [QT][CL]
-
-    if (tid == 0) maxpos_s = -1;
-    __syncthreads();
-    if (tid < QT) {
-        int p = -1, row = 0, h = 0;
-        if (tid < nq) {
-            row = b * a.rps + r0 + tid / a.hp;
-            h = hbase + tid % a.hp;
-            p = a.row_pos[row];
-        }
-        qpos[tid] = p;
-        qrow[tid] = row;
-        qhead[tid] = h;
-        mrun[tid] = -INFINITY;
-        lrun[tid] = 0.f;
-        if (p >= 0) atomicMax(&maxpos_s, p);
-    }
-    __syncthreads();
-    // Spans past the group's last row position take no part (every workgroup of the group
-    // derives the same live-span count from the row positions, and only live spans count in);
-    // a group without any active row has its zero outputs written by span 0.
-    const int nlive = maxpos_s >= 0 ? min(a.nsplit, maxpos_s / kSplit + 1) : 0;
-    if (nlive == 0) {
-        if (sp == 0)
-            for (int idx = tid; idx < nq * HD; idx += kAttnT) {
-                const int qi = idx / HD, d = idx % HD;
-                a.out[(size_t)qrow[qi] * a.H * HD + qhead[qi] * HD + d] = 0.f;
-            }
-        return;
-    }
-    if (sp >= nlive) return;
-    const int p_lo = sp * kSplit;
-    const int maxpos = min(maxpos_s, p_lo + kSplit - 1);  // last position this span scores
-    for (int idx = tid; idx < nq * HD; idx += kAttnT) {
-        int qi = idx / HD, d = idx % HD;
-        qs[idx] = a.q[(size_t)qrow[qi] * a.q_stride + qhead[qi] * HD + d] * a.scale;
-    }
-    const size_t head_base = (((size_t)a.layer * a.max_batch + b) * a.Hkv + kvh) * a.cap * HD;
-    const float* kg = a.kc + head_base;
-    const float* vg = a.vc + head_base;
-
-    // output accumulators: thread owns dims d = tid % HD of query vectors qi = tid / HD + j * (T / HD)
-    constexpr int QSTEP = kAttnT / HD;
-    constexpr int NACC = QT / QSTEP;
-    float acc[NACC];
-#pragma unroll
-    for (int j = 0; j < NACC; ++j) acc[j] = 0.f;
-    const int od = tid % HD, oq0 = tid / HD;
-
-    // K/V chunk prefetch: each thread moves CL*HD/T float4 pairs per chunk
-    constexpr int F4 = kAttnCL * HD / 4 / kAttnT;
-    f4_t pk[F4], pv[F4];
-    const int nchunks = maxpos >= p_lo ? (maxpos - p_lo) / kAttnCL + 1 : 0;
-    const float* kgs = kg + (size_t)p_lo * HD;
-    const float* vgs = vg + (size_t)p_lo * HD;
-    if (nchunks > 0) fetch_chunk<HD, F4>(pk, pv, kgs, vgs, 0, maxpos - p_lo, tid);
-    for (int c = 0; c < nchunks; ++c) {
-        __syncthreads();  // previous chunk fully consumed
-#pragma unroll
-        for (int i = 0; i < F4; ++i) {
-            int e4 = tid + i * kAttnT;
-            int j = (e4 * 4) / HD, d = (e4 * 4) % HD;
-            float* kd = ks + j * (HD + 1) + d;
-            kd[0] = pk[i][0]; kd[1] = pk[i][1]; kd[2] = pk[i][2]; kd[3] = pk[i][3];
-            *(f4_t*)(vs + j * HD + d) = pv[i];
-        }
-        __syncthreads();
-        if (c + 1 < nchunks) fetch_chunk<HD, F4>(pk, pv, kgs, vgs, c + 1, maxpos - p_lo, tid);
-        const int j0 = p_lo + c * kAttnCL;
-        // scores of every (query, key) pair of the chunk; 64 threads per query vector
-        for (int idx = tid; idx < nq * kAttnCL; idx += kAttnT) {
-            int qi = idx / kAttnCL, j = idx % kAttnCL;
-            float s = -INFINITY;
-            if (j0 + j <= qpos[qi]) {
-                const float* qr = qs + qi * HD;
-                const float* kr = ks + j * (HD + 1);
-                float d0 = 0.f;
-#pragma unroll 8
-                for (int d = 0; d < HD; ++d) d0 += qr[d] * kr[d];
-                s = d0;
-            }
-            // row max and sum over the 64 keys held by this wave's 64 lanes
-            float mx = at_wmax(s);
-            float mnew = fmaxf(mrun[qi], mx);
-            float p = (s == -INFINITY) ? 0.f : expf(s - mnew);
-            float sum = at_wsum(p);
-            ps[qi * kAttnCL + j] = p;
-            if (j == 0) {
-                float sc = mrun[qi] == -INFINITY ? 0.f : expf(mrun[qi] - mnew);
-                rescale[qi] = sc;
-                lrun[qi] = lrun[qi] * sc + sum;
-                mrun[qi] = mnew;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int jj = 0; jj < NACC; ++jj) {
-            int qi = oq0 + jj * QSTEP;
-            if (qi < nq) {
-                float o = acc[jj] * rescale[qi];
-                const float* pr = ps + qi * kAttnCL;
-#pragma unroll 8
-                for (int j = 0; j < kAttnCL; ++j) o += pr[j] * vs[j * HD + od];
-                acc[jj] = o;
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int jj = 0; jj < NACC; ++jj) {
-        int qi = oq0 + jj * QSTEP;
-        if (qi < nq) {
-            float* pp = a.part + (((size_t)qrow[qi] * a.H + qhead[qi]) * a.nsplit + sp) * (HD + 2);
-            store_through(pp + od, acc[jj]);
-            if (od == 0) {
-                store_through(pp + HD, mrun[qi]);
-                store_through(pp + HD + 1, lrun[qi]);
-            }
-        }
-    }
-    // the last live span of these query vectors to finish merges them in span order
-    if (!arrive_last(a.cnt + wg, nlive, &last_flag)) return;
-    for (int idx = tid; idx < nq * HD; idx += kAttnT) {
-        int qi = idx / HD, d = idx % HD;
-        int pos = qpos[qi];
-        float res = 0.f;
-        if (pos >= 0) {
-            const float* pp = a.part + ((size_t)qrow[qi] * a.H + qhead[qi]) * a.nsplit * (HD + 2);
-            // batches of 16 spans, every load of a batch issued before any is used (loads past
-            // nlive re-read the last live span and are not added; a load behind a "live" test
-            // would cost one memory round trip each), folded into a running maximum and sums
-            float M = -INFINITY, L = 0.f, O = 0.f;
-            for (int s0 = 0; s0 < nlive; s0 += 16) {
-                float mv[16], lv[16], ov[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float* e = pp + (size_t)min(s0 + i, nlive - 1) * (HD + 2);
-                    mv[i] = e[HD];
-                    lv[i] = e[HD + 1];
-                    ov[i] = e[d];
-                }
-                float Mn = M;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) Mn = s0 + i < nlive ? fmaxf(Mn, mv[i]) : Mn;
-                const float sc = M == -INFINITY ? 0.f : expf(M - Mn);
-                L *= sc;
-                O *= sc;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const bool live = s0 + i < nlive && mv[i] != -INFINITY;
-                    const float w = live ? expf(mv[i] - Mn) : 0.f;
-                    L += w * lv[i];
-                    O += w * ov[i];
-                }
-                M = Mn;
-            }
-            res = L > 0.f ? O / L : 0.f;
-        }
-        a.out[(size_t)qrow[qi] * a.H * HD + qhead[qi] * HD + d] = res;
-    }
+__device__ __forceinline__ void attn_put4(const AttnArgs& a, size_t row, int c, float4 v) {
+    if (a.planes) pg_put4(a.planes, a.Mp, row, c, v);
+    else *(float4*)(a.out + row * a.H * a.hd + c) = v;
 }
 
 // ---------------------------------------------------------------------------------------------
-// Blocks of many rows per sequence (verify passes of 8 or more rows, prefill chunks, the
+// Blocks of many rows per sequence (prefill chunks, the
 // training-objective forward): causal flash attention on fp32 matrix cores.  A workgroup owns
 // 16 consecutive query rows of one sequence, one KV head and one span of key tiles; each of its
 // 4 waves takes the query heads wave, wave + 4, ... of that KV head.  Per 16-position key tile,
@@ -303,7 +67,6 @@ __global__ __launch_bounds__(kAttnT) void k_attn(AttnArgs a) {
 constexpr int kPaQ = 16;                  // query rows per workgroup
 constexpr int kPaK = 16;                  // key positions per tile
 constexpr int kPaMaxSpans = 16;           // spans per group (one merge batch)
-constexpr int kPaMinRows = 8;             // rows per sequence from which blocks take k_pattn
 typedef float pf4 __attribute__((ext_vector_type(4)));
 typedef float pf2 __attribute__((ext_vector_type(2)));
 
@@ -365,7 +128,7 @@ __device__ void pa_span_merge(const AttnArgs& a, int grp_id, int nspan, int span
             const float inv = L > 0.f ? 1.f / L : 0.f;
             res = make_float4(res.x * inv, res.y * inv, res.z * inv, res.w * inv);
         }
-        *(float4*)(a.out + orow * a.H * HD + h * HD + d) = res;
+        attn_put4(a, orow, h * HD + d, res);
     }
 }
 
@@ -560,7 +323,7 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
                 for (int j = 0; j < RW; ++j) {
                     const int d = lane + 64 * j;
                     if (i0 + i < a.rps && d < HD) {
-                        if (nspan == 1) a.out[orow * a.H * HD + h * HD + d] = rv[i][j];
+                        if (nspan == 1) attn_put1(a, orow, h * HD + d, rv[i][j]);
                         else store_through(a.part + ((orow * a.H + h) * a.nsplit + sp) * (HD + 2) + d, rv[i][j]);
                     }
                 }
@@ -571,263 +334,292 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
     pa_span_merge<HD>(a, grp_id, nspan, span_t, ntile_all, b, kvh, i0, qpos, &last_flag);
 }
 
-// Verify blocks of exactly 8 rows per sequence (k = 7), 4n query heads per KV head: two heads
-// of 8 rows fill the 16 query columns of one S^T tile, so a key tile costs half the matrix work
-// of the one-head layout (whose columns 8-15 would be empty).  Waves 0 and 1 take head pairs
-// (0, 1) and (2, 3) of each pass of four heads over the even key tiles of the span, waves 2 and
-// 3 the same pairs over the odd tiles; two tiles are staged per barrier pair.  The odd-tile wave
-// of a pair hands its running max, sum and output to the even-tile wave through LDS (same lane
-// layout), which merges them and stores the rows.  Arithmetic per product as in k_pattn.
-template <int HD>
-__global__ __launch_bounds__(256) void k_pattn_pk(AttnArgs a, int nspan, int span_t) {
-    constexpr int KL = HD + 4;
-    constexpr int F4 = (kPaK * HD / 4 + 255) / 256;
-    constexpr int QD = HD / 4;
-    constexpr int VD = HD / 16;
-    static_assert(QD % 4 == 0 && (VD % 4 == 0 || VD == 2), "head dim");
-    __shared__ __attribute__((aligned(16))) float ks[2][kPaK * KL];
-    __shared__ __attribute__((aligned(16))) float vs[2][kPaK * KL];
-    __shared__ __attribute__((aligned(16))) float ot[2 * kPaQ * KL];  // per head pair: hand-off, then O rows
-    __shared__ float mlh[2][2][64];                                    // per head pair: max, sum per lane
-    __shared__ int qpos[kPaQ];
-    __shared__ int maxpos_s;
+// ---------------------------------------------------------------------------------------------
+// Blocks of fewer than 16 rows per sequence (decode steps, verify passes): flash attention on fp32
+// matrix cores over packed query vectors.  The rps x G vectors (row, query head) of a sequence
+// and KV head fill the 16 query columns of the products without gaps (rows alone would leave
+// 16 - rps of them empty for every head); a workgroup owns up to 16 NT of them and one span of
+// key tiles, and its 4 waves take the span's 16-key tiles in turn.
+//
+// A wave reads K and V from memory straight in the operand layout, with no LDS and no barrier in
+// the key loop: S^T = K Q^T walks the head dimension as dim = 16 s4 + 4 g + e (lane group g, step
+// 4 s4 + e), so that the four lanes of a key read 64 adjacent bytes per load, and O^T += V^T P^T
+// numbers the output dims as 64 t4 + 4 i + e (tile row i, tile 4 t4 + e), so that the 16 lanes of
+// a key read 256.  An operand register is refilled for the wave's next tile as soon as its products
+// are issued.  The online softmax stays in registers (see k_pattn); the waves' sums are merged
+// through LDS, and the last live span of a group to arrive merges the spans.
+//
+// Bound: K/V bytes at long contexts, one tile's chain of load, products and softmax at short ones.
+// ---------------------------------------------------------------------------------------------
+constexpr int kVaMaxRows = 15;  // rows per sequence up to which blocks run here
+constexpr int kVaMinTiles = 8;  // key tiles per span at least (two per wave)
+
+template <int HD, int NT>
+__global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan, int span_t) {
+    constexpr int QD = HD / 4;                  // S^T steps: head dims per lane group
+    constexpr int VD = HD / 16;                 // O^T tiles
+    constexpr int VV = VD < 4 ? VD : 4;         // V values per load
+    constexpr int NO = NT * VD * 4 / VV;        // groups of VV adjacent output dims per lane
+    typedef float vv_t __attribute__((ext_vector_type(VV)));
+    __shared__ __attribute__((aligned(16))) float os[4][NO][64 * VV];
+    __shared__ float ms[4][16 * NT], ls[4][16 * NT];
     __shared__ int last_flag;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = a.H / a.Hkv;
-    const int grp_id = blockIdx.x / nspan, sp = blockIdx.x % nspan;
-    const int kvh = grp_id % a.Hkv;
-    const int b = grp_id / a.Hkv;
-    if (tid == 0) maxpos_s = -1;
-    __syncthreads();
-    if (tid < kPaQ) {
-        int p = -1;
-        if (tid < 8) p = a.row_pos[b * 8 + tid];
-        qpos[tid] = p;
-        if (p >= 0) atomicMax(&maxpos_s, p);
-    }
-    __syncthreads();
-    const int maxpos = maxpos_s;
-    const int ntile_all = maxpos >= 0 ? maxpos / kPaK + 1 : 0;
-    const int t0 = nspan == 1 ? 0 : sp * span_t;
-    const int t1 = nspan == 1 ? ntile_all : min(ntile_all, t0 + span_t);
-    const size_t kvoff = (((size_t)a.layer * a.max_batch + b) * a.Hkv + kvh) * (size_t)a.cap * HD;
-    const float* kg = a.kc + kvoff;
-    const float* vg = a.vc + kvoff;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    const int pr = wave & 1, half = wave >> 1;  // head pair of the pass, key-tile parity
-    const int myq = qpos[col & 7];              // column col: row col % 8 of head 2 pr + col / 8
-    // tiles kt and kt + 1 (the second past t1: zeros)
-    auto fetch = [&](int kt, float4 (&pk)[2][F4], float4 (&pv)[2][F4]) {
+    const int G = a.H / a.Hkv, nv = a.rps * G;
+    // the column groups of one span, which read the same K/V, are 8 workgroups apart: on one XCD
+    const int c8 = blockIdx.x / 8, cg = c8 % ncg;
+    const int u = (c8 / ncg) * 8 + blockIdx.x % 8;
+    const int sp = u % nspan, kvh = (u / nspan) % a.Hkv, b = u / (nspan * a.Hkv);
+    if (b >= a.nseq) return;  // grid padding
+    // this lane's query vectors (one per column tile) and their positions
+    int vrow[NT], vpos[NT], maxpos = -1;
+    const float* qp[NT];
+    bool vok[NT];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+    for (int t = 0; t < NT; ++t) {
+        const int v = (cg * NT + t) * 16 + col;
+        vok[t] = v < nv;
+        const int vc = vok[t] ? v : 0;
+        vrow[t] = b * a.rps + vc / G;
+        const int p = a.row_pos[vrow[t]];
+        vpos[t] = vok[t] ? p : -1;
+        maxpos = max(maxpos, vpos[t]);
+        qp[t] = a.q + (size_t)vrow[t] * a.q_stride + (size_t)(kvh * G + vc % G) * HD + 4 * grp;
+    }
 #pragma unroll
-            for (int i = 0; i < F4; ++i) {
-                const int e4 = tid + 256 * i;
-                const int j = (e4 * 4) / HD, d = (e4 * 4) % HD, pos = (kt + u) * kPaK + j;
-                pk[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                pv[u][i] = pk[u][i];
-                if (e4 < kPaK * HD / 4 && kt + u < t1 && pos <= maxpos) {
-                    pk[u][i] = *(const float4*)(kg + (size_t)pos * HD + d);
-                    pv[u][i] = *(const float4*)(vg + (size_t)pos * HD + d);
-                }
-            }
+    for (int o = 8; o > 0; o >>= 1) maxpos = max(maxpos, __shfl_xor(maxpos, o, 16));
+    maxpos = __builtin_amdgcn_readfirstlane(maxpos);
+    const int ntile = maxpos >= 0 ? maxpos / 16 + 1 : 0;
+    const int nlive = max(1, (ntile + span_t - 1) / span_t);  // spans that count in (one writes zeros)
+    if (sp >= nlive) return;
+    const int t0 = sp * span_t + wave, t1 = min(ntile, (sp + 1) * span_t);
+    const size_t kvoff = (((size_t)a.layer * a.max_batch + b) * a.Hkv + kvh) * (size_t)a.cap * HD;
+    const float* kg = a.kc + kvoff + 4 * grp;
+    const float* vg = a.vc + kvoff + VV * col;
+    pf4 kf[QD / 4];
+    vv_t vf[4][VD / VV];
+    // positions past the last one re-read it (masked in the scores)
+    auto load_k = [&](int kt) {
+        const float* p = kg + (size_t)min(kt * 16 + col, maxpos) * HD;
+#pragma unroll
+        for (int s = 0; s < QD / 4; ++s) kf[s] = *(const pf4*)(p + 16 * s);
     };
-    for (int hp = 0; hp * 4 < G; ++hp) {
-        const int hh = hp * 4 + 2 * pr + (col >> 3);  // this lane column's head within the group
-        const int h = kvh * G + hh;
-        float qf[QD];
-        {
-            const float* qp = a.q + (size_t)(b * 8 + (col & 7)) * a.q_stride + h * HD + grp * QD;
+    auto load_v = [&](int kt) {
 #pragma unroll
-            for (int s = 0; s < QD; s += 4) {
-                const pf4 x = *(const pf4*)(qp + s) * a.scale;
-                qf[s] = x[0]; qf[s + 1] = x[1]; qf[s + 2] = x[2]; qf[s + 3] = x[3];
-            }
+        for (int r = 0; r < 4; ++r) {
+            const float* p = vg + (size_t)min(kt * 16 + 4 * grp + r, maxpos) * HD;
+#pragma unroll
+            for (int t = 0; t < VD / VV; ++t) vf[r][t] = *(const vv_t*)(p + 16 * VV * t);
         }
-        pf4 o[VD];  // o[t][r] = O[column col][(4 grp + r) * VD + t]
+    };
+    pf4 qf[NT][QD / 4];
 #pragma unroll
-        for (int t = 0; t < VD; ++t) o[t] = pf4{0.f, 0.f, 0.f, 0.f};
-        float m_run = -INFINITY, l_run = 0.f;
-        float4 pk[2][F4], pv[2][F4];
-        if (t0 < t1) fetch(t0, pk, pv);
-        for (int kt = t0; kt < t1; kt += 2) {
-            __syncthreads();
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+        for (int s = 0; s < QD / 4; ++s) qf[t][s] = *(const pf4*)(qp[t] + 16 * s);
+    if (t0 < t1) {
+        load_k(t0);
+        load_v(t0);
+    }
 #pragma unroll
-                for (int i = 0; i < F4; ++i) {
-                    const int e4 = tid + 256 * i;
-                    if (e4 < kPaK * HD / 4) {
-                        const int j = (e4 * 4) / HD, d = (e4 * 4) % HD;
-                        *(float4*)(ks[u] + j * KL + d) = pk[u][i];
-                        *(float4*)(vs[u] + j * KL + d) = pv[u][i];
-                    }
-                }
-            __syncthreads();
-            if (kt + 2 < t1) fetch(kt + 2, pk, pv);
-            const int mt = kt + half;
-            if (mt >= t1) continue;  // uniform per wave; the next barrier is at the loop top
-            const float* kss = ks[half];
-            const float* vss = vs[half];
-            float kf[QD], vf[4][VD];
+    for (int t = 0; t < NT; ++t) {
+        const float sc = vok[t] ? a.scale : 0.f;
 #pragma unroll
-            for (int s = 0; s < QD; s += 4) {
-                const pf4 x = *(const pf4*)(kss + col * KL + grp * QD + s);
-                kf[s] = x[0]; kf[s + 1] = x[1]; kf[s + 2] = x[2]; kf[s + 3] = x[3];
-            }
+        for (int s = 0; s < QD / 4; ++s) qf[t][s] *= sc;
+    }
+    pf4 o[NT][VD];
+    float m_run[NT], l_run[NT];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float* vr = vss + (4 * grp + r) * KL + col * VD;
-                if constexpr (VD == 2) {
-                    const pf2 x = *(const pf2*)vr;
-                    vf[r][0] = x[0]; vf[r][1] = x[1];
-                } else {
+    for (int t = 0; t < NT; ++t) {
+        m_run[t] = -INFINITY;
+        l_run[t] = 0.f;
 #pragma unroll
-                    for (int t = 0; t < VD; t += 4) {
-                        const pf4 x = *(const pf4*)(vr + t);
-                        vf[r][t] = x[0]; vf[r][t + 1] = x[1]; vf[r][t + 2] = x[2]; vf[r][t + 3] = x[3];
-                    }
-                }
-            }
-            pf4 sc4[4];
+        for (int d = 0; d < VD; ++d) o[t][d] = pf4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int kt = t0; kt < t1; kt += 4) {
+        pf4 sc[NT][2];
 #pragma unroll
-            for (int c4 = 0; c4 < 4; ++c4) sc4[c4] = pf4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NT; ++t) sc[t][0] = sc[t][1] = pf4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < QD; ++s)
-                sc4[s & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s], qf[s], sc4[s & 3], 0, 0, 0);
-            const pf4 sc = (sc4[0] + sc4[1]) + (sc4[2] + sc4[3]);
-            const int kb = mt * kPaK + 4 * grp;
-            float sv[4], mx = -INFINITY;
+        for (int s = 0; s < QD; ++s)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                sc[t][s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s / 4][s % 4], qf[t][s / 4][s % 4], sc[t][s & 1], 0, 0, 0);
+        const int nx = kt + 4 < t1 ? kt + 4 : kt;
+        load_k(nx);
+        // online softmax: this lane holds S[its query][key 4 grp + r]
+        float pr[NT][4];
+        const int kb = kt * 16 + 4 * grp;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            float sv[4], mx = -INFINITY, sum = 0.f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                sv[r] = (myq >= 0 && kb + r <= myq) ? sc[r] : -INFINITY;
+                sv[r] = kb + r <= vpos[t] ? sc[t][0][r] + sc[t][1][r] : -INFINITY;
                 mx = fmaxf(mx, sv[r]);
             }
             mx = pa_colmax(mx);
-            const float mnew = fmaxf(m_run, mx);
-            float pw[4], sum = 0.f;
+            const float mnew = fmaxf(m_run[t], mx);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                pw[r] = sv[r] == -INFINITY ? 0.f : expf(sv[r] - mnew);
-                sum += pw[r];
+                pr[t][r] = sv[r] == -INFINITY ? 0.f : expf(sv[r] - mnew);
+                sum += pr[t][r];
             }
-            sum = pa_colsum(sum);
-            const float scl = m_run == -INFINITY ? 0.f : expf(m_run - mnew);
-            l_run = l_run * scl + sum;
-            m_run = mnew;
+            const float scl = m_run[t] == -INFINITY ? 0.f : expf(m_run[t] - mnew);
+            l_run[t] = l_run[t] * scl + pa_colsum(sum);
+            m_run[t] = mnew;
 #pragma unroll
-            for (int t = 0; t < VD; ++t) o[t] *= scl;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int t = 0; t < VD; ++t)
-                    o[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][t], pw[r], o[t], 0, 0, 0);
+            for (int d = 0; d < VD; ++d) o[t][d] *= scl;
         }
-        // the odd-tile wave of each pair hands its state over (lane layout), the even-tile wave
-        // merges it
-        float* ow = ot + pr * (kPaQ * KL);
-        __syncthreads();
-        if (half == 1) {
 #pragma unroll
-            for (int t = 0; t < VD; ++t) *(pf4*)(ow + (t * 64 + lane) * 4) = o[t];
-            mlh[pr][0][lane] = m_run;
-            mlh[pr][1][lane] = l_run;
-        }
-        __syncthreads();
-        if (half == 0) {
-            const float m2 = mlh[pr][0][lane], l2 = mlh[pr][1][lane];
-            const float M = fmaxf(m_run, m2);
-            const float s1 = m_run == -INFINITY ? 0.f : expf(m_run - M);
-            const float s2 = m2 == -INFINITY ? 0.f : expf(m2 - M);
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int t = 0; t < VD; ++t) o[t] = o[t] * s1 + *(const pf4*)(ow + (t * 64 + lane) * 4) * s2;
-            l_run = l_run * s1 + l2 * s2;
-            m_run = M;
-            // O through LDS into row-major order (this wave's own hand-off area, already read)
-            const float inv = nspan == 1 ? ((myq >= 0 && l_run > 0.f) ? 1.f / l_run : 0.f) : 1.f;
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the hand-off reads are done
-            __builtin_amdgcn_wave_barrier();
+            for (int d = 0; d < VD; ++d)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    o[t][d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][d / VV][d % VV], pr[t][r], o[t][d], 0, 0, 0);
+        load_v(nx);
+    }
+    // merge the waves: group i = (t, t4, r) of a lane is VV adjacent dims, 16 VV t4 + VV (4 grp + r),
+    // of its query vector t
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+#pragma unroll
+        for (int t4 = 0; t4 < VD / VV; ++t4)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                float* dst = ow + col * KL + (4 * grp + r) * VD;
-                if constexpr (VD == 2) {
-                    *(pf2*)dst = pf2{o[0][r] * inv, o[1][r] * inv};
+                vv_t x;
+#pragma unroll
+                for (int e = 0; e < VV; ++e) x[e] = o[t][VV * t4 + e][r];
+                *(vv_t*)&os[wave][(t * (VD / VV) + t4) * 4 + r][lane * VV] = x;
+            }
+        if (grp == 0) {
+            ms[wave][16 * t + col] = m_run[t];
+            ls[wave][16 * t + col] = l_run[t];
+        }
+    }
+    __syncthreads();
+    // spans: outputs [row][head][span][HD], then (max, sum) [row][head][span][2]
+    const int rows = a.nseq * a.rps;
+    float* const pml = a.part + (size_t)rows * a.H * nspan * HD;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        float w[4], M = -INFINITY, L = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) M = fmaxf(M, ms[k][16 * t + col]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float m = ms[k][16 * t + col];
+            w[k] = m == -INFINITY ? 0.f : expf(m - M);
+            L += w[k] * ls[k][16 * t + col];
+        }
+        const float inv = nlive == 1 ? (L > 0.f ? 1.f / L : 0.f) : 1.f;
+        const int v = (cg * NT + t) * 16 + col, h = kvh * G + (vok[t] ? v % G : 0);
+        const size_t ph = ((size_t)vrow[t] * a.H + h) * nspan + sp;
+#pragma unroll
+        for (int i0 = 0; i0 < NO / NT; i0 += 4) {
+            const int i = i0 + wave;
+            vv_t x = {};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x += *(const vv_t*)&os[k][t * (NO / NT) + i][lane * VV] * w[k];
+            x *= inv;
+            if (!vok[t]) continue;
+            const int d = 16 * VV * (i / 4) + VV * (4 * grp + i % 4);
+            if (nlive == 1) {
+                if constexpr (VV == 4) {
+                    attn_put4(a, vrow[t], h * HD + d, make_float4(x[0], x[1], x[2], x[3]));
                 } else {
 #pragma unroll
-                    for (int t = 0; t < VD; t += 4)
-                        *(pf4*)(dst + t) = pf4{o[t][r] * inv, o[t + 1][r] * inv, o[t + 2][r] * inv, o[t + 3][r] * inv};
+                    for (int e = 0; e < VV; ++e) attn_put1(a, vrow[t], h * HD + d + e, x[e]);
                 }
-            }
-            if (nspan > 1 && grp == 0) {
-                float* pp = a.part + (((size_t)(b * 8 + (col & 7)) * a.H + h) * a.nsplit + sp) * (HD + 2);
-                store_through(pp + HD, m_run);
-                store_through(pp + HD + 1, l_run);
-            }
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-            constexpr int RW = (HD + 63) / 64;
-            float rv[kPaQ][RW];
+            } else {
 #pragma unroll
-            for (int c = 0; c < kPaQ; ++c)
-#pragma unroll
-                for (int j = 0; j < RW; ++j) rv[c][j] = ow[c * KL + min(lane + 64 * j, HD - 1)];
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int c = 0; c < kPaQ; ++c) {
-                const size_t orow = (size_t)(b * 8 + (c & 7));
-                const int hc = kvh * G + hp * 4 + 2 * pr + (c >> 3);
-#pragma unroll
-                for (int j = 0; j < RW; ++j) {
-                    const int d = lane + 64 * j;
-                    if (d < HD) {
-                        if (nspan == 1) a.out[orow * a.H * HD + hc * HD + d] = rv[c][j];
-                        else store_through(a.part + ((orow * a.H + hc) * a.nsplit + sp) * (HD + 2) + d, rv[c][j]);
-                    }
-                }
+                for (int e = 0; e < VV; ++e) store_through(a.part + ph * HD + d + e, x[e]);
             }
         }
+        if (nlive > 1 && vok[t] && grp == 0 && wave == 0) {
+            store_through(pml + ph * 2, M);
+            store_through(pml + ph * 2 + 1, L);
+        }
     }
-    if (nspan == 1) return;
-    pa_span_merge<HD>(a, grp_id, nspan, span_t, ntile_all, b, kvh, 0, qpos, &last_flag);
+    if (nlive == 1) return;
+    if (!arrive_last(a.cnt + (b * a.Hkv + kvh) * ncg + cg, nlive, &last_flag)) return;
+    // the last live span merges: a thread per (vector, 4 dims), spans eight per round trip (loads
+    // past the last live span re-read it and are not added)
+    constexpr int D4 = HD / 4;
+    for (int idx = tid; idx < 16 * NT * D4; idx += 256) {
+        const int v = cg * NT * 16 + idx / D4, d = (idx % D4) * 4;
+        if (v >= nv) break;
+        const int h = kvh * G + v % G;
+        const size_t row = (size_t)b * a.rps + v / G, ph = (row * a.H + h) * nspan;
+        float M = -INFINITY, L = 0.f;
+        pf4 O = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < nlive; s0 += 8) {
+            pf4 ov[8];
+            pf2 ml[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const size_t e = ph + min(s0 + k, nlive - 1);
+                ov[k] = *(const pf4*)(a.part + e * HD + d);
+                ml[k] = *(const pf2*)(pml + e * 2);
+            }
+            float Mn = M;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) Mn = s0 + k < nlive ? fmaxf(Mn, ml[k][0]) : Mn;
+            const float sc = M == -INFINITY ? 0.f : expf(M - Mn);
+            L *= sc;
+            O *= sc;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float w = s0 + k < nlive && ml[k][0] != -INFINITY ? expf(ml[k][0] - Mn) : 0.f;
+                L += w * ml[k][1];
+                O += ov[k] * w;
+            }
+            M = Mn;
+        }
+        const float inv = L > 0.f ? 1.f / L : 0.f;
+        O *= inv;
+        attn_put4(a, row, h * HD + d, make_float4(O[0], O[1], O[2], O[3]));
+    }
 }
 
-static void launch_pattn(Engine& e, hipStream_t s, const AttnArgs& a, int nseq) {
-    // the kernel reads query rows and writes output rows as 16-byte vectors
-    if (a.q_stride % 4 || ((uintptr_t)a.q & 15) || ((uintptr_t)a.out & 15)) {
-        e.bad_launch = true;
-        return;
-    }
+template <int HD>
+static void launch_vattn(Engine& e, hipStream_t s, const AttnArgs& a) {
+    const int nv = a.rps * (a.H / a.Hkv), NT = nv <= 16 ? 1 : 2;
+    const int ncg = (nv + 16 * NT - 1) / (16 * NT), groups = a.nseq * a.Hkv;
+    // Spans for about 2048 workgroups over the whole capacity (those past a sequence's length exit
+    // at once), of at least two key tiles per wave.
+    const int tiles = (a.cap + 15) / 16;
+    int nspan = std::min((tiles + kVaMinTiles - 1) / kVaMinTiles, std::max(1, 2048 / (groups * ncg)));
+    if ((size_t)groups * ncg > e.ws.attn_cnt_n) nspan = 1;
+    int span_t = (tiles + nspan - 1) / nspan;
+    span_t = (span_t + 3) / 4 * 4;
+    nspan = (tiles + span_t - 1) / span_t;
+    const dim3 grid((groups * nspan + 7) / 8 * 8 * ncg);
+    ProfEntry* pe = prof_slot(&e, kProfAttn, 0.0);
+    hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
+    if (NT == 1) hipExtLaunchKernelGGL((k_vattn<HD, 1>), grid, dim3(256), 0, s, ea, eb, 0, a, ncg, nspan, span_t);
+    else hipExtLaunchKernelGGL((k_vattn<HD, 2>), grid, dim3(256), 0, s, ea, eb, 0, a, ncg, nspan, span_t);
+    if (pe) prof_commit(&e);
+}
+
+static void launch_pattn(Engine& e, hipStream_t s, const AttnArgs& a) {
     const int nqb = (a.rps + kPaQ - 1) / kPaQ;
-    const int groups = nseq * a.Hkv * nqb;
+    const int groups = a.nseq * a.Hkv * nqb;
     // few groups: split the keys into spans for about 2048 workgroups, eight per compute unit,
     // since spans past a sequence's length exit at once (at most 16 spans, within the decode
     // kernel's partial buffer and counters)
-    // blocks of exactly 8 rows with a multiple of 4 query heads per KV head: two heads per
-    // matrix tile (k_pattn_pk), which walks its span's key tiles two at a time
-    const bool packed = a.rps == 8 && (a.H / a.Hkv) % 4 == 0;
     int nspan = 1, span_t = 1;
     if (groups < 256 && (size_t)groups <= e.ws.attn_cnt_n) {
         const int tiles = (a.cap + kPaK - 1) / kPaK;
-        // (the packed kernel does half the matrix work per tile and measured best at ~768
-        // workgroups: 79.8 us with 6 spans against 86.9 with 15 at the batched verify shape)
-        nspan = std::min(std::min(kPaMaxSpans, a.nsplit), std::max(1, (packed ? 768 : 2048) / groups));
+        nspan = std::min(std::min(kPaMaxSpans, a.nsplit), std::max(1, 2048 / groups));
         span_t = (tiles + nspan - 1) / nspan;
-        if (packed) span_t += span_t & 1;
         nspan = (tiles + span_t - 1) / span_t;
     }
     dim3 grid(groups * nspan);
     ProfEntry* pe = prof_slot(&e, kProfAttn, 0.0);
     hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
-    if (packed) {
-        switch (a.hd) {
-            case 32: hipExtLaunchKernelGGL(k_pattn_pk<32>, grid, dim3(256), 0, s, ea, eb, 0, a, nspan, span_t); break;
-            case 64: hipExtLaunchKernelGGL(k_pattn_pk<64>, grid, dim3(256), 0, s, ea, eb, 0, a, nspan, span_t); break;
-            case 128: hipExtLaunchKernelGGL(k_pattn_pk<128>, grid, dim3(256), 0, s, ea, eb, 0, a, nspan, span_t); break;
-            default: e.bad_launch = true; pe = nullptr; break;
-        }
-        if (pe) prof_commit(&e);
-        return;
-    }
     switch (a.hd) {
         case 32: hipExtLaunchKernelGGL(k_pattn<32>, grid, dim3(256), 0, s, ea, eb, 0, a, nspan, span_t); break;
         case 64: hipExtLaunchKernelGGL(k_pattn<64>, grid, dim3(256), 0, s, ea, eb, 0, a, nspan, span_t); break;
@@ -837,72 +629,41 @@ static void launch_pattn(Engine& e, hipStream_t s, const AttnArgs& a, int nseq) 
     if (pe) prof_commit(&e);
 }
 
-static size_t attn_lds(int hd, int qt) {
-    return sizeof(float) * ((size_t)qt * hd + (size_t)kAttnCL * (hd + 1) + (size_t)kAttnCL * hd + (size_t)qt * kAttnCL);
-}
-
-// Query heads per workgroup: all heads of a KV group, so that each K/V row is read once for all
-// of them (rows are then tiled 32/G at a time); one head per workgroup only for groups wider
-// than a tile.
-int attn_heads_per_wg(int nseq, int rps, int H, int Hkv) {
-    (void)nseq;
-    (void)rps;
-    const int G = H / Hkv;
-    return G > kAttnQT ? 1 : G;
-}
-
 void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int rps, const float* q, int q_stride) {
     const sd2_dims& dm = m.dm;
-    AttnArgs a;
-    a.q = q; a.q_stride = q_stride; a.kc = m.kc; a.vc = m.vc; a.out = e.ws.attn; a.row_pos = e.ws.row_pos;
+    AttnArgs a{};
+    a.q = q; a.q_stride = q_stride; a.kc = m.kc; a.vc = m.vc; a.out = e.ws.attn;
+    a.planes = e.ws.planes ? (uint16_t*)e.ws.attn : nullptr;
+    a.Mp = pg_rows(rows);
+    a.row_pos = e.ws.row_pos;
     a.rps = rps; a.H = dm.n_heads; a.Hkv = dm.n_kv_heads; a.hd = m.hd; a.cap = e.cap; a.max_batch = e.cfg.max_batch;
     a.layer = layer;
-    int nseq = rows / rps;
-    int G = dm.n_heads / dm.n_kv_heads;
-    a.hp = attn_heads_per_wg(nseq, rps, dm.n_heads, dm.n_kv_heads);
-    int rows_per_tile = kAttnQT / a.hp;
-    a.nrt = (rps + rows_per_tile - 1) / rows_per_tile;
-    a.ngrp = nseq * dm.n_kv_heads * a.nrt;
+    a.nseq = rows / rps;
     a.scale = 1.0f / sqrtf((float)m.hd);
     a.nsplit = attn_nsplit(e.cap);
     a.part = e.ws.attn_part;
     a.cnt = e.ws.attn_cnt;
-    if (rps >= kPaMinRows) {
-        // many rows per sequence: flash attention on the matrix cores
-        launch_pattn(e, s, a, nseq);
+    // the kernels read query rows and write output rows as 16-byte vectors
+    if (a.q_stride % 4 || ((uintptr_t)a.q & 15) || ((uintptr_t)a.out & 15)) {
+        e.bad_launch = true;
         return;
     }
-    int members = G / a.hp;
-    a.nsplit = attn_nsplit(e.cap);
-    a.part = e.ws.attn_part;
-    a.cnt = e.ws.attn_cnt;
-    int nblk = (a.ngrp + kXcds - 1) / kXcds * kXcds * members * a.nsplit;
-    ProfEntry* pe = prof_slot(&e, kProfAttn, 0.0);
-    hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
-    // eight query-vector slots where a group's rows and heads fit them (decode steps: one or two
-    // rows of a KV group), which quarters the query and score buffers in LDS; the row tiling,
-    // and so the group count, is the same as with 32 slots (one tile)
-    const bool q8 = a.hp * rps <= 8;
-    switch (m.hd * (q8 ? -1 : 1)) {
-        case 32: hipExtLaunchKernelGGL((k_attn<32, kAttnQT>), dim3(nblk), dim3(kAttnT), attn_lds(32, kAttnQT), s, ea, eb, 0, a); break;
-        case 64: hipExtLaunchKernelGGL((k_attn<64, kAttnQT>), dim3(nblk), dim3(kAttnT), attn_lds(64, kAttnQT), s, ea, eb, 0, a); break;
-        case 128: hipExtLaunchKernelGGL((k_attn<128, kAttnQT>), dim3(nblk), dim3(kAttnT), attn_lds(128, kAttnQT), s, ea, eb, 0, a); break;
-        case -32: hipExtLaunchKernelGGL((k_attn<32, 8>), dim3(nblk), dim3(kAttnT), attn_lds(32, 8), s, ea, eb, 0, a); break;
-        case -64: hipExtLaunchKernelGGL((k_attn<64, 8>), dim3(nblk), dim3(kAttnT), attn_lds(64, 8), s, ea, eb, 0, a); break;
-        case -128: hipExtLaunchKernelGGL((k_attn<128, 8>), dim3(nblk), dim3(kAttnT), attn_lds(128, 8), s, ea, eb, 0, a); break;
-        default: e.bad_launch = true; pe = nullptr; break;
+    // from 16 rows a tile of one head's rows is full, and the keys staged once in LDS serve all heads
+    if (rps > kVaMaxRows) {
+        launch_pattn(e, s, a);
+        return;
     }
-    if (pe) prof_commit(&e);
+    switch (m.hd) {
+        case 32: launch_vattn<32>(e, s, a); break;
+        case 64: launch_vattn<64>(e, s, a); break;
+        case 128: launch_vattn<128>(e, s, a); break;
+        default: e.bad_launch = true; break;
+    }
 }
 
-// Workgroups of the split-free attention grid for a launch shape (arrival counters needed).
+// Arrival counters of an attention launch: one per sequence, KV head and 32 query vectors.
 size_t attn_groups(int rows, int rps, int H, int Hkv) {
-    int nseq = rows / rps, G = H / Hkv;
-    int hp = attn_heads_per_wg(nseq, rps, H, Hkv);
-    int rows_per_tile = kAttnQT / hp;
-    int nrt = (rps + rows_per_tile - 1) / rows_per_tile;
-    int ngrp = nseq * Hkv * nrt;
-    return (size_t)(ngrp + kXcds - 1) / kXcds * kXcds * (G / hp);
+    return (size_t)(rows / rps) * Hkv * ((rps * (H / Hkv) + 31) / 32);
 }
 
 int attn_nsplit(int cap) { return (cap + kSplit - 1) / kSplit; }

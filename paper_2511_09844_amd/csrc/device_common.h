@@ -30,6 +30,23 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// The same sum with DPP steps (quad permutes, row mirrors, row broadcasts), every lane active: no
+// LDS round trips; uniform.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_f32(float old, float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v),
+                                                                 CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+    v += dpp_f32<0xB1, 0xf>(0.f, v);
+    v += dpp_f32<0x4E, 0xf>(0.f, v);
+    v += dpp_f32<0x141, 0xf>(0.f, v);
+    v += dpp_f32<0x140, 0xf>(0.f, v);
+    v += dpp_f32<0x142, 0xa>(0.f, v);
+    v += dpp_f32<0x143, 0xc>(0.f, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
 // (score, index) argmax with ties to the lower index.
 struct ArgBest {
     float s;

@@ -75,10 +75,11 @@ struct Workspace {
     int32_t* forced;        // [max_batch][k+2]
     int32_t* forced_on;     // [1]
     // split-K partial tiles of the projection kernel; attention partials per position span
-    // activation planes of the many-row projections (see pgemm.hip) and 1/rms of their rows
+    // planes of the residual rows (see pgemm.hip), or null: without them (fp32 weights, a static
+    // workspace too small) every projection reads fp32 rows.  With them attn and ffh hold planes
+    // as well, and ffh has ffh_n bytes.
     uint16_t* planes;
-    float* row_inv;
-    size_t planes_n;             // bytes of planes
+    size_t ffh_n;
     float* ws_part;
     int32_t* ws_cnt;
     size_t ws_part_n, ws_cnt_n;  // their capacities (floats, counters)
@@ -203,6 +204,9 @@ struct WsCall {
     const float *rcos, *rsin;
     float *qout, *kc, *vc;
     int cap, max_batch, layer;
+    const uint16_t* planes;  // X as planes, times the gain (else made from X)
+    uint16_t* yplanes;       // planes of the output (see PgArgs), with the gain ygamma
+    const void* ygamma;
     const float* ubias;  // per-sequence bias rows (stride ub_ld, row_seq): SwiGLU adds them to up, Add
                          // to the output; or null
     int ub_ld;
@@ -213,7 +217,7 @@ struct WsPlan {
 };
 WsPlan ws_plan(int M, int N, int K, int mode);
 void launch_wsgemv(Engine* e, hipStream_t s, const WsCall& c);
-// Many-row projection; false when it does not take the call (see pgemm.hip).
+// Projection on planes; false when it does not take the call (see pgemm.hip).
 bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c);
 
 void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int rps, const float* q, int q_stride);

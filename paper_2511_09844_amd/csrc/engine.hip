@@ -142,8 +142,10 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
     int att = std::max(c.verifier.n_heads * ms[0]->hd, c.drafter.n_heads * ms[1]->hd);
     int ff = std::max(c.verifier.d_ff, c.drafter.d_ff);
     w.qkv = cv.take<float>((size_t)maxm * qkv);
-    w.attn = cv.take<float>((size_t)maxm * att);
-    w.ffh = cv.take<float>((size_t)maxm * ff);
+    const bool planes = c.dtype == SD2_BF16 && !lean;
+    w.attn = cv.take<float>(planes ? pg_plane_bytes(maxm, att) / 4 : (size_t)maxm * att);
+    w.ffh_n = planes ? pg_plane_bytes(maxm, ff) : 0;
+    w.ffh = cv.take<float>(planes ? w.ffh_n / 4 : (size_t)maxm * ff);
     w.logits_v = cv.take<float>((size_t)B * (k + 1) * V);
     w.logits_d = cv.take<float>((size_t)B * k * V);
     w.hidden_dbg = cv.take<float>((size_t)B * (k + 1) * c.verifier.d_model);
@@ -196,8 +198,8 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
         // many-row projections with K ranges.  Besides the models': W_s over many rows (the
         // training-objective forward) and the MLP steering projections of more than 16 sequences
         const int R = c.steering == SD2_STEER_MLP_COND ? c.cond_rank : 0;
-        const bool mf = mlp_form(c), pg = c.dtype == SD2_BF16 && !lean;
-        for (int i = 0; i < 2 && pg; ++i) {
+        const bool mf = mlp_form(c);
+        for (int i = 0; i < 2 && planes; ++i) {
             const sd2_dims& d = *dd[i];
             int hd = d.d_model / d.n_heads;
             int shapes[10][2] = {{(d.n_heads + 2 * d.n_kv_heads) * hd, d.d_model},
@@ -236,18 +238,11 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
             int hd = dd[i]->d_model / dd[i]->n_heads;
             amax = std::max(amax, (size_t)maxm * dd[i]->n_heads * attn_nsplit(cap) * (hd + 2));
         }
-        // the planes of the many-row projections share the attention partials' memory: these live
-        // within one attention launch, those from k_planes to the projection that follows it
-        size_t planes = 0;
-        if (c.dtype == SD2_BF16 && !lean) {
-            for (int i = 0; i < 2; ++i)
-                planes = std::max(planes, pg_plane_bytes(maxm, std::max(dd[i]->d_model, dd[i]->d_ff)));
-            if (mlp_form(c) && B >= 16) planes = std::max(planes, pg_plane_bytes(B, 3 * c.verifier.d_model));
-            w.row_inv = cv.take<float>(maxm);
-        }
-        w.attn_part = cv.take<float>(std::max(amax, (planes + 3) / 4));
+        // the residual's planes share the attention partials' memory: these live within one
+        // attention launch, those from the launch that writes the residual to the projection on it
+        const size_t pn = planes ? pg_plane_bytes(maxm, std::max(c.verifier.d_model, c.drafter.d_model)) : 0;
+        w.attn_part = cv.take<float>(std::max(amax, pn / 4));
         w.planes = planes ? (uint16_t*)w.attn_part : nullptr;
-        w.planes_n = planes;
         // arrival counters: the largest split-free grid of any launch shape
         size_t gmax = 1;
         for (int i = 0; i < 2; ++i) {

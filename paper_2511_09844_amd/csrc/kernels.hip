@@ -4,6 +4,7 @@
 
 #include "device_common.h"
 #include "engine.h"
+#include "pgemm.h"
 
 namespace sd2 {
 
@@ -59,7 +60,23 @@ struct PlanArgs {
     float* x;
     float* ss;   // [rows][d/16]
     const void* embed;
+    uint16_t* planes;       // planes of the rows times the first layer's norm gain, or null
+    const uint16_t* gamma;
+    int Mp;
 };
+
+template <typename TW>
+__device__ __forceinline__ float4 load_row4(const TW* p, int i);
+template <>
+__device__ __forceinline__ float4 load_row4<float>(const float* p, int i) { return *(const float4*)(p + i); }
+template <>
+__device__ __forceinline__ float4 load_row4<uint16_t>(const uint16_t* p, int i) {
+    const uint2 w = *(const uint2*)(p + i);
+    return make_float4(bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y));
+}
+__device__ __forceinline__ float4 add4(float4 a, float4 b) {
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
 
 template <typename TW>
 __global__ __launch_bounds__(256) void k_plan_embed(PlanArgs a) {
@@ -109,21 +126,25 @@ __global__ __launch_bounds__(256) void k_plan_embed(PlanArgs a) {
     float* xr = a.x + (size_t)r * a.d;
     const TW* er = (const TW*)a.embed + (size_t)tok * a.d;
     const float* sr = a.steer + (size_t)b * a.d;
-    const int nsl = a.d / 16;
-    for (int sl = threadIdx.x; sl < nsl; sl += blockDim.x) {
-        float acc = 0.0f;
-        for (int c = 0; c < 16; ++c) {
-            int i = sl * 16 + c;
-            float v = 0.0f;
-            if (active) {
-                v = load_scalar<TW>(er, i);
-                if (a.add_steer) v += sr[i];
-                if (a.row_add) v += a.row_add[(size_t)r * a.d + i];
-            }
-            xr[i] = v;
-            acc += v * v;
+    // four columns per thread (a slice of 16 columns is four neighbouring lanes): one thread per
+    // slice, 16 scalar loads in a row each, took 13 us for 512 rows of 4096
+    for (int i = 4 * threadIdx.x; i < a.d; i += 4 * blockDim.x) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (active) {
+            v = load_row4<TW>(er, i);
+            if (a.add_steer) v = add4(v, *(const float4*)(sr + i));
+            if (a.row_add) v = add4(v, *(const float4*)(a.row_add + (size_t)r * a.d + i));
         }
-        a.ss[(size_t)r * nsl + sl] = acc;
+        *(float4*)(xr + i) = v;
+        if (a.planes) {
+            const uint2 g = *(const uint2*)(a.gamma + i);
+            pg_put4(a.planes, a.Mp, r, i,
+                    make_float4(v.x * bf16_lo(g.x), v.y * bf16_hi(g.x), v.z * bf16_lo(g.y), v.w * bf16_hi(g.y)));
+        }
+        float acc = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+        acc += __shfl_xor(acc, 1, 4);
+        acc += __shfl_xor(acc, 2, 4);
+        if ((threadIdx.x & 3) == 0) a.ss[(size_t)r * (a.d / 16) + i / 16] = acc;
     }
 }
 
@@ -138,6 +159,7 @@ void launch_plan_embed(hipStream_t s, Engine& e, ModelDev& m, int kind, int j, i
     a.steer = e.ws.steer;
     a.add_steer = !e.mlp && e.w_steer && (&m == &e.md) && (kind == kPlanDraft1 || kind == kPlanDraftJ);
     a.row_pos = e.ws.row_pos; a.row_seq = e.ws.row_seq; a.x = m.x; a.ss = m.ss; a.embed = m.embed;
+    a.planes = e.ws.planes; a.gamma = (const uint16_t*)m.layer[kAttnNorm]; a.Mp = pg_rows(rows);
     prof_begin(&e, kProfOther, 0.0);
     if (e.bf16) k_plan_embed<uint16_t><<<rows, 256, 0, s>>>(a);
     else k_plan_embed<float><<<rows, 256, 0, s>>>(a);
@@ -399,8 +421,14 @@ void launch_layer(hipStream_t s, Engine& e, ModelDev& m, int layer, int rows, in
     const void* const* W = m.layer + (size_t)layer * 9;
     int hd = m.hd, H = dm.n_heads, Hkv = dm.n_kv_heads;
     if (e.bf16) {
+        // Every operand passes as planes where the workspace has them: the residual's with the
+        // gain of the norm that reads it next, the attention's and the MLP's as they are.
+        uint16_t* const xp = e.ws.planes;
+        uint16_t* const ap = xp ? (uint16_t*)e.ws.attn : nullptr;
+        uint16_t* const fp = xp ? (uint16_t*)e.ws.ffh : nullptr;
         // Q|K|V with the attention RMSNorm as prologue, RoPE and the cache append as epilogue
         WsCall c = ws_base(e, m);
+        c.planes = xp;
         c.X = m.x; c.M = rows; c.K = dm.d_model; c.gamma = W[kAttnNorm]; c.ss = m.ss;
         c.W[0] = W[kWq]; c.W[1] = W[kWk]; c.W[2] = W[kWv];
         c.seg_rows[0] = H * hd; c.seg_rows[1] = Hkv * hd; c.seg_rows[2] = Hkv * hd;
@@ -414,18 +442,21 @@ void launch_layer(hipStream_t s, Engine& e, ModelDev& m, int layer, int rows, in
         WsCall o = ws_base(e, m);
         o.X = e.ws.attn; o.M = rows; o.K = H * hd; o.W[0] = W[kWo]; o.seg_rows[0] = dm.d_model; o.nseg = 1;
         o.mode = kEpiAdd; o.Y = m.x; o.ldy = dm.d_model; o.ss_out = m.ss;
+        o.planes = ap; o.yplanes = xp; o.ygamma = W[kFfnNorm];
         launch_wsgemv(&e, s, o);
         // gate|up with the FFN RMSNorm prologue and SwiGLU epilogue
         WsCall g = ws_base(e, m);
         g.X = m.x; g.M = rows; g.K = dm.d_model; g.gamma = W[kFfnNorm]; g.ss = m.ss;
         g.W[0] = W[kWg]; g.W[1] = W[kWu]; g.seg_rows[0] = dm.d_ff; g.seg_rows[1] = dm.d_ff; g.nseg = 2;
         g.mode = kEpiSwiglu; g.Y = e.ws.ffh; g.ldy = dm.d_ff;
+        g.planes = xp; g.yplanes = fp;
         g.ubias = up_bias; g.ub_ld = ub_ld; g.row_seq = bias_rows;
         launch_wsgemv(&e, s, g);
         // down projection + residual
         WsCall d = ws_base(e, m);
         d.X = e.ws.ffh; d.M = rows; d.K = dm.d_ff; d.W[0] = W[kWd]; d.seg_rows[0] = dm.d_model; d.nseg = 1;
         d.mode = kEpiAdd; d.Y = m.x; d.ldy = dm.d_model; d.ss_out = m.ss;
+        d.planes = fp; d.yplanes = xp; d.ygamma = layer + 1 < dm.n_layers ? W[9 + kAttnNorm] : m.final_norm;
         d.ubias = out_bias; d.ub_ld = ub_ld; d.row_seq = bias_rows;
         launch_wsgemv(&e, s, d);
         return;
@@ -473,6 +504,7 @@ void launch_lm_head(Engine& e, ModelDev& m, int rows, float* Y, const int32_t* o
         c.X = m.x; c.M = rows; c.K = m.dm.d_model; c.gamma = m.final_norm; c.ss = m.ss;
         c.W[0] = m.lm_head; c.seg_rows[0] = m.dm.vocab; c.nseg = 1; c.mode = kEpiStore;
         c.Y = Y; c.ldy = m.dm.vocab; c.out_map = out_map;
+        c.planes = e.ws.planes;
         launch_wsgemv(&e, e.stream, c);
         return;
     }

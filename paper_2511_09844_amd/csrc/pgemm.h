@@ -1,5 +1,6 @@
-// Many-row projections on the matrix cores (see pgemm.hip).
+// Projections on activation planes (see pgemm.hip).
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -22,5 +23,36 @@ PgPlan pg_plan(int M, int N, int K);
 inline int pg_rows(int M) { return (M + 15) / 16 * 16; }
 // bytes of the planes of M rows and K columns
 inline size_t pg_plane_bytes(int M, int K) { return (size_t)pg_rows(M) * K * 4 + kPgSlack; }
+
+#ifdef __HIPCC__
+typedef __bf16 pg_bf2 __attribute__((ext_vector_type(2)));
+typedef float pg_f2 __attribute__((ext_vector_type(2)));
+
+// hi/lo bf16 split of two fp32 values, packed (hi = x rounded to nearest even, lo = (x - hi)
+// rounded likewise)
+__device__ __forceinline__ void pg_split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+    const pg_f2 v = {x0, x1};
+    const pg_bf2 h = __builtin_convertvector(v, pg_bf2);
+    const pg_bf2 l = __builtin_convertvector(v - __builtin_convertvector(h, pg_f2), pg_bf2);
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+// Columns c .. c + 3 (c a multiple of 4), or column c, of a row into planes of Mp rows.
+__device__ __forceinline__ void pg_put4(uint16_t* planes, int Mp, size_t row, int c, float4 v) {
+    uint2 h, l;
+    pg_split2(v.x, v.y, h.x, l.x);
+    pg_split2(v.z, v.w, h.y, l.y);
+    uint16_t* p = planes + ((size_t)(c / kPgBlk) * Mp + row) * kPgBlkWords + c % kPgBlk;
+    *(uint2*)p = h;
+    *(uint2*)(p + kPgBlk) = l;
+}
+__device__ __forceinline__ void pg_put1(uint16_t* planes, int Mp, size_t row, int c, float v) {
+    uint32_t h, l;
+    pg_split2(v, 0.f, h, l);
+    uint16_t* p = planes + ((size_t)(c / kPgBlk) * Mp + row) * kPgBlkWords + c % kPgBlk;
+    p[0] = (uint16_t)h;
+    p[kPgBlk] = (uint16_t)l;
+}
+#endif
 
 }  // namespace sd2

@@ -1,12 +1,12 @@
-// Projections of more than 16 activation rows with bf16 weights (prefill chunks, verify passes of
-// several sequences, the training-objective forward):
+// Projections with bf16 weights outside the persistent kernel, on any number of activation rows
+// (drafter steps and verify passes of batches, prefill chunks, the training-objective forward):
 //
 //   Y[m][n] (op)= sum_k W[n][k] * xn[m][k],   xn = x (optionally RMS-normalised and scaled by gamma)
 //
-// The activations enter as "planes": k_planes splits each value (times the gain) once into a bf16
-// hi/lo pair and stores it as [K / 64][row][64 hi | 64 lo], the order in which a workgroup stages
-// it, so staging is a linear copy (16-byte loads, 16-byte LDS stores) with no arithmetic.  It also
-// takes 1/rms of every row, which the epilogue applies.
+// The activations enter as "planes": whoever produces a value (times the gain of the norm that
+// reads it) splits it once into a bf16 hi/lo pair and stores it as [K / 64][row][64 hi | 64 lo],
+// the order in which a workgroup stages it, so staging is a linear copy (16-byte loads, 16-byte
+// LDS stores) with no arithmetic.  1/rms of the rows is applied by the epilogue.
 //
 // A workgroup of four waves owns 16 MG rows and 64 NG weight rows: each wave holds 16 NG weight
 // rows of its own, whose fragments it loads straight into registers (a weight is read by one wave
@@ -34,77 +34,52 @@
 namespace sd2 {
 
 typedef __bf16 pg_bf8 __attribute__((ext_vector_type(8)));
-typedef __bf16 pg_bf2 __attribute__((ext_vector_type(2)));
 typedef float pg_f4 __attribute__((ext_vector_type(4)));
-typedef float pg_f2 __attribute__((ext_vector_type(2)));
 typedef unsigned int pg_u4 __attribute__((ext_vector_type(4)));
-typedef int pg_i4 __attribute__((ext_vector_type(4)));
 
-// hi/lo bf16 split of two fp32 values, packed (hi = x rounded to nearest even, lo = (x - hi)
-// rounded likewise)
-__device__ __forceinline__ void pg_split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-    const pg_f2 v = {x0, x1};
-    const pg_bf2 h = __builtin_convertvector(v, pg_bf2);
-    const pg_bf2 l = __builtin_convertvector(v - __builtin_convertvector(h, pg_f2), pg_bf2);
-    hi = __builtin_bit_cast(uint32_t, h);
-    lo = __builtin_bit_cast(uint32_t, l);
-}
-
+// Planes of rows that no producer stored as planes (steering projections, the training objective).
 struct PlaneArgs {
     const float* X;
-    int ldx;
     const int32_t* in_map;  // source row of each row (negative: zeros), or null
-    int M, Mp, K;           // rows, rows of the planes, columns
+    int Mp, K;              // rows of the planes, columns
     const uint16_t* gamma;  // bf16 gain, or null
-    const float* ss;        // [rows][nss] sums of squares (with gamma)
-    int nss;
-    float eps;
     uint16_t* planes;
-    float* inv;             // [M] 1/rms (1 without gamma)
 };
 
-constexpr int kPlaneCols = 1024;  // columns per workgroup of k_planes: one float4 per thread
+constexpr int kPlaneCols = 1024;  // columns per workgroup: one float4 per thread
 
 __global__ __launch_bounds__(256) void k_planes(PlaneArgs a) {
-    const int row = blockIdx.x, tid = threadIdx.x;
+    const int row = blockIdx.x, c = blockIdx.y * kPlaneCols + 4 * threadIdx.x;
     const int src = a.in_map ? a.in_map[row] : row;
-    const int c = blockIdx.y * kPlaneCols + 4 * tid;
-    if (c < a.K) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (src >= 0) v = *(const float4*)(a.X + (size_t)src * a.ldx + c);
-        if (a.gamma) {
-            const uint2 w = *(const uint2*)(a.gamma + c);
-            v.x *= bf16_lo(w.x); v.y *= bf16_hi(w.x); v.z *= bf16_lo(w.y); v.w *= bf16_hi(w.y);
-        }
-        uint2 h, l;
-        pg_split2(v.x, v.y, h.x, l.x);
-        pg_split2(v.z, v.w, h.y, l.y);
-        uint16_t* p = a.planes + ((size_t)(c / kPgBlk) * a.Mp + row) * kPgBlkWords + c % kPgBlk;
-        *(uint2*)p = h;
-        *(uint2*)(p + kPgBlk) = l;
+    if (c >= a.K) return;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (src >= 0) v = *(const float4*)(a.X + (size_t)src * a.K + c);
+    if (a.gamma) {
+        const uint2 w = *(const uint2*)(a.gamma + c);
+        v.x *= bf16_lo(w.x); v.y *= bf16_hi(w.x); v.z *= bf16_lo(w.y); v.w *= bf16_hi(w.y);
     }
-    if (blockIdx.y == 0 && tid < 64) {
-        float sm = 0.f;
-        if (a.gamma && src >= 0)
-            for (int i = tid; i < a.nss; i += 64) sm += a.ss[(size_t)src * a.nss + i];
-        sm = wave_sum(sm);
-        if (tid == 0) a.inv[row] = a.gamma ? rsqrtf(sm / (float)a.K + a.eps) : 1.0f;
-    }
+    pg_put4(a.planes, a.Mp, row, c, v);
 }
 
 struct PgArgs {
     const uint16_t* planes;
-    const float* inv;
+    // RMSNorm input (ss not null): the outputs of a row are scaled by 1/rms, from the nss partial
+    // sums of squares of its source row
+    const float* ss;
+    const int32_t* in_map;
+    int nss;
+    float eps;
     int M, Mp, K, S, nblk_m, nblk_n, nbs;
     const uint16_t* W[3];
     int pairs;          // pairs of 16-row sub-tiles
     int tiles;          // 16-column tiles of the output (store, add, SwiGLU)
     int seg_pairs[2];   // Q|K|V: pairs of Q and of K
-    int mode;
     float* Y;
     int ldy;
     const int32_t* out_map;
     float* ss_out;
+    uint16_t* yplanes;       // SwiGLU: planes of the output, in place of Y; add: planes of the new
+    const uint16_t* ygamma;  // residual times this gain, beside Y; or null
     float* part;
     int32_t* cnt;
     int H, Hkv, hd;
@@ -116,40 +91,76 @@ struct PgArgs {
     int ub_ld;
 };
 
-// Weight row of lane row n in sub-tile `sub` of pair P.
+// Segment (Q, K or V) of pair P, which becomes the pair's number within it.
+__device__ __forceinline__ int pg_seg(const PgArgs& a, int& P) {
+    int seg = 0;
+    if (P >= a.seg_pairs[0]) { P -= a.seg_pairs[0]; seg = 1; }
+    if (seg == 1 && P >= a.seg_pairs[1]) { P -= a.seg_pairs[1]; seg = 2; }
+    return seg;
+}
+
+// Weight row of lane row n in sub-tile `sub` of pair P (P uniform, so that all but n stays scalar).
+template <int MODE>
 __device__ __forceinline__ const uint16_t* pg_row(const PgArgs& a, int P, int sub, int n) {
-    if (a.mode == kEpiSwiglu) return a.W[sub] + (size_t)(P * 16 + n) * a.K;
-    if (a.mode == kEpiQkv) {
-        int seg = 0;
-        if (P >= a.seg_pairs[0]) { P -= a.seg_pairs[0]; seg = 1; }
-        if (seg == 1 && P >= a.seg_pairs[1]) { P -= a.seg_pairs[1]; seg = 2; }
+    if constexpr (MODE == kEpiSwiglu) {
+        return (sub ? a.W[1] : a.W[0]) + (size_t)(P * 16 + n) * a.K;
+    } else if constexpr (MODE == kEpiQkv) {
+        const int seg = pg_seg(a, P);
         const int per = a.hd / 32, h = P / per, p = P % per;
         return (seg == 0 ? a.W[0] : seg == 1 ? a.W[1] : a.W[2]) + (size_t)(h * a.hd + sub * (a.hd / 2) + 16 * p + n) * a.K;
+    } else {
+        // an odd number of tiles leaves the last pair half empty: its second sub-tile re-reads the first
+        return a.W[0] + (size_t)(min(2 * P + sub, a.tiles - 1) * 16 + n) * a.K;
     }
-    // an odd number of tiles leaves the last pair half empty: its second sub-tile re-reads the first
-    return a.W[0] + (size_t)(min(2 * P + sub, a.tiles - 1) * 16 + n) * a.K;
 }
 
 __device__ __forceinline__ pg_f4 pg_ld4(const float* p) { return *(const pg_f4*)p; }
 
-// Epilogue of pair P for one row: lane (n, q) holds columns 4q .. 4q + 3 of both sub-tiles.
-// Executed by all lanes (`valid`: the row exists), since the add mode reduces across lanes.
-__device__ __forceinline__ void pg_epilogue(const PgArgs& a, int P, int row, bool valid, int q, pg_f4 v0, pg_f4 v1) {
-    if (a.mode == kEpiStore) {
+__device__ __forceinline__ void pg_put_gain(const PgArgs& a, int row, int c, pg_f4 v) {
+    const uint2 w = *(const uint2*)(a.ygamma + c);
+    pg_put4(a.yplanes, a.Mp, row, c,
+            make_float4(v.x * bf16_lo(w.x), v.y * bf16_hi(w.x), v.z * bf16_lo(w.y), v.w * bf16_hi(w.y)));
+}
+
+// What an epilogue reads of one pair and row: the residual (add) or the rotation (Q|K|V).
+struct PgPre {
+    pg_f4 a, b;
+};
+template <int MODE>
+__device__ __forceinline__ PgPre pg_pre(const PgArgs& a, int P, int row, int pos, int q) {
+    PgPre r = {};
+    if constexpr (MODE == kEpiAdd) {
+        const float* y = a.Y + (size_t)row * a.ldy + 32 * P + 4 * q;
+        r.a = pg_ld4(y);
+        r.b = pg_ld4(2 * P + 1 < a.tiles ? y + 16 : y);
+    } else if constexpr (MODE == kEpiQkv) {
+        pg_seg(a, P);  // (V pairs read factors they do not use)
+        const size_t o = (size_t)max(pos, 0) * (a.hd / 2) + 16 * (P % (a.hd / 32)) + 4 * q;
+        r.a = pg_ld4(a.rcos + o);
+        r.b = pg_ld4(a.rsin + o);
+    }
+    return r;
+}
+
+// Epilogue of pair P for one row (at position pos): lane (n, q) holds columns 4q .. 4q + 3 of both
+// sub-tiles.  Executed by all lanes (`valid`: the row exists), since the add mode reduces across
+// lanes.
+template <int MODE>
+__device__ __forceinline__ void pg_epilogue(const PgArgs& a, int P, int row, bool valid, int pos, int q, pg_f4 v0,
+                                            pg_f4 v1, const PgPre& pre) {
+    if constexpr (MODE == kEpiStore) {
         if (!valid) return;
         const int orow = a.out_map ? a.out_map[row] : row;
         if (orow < 0) return;
         float* y = a.Y + (size_t)orow * a.ldy + 32 * P + 4 * q;
         *(pg_f4*)y = v0;
         if (2 * P + 1 < a.tiles) *(pg_f4*)(y + 16) = v1;
-    } else if (a.mode == kEpiAdd) {
+    } else if constexpr (MODE == kEpiAdd) {
         const bool two = 2 * P + 1 < a.tiles;
         float s0 = 0.f, s1 = 0.f;
         if (valid) {
             float* y = a.Y + (size_t)row * a.ldy + 32 * P + 4 * q;
-            pg_f4 r0 = pg_ld4(y), r1 = two ? pg_ld4(y + 16) : pg_f4{0.f, 0.f, 0.f, 0.f};
-            r0 += v0;
-            r1 += v1;
+            pg_f4 r0 = pre.a + v0, r1 = pre.b + v1;
             if (a.ubias) {
                 const float* ub = a.ubias + (size_t)a.row_seq[row] * a.ub_ld + 32 * P + 4 * q;
                 r0 += pg_ld4(ub);
@@ -157,6 +168,10 @@ __device__ __forceinline__ void pg_epilogue(const PgArgs& a, int P, int row, boo
             }
             *(pg_f4*)y = r0;
             if (two) *(pg_f4*)(y + 16) = r1;
+            if (a.yplanes) {
+                pg_put_gain(a, row, 32 * P + 4 * q, r0);
+                if (two) pg_put_gain(a, row, 32 * P + 16 + 4 * q, r1);
+            }
             s0 = (r0.x * r0.x + r0.y * r0.y) + (r0.z * r0.z + r0.w * r0.w);
             s1 = (r1.x * r1.x + r1.y * r1.y) + (r1.z * r1.z + r1.w * r1.w);
         }
@@ -168,24 +183,20 @@ __device__ __forceinline__ void pg_epilogue(const PgArgs& a, int P, int row, boo
             a.ss_out[(size_t)row * a.tiles + 2 * P] = s0;
             if (two) a.ss_out[(size_t)row * a.tiles + 2 * P + 1] = s1;
         }
-    } else if (a.mode == kEpiSwiglu) {
+    } else if constexpr (MODE == kEpiSwiglu) {
         if (!valid) return;
         if (a.ubias) v1 += pg_ld4(a.ubias + (size_t)a.row_seq[row] * a.ub_ld + 16 * P + 4 * q);
         pg_f4 o = {silu(v0.x) * v1.x, silu(v0.y) * v1.y, silu(v0.z) * v1.z, silu(v0.w) * v1.w};
-        *(pg_f4*)(a.Y + (size_t)row * a.ldy + 16 * P + 4 * q) = o;
+        if (a.yplanes) pg_put4(a.yplanes, a.Mp, row, 16 * P + 4 * q, make_float4(o.x, o.y, o.z, o.w));
+        else *(pg_f4*)(a.Y + (size_t)row * a.ldy + 16 * P + 4 * q) = o;
     } else {
         if (!valid) return;
-        int seg = 0;
-        if (P >= a.seg_pairs[0]) { P -= a.seg_pairs[0]; seg = 1; }
-        if (seg == 1 && P >= a.seg_pairs[1]) { P -= a.seg_pairs[1]; seg = 2; }
+        const int seg = pg_seg(a, P);
         const int per = a.hd / 32, h = P / per, i = 16 * (P % per) + 4 * q, half = a.hd / 2;
-        const int pos = a.row_pos[row];
         if (seg < 2) {
-            const int pp = pos < 0 ? 0 : pos;
-            const pg_f4 c = pg_ld4(a.rcos + (size_t)pp * half + i), s = pg_ld4(a.rsin + (size_t)pp * half + i);
             const pg_f4 x = v0;
-            v0 = x * c - v1 * s;
-            v1 = v1 * c + x * s;
+            v0 = x * pre.a - v1 * pre.b;
+            v1 = v1 * pre.a + x * pre.b;
         }
         float* y;
         if (seg == 0) {
@@ -200,7 +211,7 @@ __device__ __forceinline__ void pg_epilogue(const PgArgs& a, int P, int row, boo
     }
 }
 
-template <int MG, int NG, int KB>
+template <int MG, int NG, int KB, int MODE>
 __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     static_assert(NG % 2 == 0, "sub-tiles come in pairs");
     constexpr int kBlkB = 16 * MG * kPgBlkWords * 2;    // bytes of one 64-column block in LDS
@@ -208,8 +219,9 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     constexpr int NA = kStageB / (256 * 16);            // 16-byte words per thread and step
     static_assert(NA >= 1, "stage");
     __shared__ __attribute__((aligned(16))) char sm[2 * kStageB];
+    __shared__ float inv_s[16 * MG];
     __shared__ int last_s;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, q = lane >> 4;
     // workgroups are dealt to the 8 XCDs in turn, so blocks b, b + 8, ... share an XCD: they take
     // the row blocks of one weight block, whose weights then come from that XCD's L2
@@ -220,16 +232,10 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     const int P0 = nb * 2 * NG + wave * (NG / 2);       // first pair of this wave
     const uint16_t* wp[NG];
 #pragma unroll
-    for (int j = 0; j < NG; ++j) wp[j] = pg_row(a, min(P0 + j / 2, a.pairs - 1), j & 1, n) + 16 * q;
+    for (int j = 0; j < NG; ++j) wp[j] = pg_row<MODE>(a, min(P0 + j / 2, a.pairs - 1), j & 1, n) + 16 * q;
     // this range's steps of 64 KB columns
     const int nst = a.K / (kPgBlk * KB);
-    const int b0 = (int)((long)nst * s / a.S), b1 = (int)((long)nst * (s + 1) / a.S);
-
-    pg_f4 acc[MG][NG];
-#pragma unroll
-    for (int g = 0; g < MG; ++g)
-#pragma unroll
-        for (int j = 0; j < NG; ++j) acc[g][j] = pg_f4{0.f, 0.f, 0.f, 0.f};
+    const int b0 = nst * s / a.S, b1 = nst * (s + 1) / a.S;
 
     pg_u4 w[KB][2][NG];
     pg_u4 xa[NA];
@@ -253,9 +259,79 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
 #pragma unroll
         for (int e = 0; e < NA; ++e) *(pg_u4*)(sbase + buf * kStageB + e * 4096) = xa[e];
     };
+    // Prologue.  Loads return in the order of their issue: positions, then with few rows the row
+    // statistics (4 MG rows of partial sums of squares per wave, all in flight together), the planes
+    // and the weights of the first step, and what the epilogue reads; the sums are added while the
+    // weights are on their way.  With more rows the statistics would fill the registers: they follow
+    // the weights, eight rows in flight, and the epilogue reads its inputs itself.
+    constexpr bool kFew = MG <= 2;
+    constexpr int RW = 4 * MG, RU = RW < 8 ? RW : 8;
+    int pos[MG];
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+        pos[g] = MODE == kEpiQkv && kFew ? a.row_pos[min(m0 + 16 * g + n, a.M - 1)] : 0;
+    const bool stats = MODE != kEpiAdd && a.ss;
+    const int n4s = a.nss / 4;
+    pg_f4 sv[RU];
+    auto load_ss = [&](int r0, int f0) {
+        int src[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) src[u] = min(m0 + wave * RW + r0 + u, a.M - 1);
+        if (a.in_map)
+#pragma unroll
+            for (int u = 0; u < RU; ++u) src[u] = max(a.in_map[src[u]], 0);
+        const int f = 4 * min(f0 + lane, n4s - 1);
+#pragma unroll
+        for (int u = 0; u < RU; ++u) sv[u] = *(const pg_f4*)(a.ss + (size_t)src[u] * a.nss + f);
+    };
+    auto sum_ss = [&](int r0) {
+        float sm[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) sm[u] = lane < n4s ? (sv[u].x + sv[u].y) + (sv[u].z + sv[u].w) : 0.f;
+        for (int f0 = 64; f0 < n4s; f0 += 64) {
+            load_ss(r0, f0);
+#pragma unroll
+            for (int u = 0; u < RU; ++u)
+                sm[u] += f0 + lane < n4s ? (sv[u].x + sv[u].y) + (sv[u].z + sv[u].w) : 0.f;
+        }
+        // lane u keeps row u's sum
+        float mine = 0.f;
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const float x = wave_sum_dpp(sm[u]);
+            mine = lane == u ? x : mine;
+        }
+        if (lane < RU) inv_s[wave * RW + r0 + lane] = rsqrtf(mine / (float)a.K + a.eps);
+    };
+    if (kFew && stats) load_ss(0, 0);
     load_x(b0);
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) { load_w(b0, kb, 0); load_w(b0, kb, 1); }
+    PgPre pre[kFew ? MG : 1][NG / 2];
+    if constexpr (kFew)
+#pragma unroll
+        for (int g = 0; g < MG; ++g)
+#pragma unroll
+            for (int p = 0; p < NG / 2; ++p)
+                pre[g][p] = pg_pre<MODE>(a, min(P0 + p, a.pairs - 1), min(m0 + 16 * g + n, a.M - 1), pos[g], q);
+    if (stats) {
+        if constexpr (kFew) {
+            sum_ss(0);
+        } else {
+#pragma unroll 1
+            for (int r0 = 0; r0 < RW; r0 += RU) {
+                load_ss(r0, 0);
+                sum_ss(r0);
+            }
+        }
+    } else if (tid < 16 * MG) {
+        inv_s[tid] = 1.0f;
+    }
+    pg_f4 acc[MG][NG];
+#pragma unroll
+    for (int g = 0; g < MG; ++g)
+#pragma unroll
+        for (int j = 0; j < NG; ++j) acc[g][j] = pg_f4{0.f, 0.f, 0.f, 0.f};
     stage(0);
     __syncthreads();
     for (int step = b0; step < b1; ++step) {
@@ -308,12 +384,24 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
         for (int g = 0; g < MG; ++g)
 #pragma unroll
             for (int j = 0; j < NG; ++j) acc[g][j] = pg_f4{0.f, 0.f, 0.f, 0.f};
-        for (int t = 0; t < a.S; ++t) {
-            const float* ps = pt + (size_t)t * kTile;
+        // several ranges' sums per round trip, as many as fit 128 registers (loads past S re-read
+        // the last range and are not added)
+        constexpr int TB = 32 / (MG * NG);
+        for (int t0 = 0; t0 < a.S; t0 += TB) {
+            pg_f4 pv[TB][MG][NG];
 #pragma unroll
-            for (int g = 0; g < MG; ++g)
+            for (int t = 0; t < TB; ++t)
 #pragma unroll
-                for (int j = 0; j < NG; ++j) acc[g][j] += pg_ld4(ps + (g * NG + j) * 256);
+                for (int g = 0; g < MG; ++g)
+#pragma unroll
+                    for (int j = 0; j < NG; ++j)
+                        pv[t][g][j] = pg_ld4(pt + (size_t)min(t0 + t, a.S - 1) * kTile + (g * NG + j) * 256);
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int g = 0; g < MG; ++g)
+#pragma unroll
+                    for (int j = 0; j < NG; ++j) acc[g][j] += t0 + t < a.S ? pv[t][g][j] : pg_f4{0.f, 0.f, 0.f, 0.f};
         }
     }
 #pragma unroll
@@ -321,10 +409,18 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
         const int row = m0 + 16 * g + n;
         const bool valid = row < a.M;
         const int rr = min(row, a.M - 1);
-        const float sc = a.inv[rr];
+        const float sc = inv_s[16 * g + n];
 #pragma unroll
         for (int p = 0; p < NG / 2; ++p)
-            if (P0 + p < a.pairs) pg_epilogue(a, P0 + p, rr, valid, q, acc[g][2 * p] * sc, acc[g][2 * p + 1] * sc);
+            if (P0 + p < a.pairs) {
+                if constexpr (kFew) {
+                    pg_epilogue<MODE>(a, P0 + p, rr, valid, pos[g], q, acc[g][2 * p] * sc, acc[g][2 * p + 1] * sc, pre[g][p]);
+                } else {
+                    const int ps = MODE == kEpiQkv ? a.row_pos[rr] : 0;
+                    pg_epilogue<MODE>(a, P0 + p, rr, valid, ps, q, acc[g][2 * p] * sc, acc[g][2 * p + 1] * sc,
+                                      pg_pre<MODE>(a, P0 + p, rr, ps, q));
+                }
+            }
     }
 }
 
@@ -362,15 +458,35 @@ PgPlan pg_plan(int M, int N, int K) {
 }
 
 template <int MG, int NG, int KB>
-static void pg_launch(hipStream_t s, ProfEntry* pe, dim3 grid, const PgArgs& a) {
-    hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB>), grid, dim3(256), 0, s, pe ? pe->a : nullptr, pe ? pe->b : nullptr, 0, a);
+static void pg_launch(hipStream_t s, ProfEntry* pe, int mode, const PgArgs& a) {
+    const dim3 grid(a.nbs * a.S), blk(256);
+    hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
+    if (mode == kEpiStore) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiStore>), grid, blk, 0, s, ea, eb, 0, a);
+    else if (mode == kEpiAdd) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiAdd>), grid, blk, 0, s, ea, eb, 0, a);
+    else if (mode == kEpiSwiglu) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiSwiglu>), grid, blk, 0, s, ea, eb, 0, a);
+    else hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiQkv>), grid, blk, 0, s, ea, eb, 0, a);
 }
 
 bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
     Workspace& ws = e->ws;
-    if (c.K % 128 || !ws.planes || pg_plane_bytes(c.M, c.K) > ws.planes_n || c.M > e->maxm) return false;
-    if (c.nseg != 1 && c.mode != kEpiQkv && c.mode != kEpiSwiglu) return false;
+    if (c.K % 128 || (c.nseg != 1 && c.mode != kEpiQkv && c.mode != kEpiSwiglu)) return false;
     PgArgs a{};
+    a.M = c.M; a.Mp = pg_rows(c.M); a.K = c.K;
+    a.planes = c.planes;
+    if (!a.planes) {
+        // the MLP's planes are free outside a layer
+        if (!ws.planes || c.M > e->maxm || pg_plane_bytes(c.M, c.K) > ws.ffh_n) return false;
+        PlaneArgs x{};
+        x.X = c.X; x.in_map = c.in_map; x.Mp = a.Mp; x.K = c.K; x.gamma = (const uint16_t*)c.gamma;
+        x.planes = (uint16_t*)ws.ffh;
+        prof_begin(e, kProfOther, 0.0);
+        k_planes<<<dim3(c.M, (c.K + kPlaneCols - 1) / kPlaneCols), 256, 0, s>>>(x);
+        prof_end(e);
+        a.planes = x.planes;
+    }
+    if (c.gamma) {
+        a.ss = c.ss; a.in_map = c.in_map; a.nss = c.nss; a.eps = c.eps;
+    }
     int N = 0;
     for (int i = 0; i < 3; ++i) {
         a.W[i] = i < c.nseg ? (const uint16_t*)c.W[i] : nullptr;
@@ -378,17 +494,8 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
     }
     PgPlan p = pg_plan(c.M, N, c.K);
     if (p.part > ws.ws_part_n || p.cnt > ws.ws_cnt_n) p.S = 1;  // partials must fit the workspace
-    PlaneArgs x{};
-    x.X = c.X; x.ldx = c.K; x.in_map = c.in_map; x.M = c.M; x.Mp = pg_rows(c.M); x.K = c.K;
-    x.gamma = (const uint16_t*)c.gamma; x.ss = c.ss; x.nss = c.nss; x.eps = c.eps;
-    x.planes = ws.planes; x.inv = ws.row_inv;
-    prof_begin(e, kProfOther, 0.0);
-    k_planes<<<dim3(c.M, (c.K + kPlaneCols - 1) / kPlaneCols), 256, 0, s>>>(x);
-    prof_end(e);
-    a.planes = ws.planes; a.inv = ws.row_inv;
-    a.M = c.M; a.Mp = x.Mp; a.K = c.K; a.S = p.S; a.nblk_m = p.nblk_m; a.nblk_n = p.nblk_n;
+    a.S = p.S; a.nblk_m = p.nblk_m; a.nblk_n = p.nblk_n;
     a.nbs = 8 * p.nblk_m * ((p.nblk_n + 7) / 8);
-    a.mode = c.mode;
     if (c.mode == kEpiSwiglu) {
         a.pairs = a.tiles = c.seg_rows[0] / 16;
     } else {
@@ -399,17 +506,17 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
         a.seg_pairs[0] = c.seg_rows[0] / 32;
         a.seg_pairs[1] = c.seg_rows[1] / 32;
     }
-    a.Y = c.Y; a.ldy = c.ldy; a.out_map = c.out_map; a.ss_out = c.ss_out; a.part = c.part; a.cnt = c.cnt;
+    a.Y = c.Y; a.ldy = c.ldy; a.out_map = c.out_map; a.ss_out = c.ss_out;
+    a.yplanes = c.yplanes; a.ygamma = (const uint16_t*)c.ygamma; a.part = c.part; a.cnt = c.cnt;
     a.H = c.H; a.Hkv = c.Hkv; a.hd = c.hd; a.row_pos = c.row_pos; a.row_seq = c.row_seq;
     a.rcos = c.rcos; a.rsin = c.rsin; a.qout = c.qout; a.kc = c.kc; a.vc = c.vc;
     a.cap = c.cap; a.max_batch = c.max_batch; a.layer = c.layer; a.ubias = c.ubias; a.ub_ld = c.ub_ld;
     ProfEntry* pe = prof_slot(e, kProfGemv, (double)N * c.K * 2.0 + (double)c.M * c.K * 4.0 + (double)c.M * N * 4.0);
-    const dim3 grid(a.nbs * p.S);
-    if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, grid, a);
-    else if (p.MG == 2) pg_launch<2, 2, 4>(s, pe, grid, a);
-    else if (p.MG == 4) pg_launch<4, 2, 2>(s, pe, grid, a);
-    else if (p.NG == 2) pg_launch<8, 2, 1>(s, pe, grid, a);
-    else pg_launch<8, 4, 1>(s, pe, grid, a);
+    if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, c.mode, a);
+    else if (p.MG == 2) pg_launch<2, 2, 4>(s, pe, c.mode, a);
+    else if (p.MG == 4) pg_launch<4, 2, 2>(s, pe, c.mode, a);
+    else if (p.NG == 2) pg_launch<8, 2, 1>(s, pe, c.mode, a);
+    else pg_launch<8, 4, 1>(s, pe, c.mode, a);
     if (pe) prof_commit(e);
     return true;
 }

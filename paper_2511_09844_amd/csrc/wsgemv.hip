@@ -422,12 +422,9 @@ WsPlan ws_plan(int M, int N, int K, int mode) {
 }
 
 void launch_wsgemv(Engine* e, hipStream_t s, const WsCall& c) {
-    // more than one 16-row group: the many-row kernel (pgemm.hip), which reads the weights once
-    // per 32 to 128 rows and not per 16; also a full 16-row group against a vocabulary-sized
-    // weight (the batched drafter steps' LM head), which it streams faster
-    int nrows = 0;
-    for (int i = 0; i < c.nseg; ++i) nrows += c.seg_rows[i];
-    if ((c.M > 16 || (c.M == 16 && nrows >= 32768)) && launch_pgemm(e, s, c)) return;
+    // rows that come as planes, and more than one 16-row group, run on the plane kernel
+    // (pgemm.hip); up to 16 fp32 rows (the steering projections) save the launch that makes planes
+    if ((c.planes || c.M > 16) && launch_pgemm(e, s, c)) return;
     for (int r0 = 0; r0 < c.M; r0 += 16) {
         int M = c.M - r0 < 16 ? c.M - r0 : 16;
         WsArgs a{};
