@@ -26,6 +26,7 @@ struct AttnArgs {
     uint16_t* planes;  // output as planes of Mp rows (see pgemm.hip), in place of out; or null
     int Mp;
     const int32_t* row_pos;
+    const int32_t* row_off;  // packed rows: first row of every sequence (its rows: up to the next one's), or null
     int rps, H, Hkv, hd, cap, max_batch, layer;
     int nseq;   // sequences
     int nsplit; // spans the partials have room for
@@ -33,6 +34,12 @@ struct AttnArgs {
     float* part;     // k_pattn: [row][head][nsplit][HD + 2]
     int32_t* cnt;    // one arrival counter per workgroup of the split-free grid
 };
+
+// First row and number of rows of sequence b.
+__device__ __forceinline__ int attn_rows(const AttnArgs& a, int b, int& n) {
+    n = a.row_off ? a.row_off[b + 1] - a.row_off[b] : a.rps;
+    return a.row_off ? a.row_off[b] : b * a.rps;
+}
 
 // One output value, or four neighbouring ones: column c of row `row`.
 __device__ __forceinline__ void attn_put1(const AttnArgs& a, size_t row, int c, float v) {
@@ -89,7 +96,7 @@ __device__ __forceinline__ float pa_colsum(float v) {
 // requested at once.  qpos holds the block's row positions (-1: no row).
 template <int HD>
 __device__ void pa_span_merge(const AttnArgs& a, int grp_id, int nspan, int span_t, int ntile_all, int b, int kvh,
-                              int i0, const int* qpos, int* last_flag) {
+                              int i0, int rbase, int nrows, const int* qpos, int* last_flag) {
     if (!arrive_last(a.cnt + grp_id, nspan, last_flag)) return;
     const int tid = threadIdx.x, G = a.H / a.Hkv;
     const int nlive = min(nspan, ntile_all > 0 ? (ntile_all - 1) / span_t + 1 : 0);
@@ -97,8 +104,8 @@ __device__ void pa_span_merge(const AttnArgs& a, int grp_id, int nspan, int span
     for (int idx = tid; idx < kPaQ * G * D4; idx += 256) {
         const int i = idx / (G * D4), hh = (idx / D4) % G, d = (idx % D4) * 4;
         const int row = i0 + i;
-        if (row >= a.rps) continue;
-        const size_t orow = (size_t)(b * a.rps + row);
+        if (row >= nrows) continue;
+        const size_t orow = (size_t)(rbase + row);
         const int h = kvh * G + hh;
         float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
         if (qpos[i] >= 0 && nlive > 0) {
@@ -153,11 +160,14 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
     const int kvh = (grp_id / nqb) % a.Hkv;
     const int b = grp_id / (nqb * a.Hkv);
     const int i0 = qb * kPaQ;
+    int nrows;
+    const int rbase = attn_rows(a, b, nrows);
+    if (i0 >= nrows) return;  // (uniform)
     if (tid == 0) maxpos_s = -1;
     __syncthreads();
     if (tid < kPaQ) {
         int p = -1;
-        if (i0 + tid < a.rps) p = a.row_pos[b * a.rps + i0 + tid];
+        if (i0 + tid < nrows) p = a.row_pos[rbase + i0 + tid];
         qpos[tid] = p;
         if (p >= 0) atomicMax(&maxpos_s, p);
     }
@@ -195,8 +205,8 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
         float qf[QD];
         {
             const int qrow = i0 + col;
-            const bool ok = qrow < a.rps;
-            const float* qp = a.q + (size_t)(b * a.rps + (ok ? qrow : 0)) * a.q_stride + h * HD + grp * QD;
+            const bool ok = qrow < nrows;
+            const float* qp = a.q + (size_t)(rbase + (ok ? qrow : 0)) * a.q_stride + h * HD + grp * QD;
             const float qs = ok ? a.scale : 0.f;
 #pragma unroll
             for (int s = 0; s < QD; s += 4) {
@@ -301,9 +311,9 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
                         *(pf4*)(dst + t) = pf4{o[t][r] * inv, o[t + 1][r] * inv, o[t + 2][r] * inv, o[t + 3][r] * inv};
                 }
             }
-            if (nspan > 1 && grp == 0 && i0 + col < a.rps) {
+            if (nspan > 1 && grp == 0 && i0 + col < nrows) {
                 // this span's max and sum of the lane's row
-                float* pp = a.part + (((size_t)(b * a.rps + i0 + col) * a.H + h) * a.nsplit + sp) * (HD + 2);
+                float* pp = a.part + (((size_t)(rbase + i0 + col) * a.H + h) * a.nsplit + sp) * (HD + 2);
                 store_through(pp + HD, m_run);
                 store_through(pp + HD + 1, l_run);
             }
@@ -318,11 +328,11 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int i = 0; i < kPaQ; ++i) {
-                const size_t orow = (size_t)(b * a.rps + i0 + i);
+                const size_t orow = (size_t)(rbase + i0 + i);
 #pragma unroll
                 for (int j = 0; j < RW; ++j) {
                     const int d = lane + 64 * j;
-                    if (i0 + i < a.rps && d < HD) {
+                    if (i0 + i < nrows && d < HD) {
                         if (nspan == 1) attn_put1(a, orow, h * HD + d, rv[i][j]);
                         else store_through(a.part + ((orow * a.H + h) * a.nsplit + sp) * (HD + 2) + d, rv[i][j]);
                     }
@@ -331,7 +341,7 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
         }
     }
     if (nspan == 1) return;
-    pa_span_merge<HD>(a, grp_id, nspan, span_t, ntile_all, b, kvh, i0, qpos, &last_flag);
+    pa_span_merge<HD>(a, grp_id, nspan, span_t, ntile_all, b, kvh, i0, rbase, nrows, qpos, &last_flag);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -366,12 +376,14 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
     __shared__ int last_flag;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    const int G = a.H / a.Hkv, nv = a.rps * G;
+    const int G = a.H / a.Hkv;
     // the column groups of one span, which read the same K/V, are 8 workgroups apart: on one XCD
     const int c8 = blockIdx.x / 8, cg = c8 % ncg;
     const int u = (c8 / ncg) * 8 + blockIdx.x % 8;
     const int sp = u % nspan, kvh = (u / nspan) % a.Hkv, b = u / (nspan * a.Hkv);
     if (b >= a.nseq) return;  // grid padding
+    int nrows;
+    const int rbase = attn_rows(a, b, nrows), nv = nrows * G;
     // this lane's query vectors (one per column tile) and their positions
     int vrow[NT], vpos[NT], maxpos = -1;
     const float* qp[NT];
@@ -381,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
         const int v = (cg * NT + t) * 16 + col;
         vok[t] = v < nv;
         const int vc = vok[t] ? v : 0;
-        vrow[t] = b * a.rps + vc / G;
+        vrow[t] = rbase + vc / G;
         const int p = a.row_pos[vrow[t]];
         vpos[t] = vok[t] ? p : -1;
         maxpos = max(maxpos, vpos[t]);
@@ -552,7 +564,7 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
         const int v = cg * NT * 16 + idx / D4, d = (idx % D4) * 4;
         if (v >= nv) break;
         const int h = kvh * G + v % G;
-        const size_t row = (size_t)b * a.rps + v / G, ph = (row * a.H + h) * nspan;
+        const size_t row = (size_t)rbase + v / G, ph = (row * a.H + h) * nspan;
         float M = -INFINITY, L = 0.f;
         pf4 O = {0.f, 0.f, 0.f, 0.f};
         for (int s0 = 0; s0 < nlive; s0 += 8) {
@@ -593,6 +605,8 @@ static void launch_vattn(Engine& e, hipStream_t s, const AttnArgs& a) {
     const int tiles = (a.cap + 15) / 16;
     int nspan = std::min((tiles + kVaMinTiles - 1) / kVaMinTiles, std::max(1, 2048 / (groups * ncg)));
     if ((size_t)groups * ncg > e.ws.attn_cnt_n) nspan = 1;
+    const size_t per = (size_t)a.nseq * a.rps * a.H * (HD + 2);  // the partials' room
+    nspan = std::max<int>(1, std::min<size_t>(nspan, e.ws.attn_part_n / per));
     int span_t = (tiles + nspan - 1) / nspan;
     span_t = (span_t + 3) / 4 * 4;
     nspan = (tiles + span_t - 1) / span_t;
@@ -604,7 +618,7 @@ static void launch_vattn(Engine& e, hipStream_t s, const AttnArgs& a) {
     if (pe) prof_commit(&e);
 }
 
-static void launch_pattn(Engine& e, hipStream_t s, const AttnArgs& a) {
+static void launch_pattn(Engine& e, hipStream_t s, AttnArgs a) {
     const int nqb = (a.rps + kPaQ - 1) / kPaQ;
     const int groups = a.nseq * a.Hkv * nqb;
     // few groups: split the keys into spans for about 2048 workgroups, eight per compute unit,
@@ -614,9 +628,13 @@ static void launch_pattn(Engine& e, hipStream_t s, const AttnArgs& a) {
     if (groups < 256 && (size_t)groups <= e.ws.attn_cnt_n) {
         const int tiles = (a.cap + kPaK - 1) / kPaK;
         nspan = std::min(std::min(kPaMaxSpans, a.nsplit), std::max(1, 2048 / groups));
+        // (as many as the partials have room for)
+        const size_t per = (size_t)a.nseq * a.rps * a.H * (a.hd + 2);
+        nspan = std::max<int>(1, std::min<size_t>(nspan, e.ws.attn_part_n / per));
         span_t = (tiles + nspan - 1) / nspan;
         nspan = (tiles + span_t - 1) / span_t;
     }
+    a.nsplit = nspan;
     dim3 grid(groups * nspan);
     ProfEntry* pe = prof_slot(&e, kProfAttn, 0.0);
     hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
@@ -636,6 +654,7 @@ void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int
     a.planes = e.ws.planes ? (uint16_t*)e.ws.attn : nullptr;
     a.Mp = pg_rows(rows);
     a.row_pos = e.ws.row_pos;
+    a.row_off = e.live_off;
     a.rps = rps; a.H = dm.n_heads; a.Hkv = dm.n_kv_heads; a.hd = m.hd; a.cap = e.cap; a.max_batch = e.cfg.max_batch;
     a.layer = layer;
     a.nseq = rows / rps;

@@ -10,7 +10,11 @@ namespace sd2 {
 
 constexpr int kMaxK = 32;
 constexpr int kVocabChunks = 64;     // vocabulary slices per row in the sampler's partial reductions
-constexpr int kPrefillRows = 512;    // rows per prefill chunk (all sequences together)
+// Rows per prefill chunk (all sequences together).  Larger chunks read the weights fewer times and
+// give the projections enough tiles to fill the chip unsplit (8B layer, per row: 1.33 us at 512
+// rows, 0.73 at 2048).  The small size (see WsForm) is also the most a training-objective chunk may
+// hold.
+constexpr int kPrefillRows = 2048, kPrefillRowsSmall = 512;
 
 struct ModelDev {
     sd2_dims dm;
@@ -52,6 +56,7 @@ struct Workspace {
     // row plans
     int32_t* row_pos;       // [maxm]
     int32_t* row_seq;       // [maxm]
+    int32_t* row_off;       // [max_batch + 1] prefill: first row of each sequence's live rows, and their number
     int32_t* lm_map_d;      // [k][2*max_batch] drafter LM-head output rows per step
     int32_t* steer_map;     // [max_batch]
     int32_t* ident_map;     // [2 max_batch] 0..2 max_batch-1
@@ -86,7 +91,8 @@ struct Workspace {
     float* attn_part;
     int32_t* attn_cnt;
     int32_t* nonfinite;     // set to 1 by the sampler when a logit row it reads holds a NaN or an infinity
-    size_t attn_cnt_n;      // its capacity (counters)
+    size_t attn_cnt_n;      // capacity of attn_cnt (counters)
+    size_t attn_part_n;     // capacity of attn_part (floats)
     // MLP steering (null unless cfg.steering == SD2_STEER_MLP)
     float* taps;            // [3][maxm][d_V] verifier residual after the tap blocks (per-operation path)
     float* tapsel;          // [max_batch][3 d_V] [h; m; l] of each sequence's steering row
@@ -119,7 +125,8 @@ struct Engine {
     float ln_eps;
     int tap_layer[3];       // 0-based verifier layers after which h, m, l are taken
     Workspace ws;
-    int cap, maxm, batch;
+    int cap, maxm, batch, prefill_rows;
+    const int32_t* live_off;  // ws.row_off while a prefill chunk's rows are packed, else null
     bool prefilled;
     hipStream_t stream;
     bool bf16;
@@ -151,9 +158,13 @@ void prof_end(Engine* e);
 ProfEntry* prof_slot(Engine* e, int cls, double bytes);
 void prof_commit(Engine* e);
 
-// lean: without the buffers of the many-row projections (they then run 16 rows at a time)
+// Workspace forms.  kWsFull: prefill chunks of kPrefillRows.  kWsSmall: of kPrefillRowsSmall (fp32
+// weights, and every configuration whose workspace then fits the static one, so that a handle
+// computes the same in either).  kWsLean: small, and without planes, projections then running 16 fp32
+// rows at a time (a static workspace that holds the configuration only so).
+enum WsForm { kWsFull, kWsSmall, kWsLean };
 size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, ModelDev* md, int* maxm,
-             MkState* mk = nullptr, bool lean = false);
+             MkState* mk = nullptr, WsForm form = kWsFull);
 
 // ---- launchers (kernels.hip) ----
 void launch_rope_table(hipStream_t s, ModelDev& m, int cap);
@@ -204,6 +215,7 @@ struct WsCall {
     const float *rcos, *rsin;
     float *qout, *kc, *vc;
     int cap, max_batch, layer;
+    const int32_t* m_live;   // rows that hold data, of M (on the device; null: all of them)
     const uint16_t* planes;  // X as planes, times the gain (else made from X)
     uint16_t* yplanes;       // planes of the output (see PgArgs), with the gain ygamma
     const void* ygamma;

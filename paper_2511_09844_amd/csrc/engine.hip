@@ -96,9 +96,15 @@ int bias_len(const sd2_config& c) {
     return c.steering == SD2_STEER_MLP ? c.drafter.n_layers * c.drafter.d_ff : c.drafter.d_model;
 }
 
-int max_rows(const sd2_config& c) {
+WsForm ws_form(const sd2_config& c) {
+    return c.dtype == SD2_F32 || carve(c, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, kWsSmall) <= kStaticWorkspaceBytes
+               ? kWsSmall
+               : kWsFull;
+}
+
+int max_rows(const sd2_config& c, int prefill) {
     int B = c.max_batch;
-    return std::max(std::max(B * (c.k + 1), 2 * B), kPrefillRows);
+    return std::max(std::max(B * (c.k + 1), 2 * B), prefill);
 }
 
 void model_dims(ModelDev* m, const sd2_dims& d) {
@@ -112,10 +118,10 @@ void model_dims(ModelDev* m, const sd2_dims& d) {
 namespace sd2 {
 
 size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, ModelDev* md, int* maxm_out,
-             MkState* mk, bool lean) {
+             MkState* mk, WsForm form) {
     Carver cv{base};
     int B = c.max_batch, k = c.k, cap = c.max_seq_len, V = c.verifier.vocab;
-    int maxm = max_rows(c);
+    int maxm = max_rows(c, form == kWsFull ? kPrefillRows : kPrefillRowsSmall);
     if (maxm_out) *maxm_out = maxm;
     ModelDev tv, td;
     model_dims(&tv, c.verifier);
@@ -135,6 +141,7 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
     w.hcap_ss = cv.take<float>((size_t)B * (c.verifier.d_model / 16));
     w.row_pos = cv.take<int32_t>(maxm);
     w.row_seq = cv.take<int32_t>(maxm);
+    if (c.dtype == SD2_BF16 && form != kWsLean) w.row_off = cv.take<int32_t>(B + 1);
     w.lm_map_d = cv.take<int32_t>((size_t)k * 2 * B);
     w.steer_map = cv.take<int32_t>(B);
     w.ident_map = cv.take<int32_t>(2 * (size_t)B);
@@ -142,7 +149,7 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
     int att = std::max(c.verifier.n_heads * ms[0]->hd, c.drafter.n_heads * ms[1]->hd);
     int ff = std::max(c.verifier.d_ff, c.drafter.d_ff);
     w.qkv = cv.take<float>((size_t)maxm * qkv);
-    const bool planes = c.dtype == SD2_BF16 && !lean;
+    const bool planes = c.dtype == SD2_BF16 && form != kWsLean;
     w.attn = cv.take<float>(planes ? pg_plane_bytes(maxm, att) / 4 : (size_t)maxm * att);
     w.ffh_n = planes ? pg_plane_bytes(maxm, ff) : 0;
     w.ffh = cv.take<float>(planes ? w.ffh_n / 4 : (size_t)maxm * ff);
@@ -216,9 +223,11 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
             for (int rows = 16; rows <= pg_rows(maxm); rows += 16)
                 for (auto& sh : shapes) {
                     if (sh[0] <= 0) continue;
-                    const PgPlan p = pg_plan(rows, sh[0], sh[1]);
-                    pmax = std::max(pmax, p.part);
-                    pg_cnt = std::max(pg_cnt, p.cnt);
+                    for (int packed = 0; packed < 2; ++packed) {
+                        const PgPlan p = pg_plan(rows, sh[0], sh[1], packed);
+                        pmax = std::max(pmax, p.part);
+                        pg_cnt = std::max(pg_cnt, p.cnt);
+                    }
                 }
         }
         w.ws_part = cv.take<float>(std::max<size_t>(pmax, 1));
@@ -236,12 +245,14 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
         const sd2_dims* dd[2] = {&c.verifier, &c.drafter};
         for (int i = 0; i < 2; ++i) {
             int hd = dd[i]->d_model / dd[i]->n_heads;
-            amax = std::max(amax, (size_t)maxm * dd[i]->n_heads * attn_nsplit(cap) * (hd + 2));
+            // (a prefill chunk splits its keys only as far as its partials fit)
+            amax = std::max(amax, (size_t)max_rows(c, kPrefillRowsSmall) * dd[i]->n_heads * attn_nsplit(cap) * (hd + 2));
         }
         // the residual's planes share the attention partials' memory: these live within one
         // attention launch, those from the launch that writes the residual to the projection on it
         const size_t pn = planes ? pg_plane_bytes(maxm, std::max(c.verifier.d_model, c.drafter.d_model)) : 0;
-        w.attn_part = cv.take<float>(std::max(amax, pn / 4));
+        w.attn_part_n = std::max(amax, pn / 4);
+        w.attn_part = cv.take<float>(w.attn_part_n);
         w.planes = planes ? (uint16_t*)w.attn_part : nullptr;
         // arrival counters: the largest split-free grid of any launch shape
         size_t gmax = 1;
@@ -251,7 +262,7 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
             gmax = std::max(gmax, attn_groups(B, 1, d.n_heads, d.n_kv_heads));
             gmax = std::max(gmax, attn_groups(B * (c.k + 1), c.k + 1, d.n_heads, d.n_kv_heads));
             for (int nseq = 1; nseq <= B; ++nseq) {
-                int rps = std::max(1, kPrefillRows / nseq);
+                int rps = std::max(1, kPrefillRowsSmall / nseq);
                 gmax = std::max(gmax, attn_groups(nseq * rps, rps, d.n_heads, d.n_kv_heads));
             }
         }
@@ -487,7 +498,7 @@ extern "C" {
 
 size_t sd2_workspace_bytes(const sd2_config* cfg) {
     if (!config_ok(cfg)) return 0;
-    return carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr);
+    return carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, ws_form(*cfg));
 }
 
 const char* sd2_status_string(sd2_status s) {
@@ -533,9 +544,11 @@ static sd2_status create_impl(const sd2_config* cfg, const sd2_weights* verifier
     if (!unsteered && !aligned16(w_steer)) return SD2_ERR_INVALID_ARG;
     if (!workspace || ((uintptr_t)workspace % kAlign) != 0) return SD2_ERR_INVALID_ARG;
     size_t need = sd2_workspace_bytes(cfg);
-    // the static workspace may hold a configuration only without the many-row projections' buffers
-    const bool lean = slot && need > workspace_bytes;
-    if (lean) need = carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, true);
+    WsForm form = ws_form(*cfg);
+    if (slot && need > workspace_bytes) {
+        form = kWsLean;
+        need = carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, form);
+    }
     if (workspace_bytes < need) return SD2_ERR_INVALID_ARG;
     // the kernels are built for gfx950 with XNACK (page-fault replay) off, MI355X's default mode
     {
@@ -557,6 +570,7 @@ static sd2_status create_impl(const sd2_config* cfg, const sd2_weights* verifier
     }
     e->cfg = *cfg;
     e->cap = cfg->max_seq_len;
+    e->prefill_rows = form == kWsFull ? kPrefillRows : kPrefillRowsSmall;
     e->bf16 = cfg->dtype == SD2_BF16;
     e->stream = (hipStream_t)hip_stream;
     e->w_steer = unsteered ? nullptr : w_steer;
@@ -585,7 +599,7 @@ static sd2_status create_impl(const sd2_config* cfg, const sd2_weights* verifier
     }
     // Graph replay needs a capturable (non-null) stream; SD2_NO_GRAPH=1 forces eager launches.
     e->use_graph = hip_stream != nullptr && getenv("SD2_NO_GRAPH") == nullptr;
-    carve(*cfg, (char*)workspace, &e->ws, &e->mv, &e->md, &e->maxm, &e->mk, lean);
+    carve(*cfg, (char*)workspace, &e->ws, &e->mv, &e->md, &e->maxm, &e->mk, form);
     const sd2_weights* src[2] = {verifier, drafter};
     ModelDev* dst[2] = {&e->mv, &e->md};
     for (int i = 0; i < 2; ++i) {
@@ -650,7 +664,7 @@ static size_t loss_carve(const sd2_config& c, int n, int chunk, char* base, Loss
 
 size_t sd2_train_loss_scratch_bytes(const sd2_config* cfg, int32_t max_len, int32_t rows_per_chunk) {
     if (!config_ok(cfg) || cfg->steering != SD2_STEER_INPUT) return 0;
-    if (max_len < 2 || max_len > cfg->max_seq_len || rows_per_chunk < 1 || rows_per_chunk > kPrefillRows) return 0;
+    if (max_len < 2 || max_len > cfg->max_seq_len || rows_per_chunk < 1 || rows_per_chunk > kPrefillRowsSmall) return 0;
     return loss_carve(*cfg, max_len, rows_per_chunk, nullptr, nullptr);
 }
 
@@ -660,7 +674,7 @@ sd2_status sd2_train_loss(sd2_handle_t h, const int32_t* tokens, const int32_t* 
     if (!h || !tokens || !deltas || !out_kl || !out_loss || !scratch) return SD2_ERR_INVALID_ARG;
     Engine* e = reinterpret_cast<Engine*>(h);
     if (e->cfg.steering != SD2_STEER_INPUT) return SD2_ERR_UNSUPPORTED;
-    if (n < 2 || rows_per_chunk < 1 || rows_per_chunk > kPrefillRows) return SD2_ERR_INVALID_ARG;
+    if (n < 2 || rows_per_chunk < 1 || rows_per_chunk > kPrefillRowsSmall) return SD2_ERR_INVALID_ARG;
     if (n > e->cap) return SD2_ERR_CAPACITY;
     if ((uintptr_t)scratch % kAlign || scratch_bytes < loss_carve(e->cfg, n, rows_per_chunk, nullptr, nullptr))
         return SD2_ERR_INVALID_ARG;
@@ -678,7 +692,7 @@ sd2_status sd2_create_noalloc(const sd2_config* cfg, const sd2_weights* verifier
     if (!out) return SD2_ERR_INVALID_ARG;
     *out = nullptr;
     if (!config_ok(cfg) || mlp_form(*cfg)) return SD2_ERR_INVALID_ARG;
-    if (carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, true) > kStaticWorkspaceBytes)
+    if (carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, kWsLean) > kStaticWorkspaceBytes)
         return SD2_ERR_CAPACITY;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return SD2_ERR_HIP;
@@ -720,11 +734,13 @@ sd2_status sd2_prefill(sd2_handle_t h, int32_t batch, const int32_t* tokens, con
     if ((int64_t)max_prompt + e->cfg.max_new_tokens + e->cfg.k + 1 > e->cap) return SD2_ERR_CAPACITY;
     hipStream_t s = e->stream;
     e->batch = batch;
-    int chunk = std::max(1, std::min(max_prompt - 1, kPrefillRows / batch));
+    int chunk = std::max(1, std::min(max_prompt - 1, e->prefill_rows / batch));
     int rows = batch * chunk;
     int nchunks = max_prompt > 1 ? (max_prompt - 1 + chunk - 1) / chunk : 0;
     hipError_t err = hipMemsetAsync(e->ws.hcap, 0, sizeof(float) * (size_t)batch * e->mv.dm.d_model, s);
     if (err != hipSuccess) return hip_fail(e, err, "hipMemsetAsync");
+    // several prompts: the rows a chunk has of each are packed, and the launches cover only those
+    e->live_off = batch > 1 ? e->ws.row_off : nullptr;
     for (int c = 0; c < nchunks; ++c) {
         launch_plan_embed(s, *e, e->mv, kPlanPrefill, c, rows, tokens, lens, max_prompt, chunk);
         for (int l = 0; l < e->mv.dm.n_layers; ++l) {
@@ -735,12 +751,14 @@ sd2_status sd2_prefill(sd2_handle_t h, int32_t batch, const int32_t* tokens, con
     }
     // the first round's steering from position len-2 (a one-token prompt gets none: the finish
     // step below clears it)
+    // (the steering rows are one per sequence)
     if (e->mlp) launch_mlp_steer(*e, nullptr, nullptr, batch);
     else if (e->w_steer) launch_steer(*e, e->ws.hcap, e->ws.hcap_ss, nullptr, batch);
     for (int c = 0; c < nchunks; ++c) {
         launch_plan_embed(s, *e, e->md, kPlanPrefill, c, rows, tokens, lens, max_prompt, chunk);
         for (int l = 0; l < e->md.dm.n_layers; ++l) launch_layer(s, *e, e->md, l, rows, chunk);
     }
+    e->live_off = nullptr;
     launch_prefill_finish(s, *e, batch, tokens, lens, max_prompt);
     sd2_status st = check_launch(e, "prefill");
     if (st != SD2_OK) return st;

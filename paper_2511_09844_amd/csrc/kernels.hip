@@ -60,6 +60,7 @@ struct PlanArgs {
     float* x;
     float* ss;   // [rows][d/16]
     const void* embed;
+    const int32_t* live;    // prefill with packed rows (planned by k_prefill_plan): their number; or null
     uint16_t* planes;       // planes of the rows times the first layer's norm gain, or null
     const uint16_t* gamma;
     int Mp;
@@ -108,6 +109,12 @@ __global__ __launch_bounds__(256) void k_plan_embed(PlanArgs a) {
             tok = i == 0 ? a.hist[(size_t)b * a.cap + t - 1] : a.drafts[b * a.k + i - 1];
             active = true;
         }
+    } else if (a.live) {  // prefill chunk, packed
+        if (r >= *a.live) return;
+        b = a.row_seq[r];
+        pos = a.row_pos[r];
+        tok = a.prompt_tok[(size_t)b * a.max_prompt + pos];
+        active = true;
     } else {  // prefill chunk
         b = r / a.chunk;
         int i = r % a.chunk;
@@ -119,7 +126,7 @@ __global__ __launch_bounds__(256) void k_plan_embed(PlanArgs a) {
     }
     if (!active) pos = -1;
     tok = tok < 0 ? 0 : (tok >= a.vocab ? a.vocab - 1 : tok);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && !a.live) {
         a.row_pos[r] = pos;
         a.row_seq[r] = b;
     }
@@ -148,6 +155,38 @@ __global__ __launch_bounds__(256) void k_plan_embed(PlanArgs a) {
     }
 }
 
+// Packed rows of a prefill chunk: positions j * chunk .. of every sequence that has them (its last
+// prompt token excluded), sequence after sequence; rows past the last are inactive.  One block.
+__global__ __launch_bounds__(256) void k_prefill_plan(const int32_t* prompt_len, int max_prompt, int batch, int j,
+                                                      int chunk, int rows, int32_t* row_pos, int32_t* row_seq,
+                                                      int32_t* row_off) {
+    __shared__ int off[257];
+    const int tid = threadIdx.x;
+    const int n = tid < batch ? min(max(min(prompt_len[tid], max_prompt) - 1 - j * chunk, 0), chunk) : 0;
+    if (tid == 0) off[0] = 0;
+    off[tid + 1] = n;
+    __syncthreads();
+    for (int d = 1; d < 256; d *= 2) {
+        const int v = tid >= d ? off[tid + 1 - d] : 0;
+        __syncthreads();
+        off[tid + 1] += v;
+        __syncthreads();
+    }
+    if (tid <= batch) row_off[tid] = off[tid];
+    if (tid == 0) row_off[batch] = off[batch];
+    for (int idx = tid; idx < batch * chunk; idx += 256) {
+        const int b = idx / chunk, i = idx % chunk;
+        if (i < off[b + 1] - off[b]) {
+            row_pos[off[b] + i] = j * chunk + i;
+            row_seq[off[b] + i] = b;
+        }
+    }
+    for (int r = off[batch] + tid; r < rows; r += 256) {
+        row_pos[r] = -1;
+        row_seq[r] = 0;
+    }
+}
+
 void launch_plan_embed(hipStream_t s, Engine& e, ModelDev& m, int kind, int j, int rows, const int32_t* prompt_tok,
                        const int32_t* prompt_len, int max_prompt, int chunk, const float* row_add) {
     PlanArgs a;
@@ -160,7 +199,11 @@ void launch_plan_embed(hipStream_t s, Engine& e, ModelDev& m, int kind, int j, i
     a.add_steer = !e.mlp && e.w_steer && (&m == &e.md) && (kind == kPlanDraft1 || kind == kPlanDraftJ);
     a.row_pos = e.ws.row_pos; a.row_seq = e.ws.row_seq; a.x = m.x; a.ss = m.ss; a.embed = m.embed;
     a.planes = e.ws.planes; a.gamma = (const uint16_t*)m.layer[kAttnNorm]; a.Mp = pg_rows(rows);
+    a.live = kind == kPlanPrefill && e.live_off ? e.live_off + e.batch : nullptr;
     prof_begin(&e, kProfOther, 0.0);
+    if (a.live)
+        k_prefill_plan<<<1, 256, 0, s>>>(prompt_len, max_prompt, e.batch, j, chunk, rows, e.ws.row_pos, e.ws.row_seq,
+                                         e.ws.row_off);
     if (e.bf16) k_plan_embed<uint16_t><<<rows, 256, 0, s>>>(a);
     else k_plan_embed<float><<<rows, 256, 0, s>>>(a);
     prof_end(&e);
@@ -426,8 +469,10 @@ void launch_layer(hipStream_t s, Engine& e, ModelDev& m, int layer, int rows, in
         uint16_t* const xp = e.ws.planes;
         uint16_t* const ap = xp ? (uint16_t*)e.ws.attn : nullptr;
         uint16_t* const fp = xp ? (uint16_t*)e.ws.ffh : nullptr;
+        const int32_t* const live = e.live_off ? e.live_off + e.batch : nullptr;
         // Q|K|V with the attention RMSNorm as prologue, RoPE and the cache append as epilogue
         WsCall c = ws_base(e, m);
+        c.m_live = live;
         c.planes = xp;
         c.X = m.x; c.M = rows; c.K = dm.d_model; c.gamma = W[kAttnNorm]; c.ss = m.ss;
         c.W[0] = W[kWq]; c.W[1] = W[kWk]; c.W[2] = W[kWv];
@@ -442,21 +487,21 @@ void launch_layer(hipStream_t s, Engine& e, ModelDev& m, int layer, int rows, in
         WsCall o = ws_base(e, m);
         o.X = e.ws.attn; o.M = rows; o.K = H * hd; o.W[0] = W[kWo]; o.seg_rows[0] = dm.d_model; o.nseg = 1;
         o.mode = kEpiAdd; o.Y = m.x; o.ldy = dm.d_model; o.ss_out = m.ss;
-        o.planes = ap; o.yplanes = xp; o.ygamma = W[kFfnNorm];
+        o.m_live = live; o.planes = ap; o.yplanes = xp; o.ygamma = W[kFfnNorm];
         launch_wsgemv(&e, s, o);
         // gate|up with the FFN RMSNorm prologue and SwiGLU epilogue
         WsCall g = ws_base(e, m);
         g.X = m.x; g.M = rows; g.K = dm.d_model; g.gamma = W[kFfnNorm]; g.ss = m.ss;
         g.W[0] = W[kWg]; g.W[1] = W[kWu]; g.seg_rows[0] = dm.d_ff; g.seg_rows[1] = dm.d_ff; g.nseg = 2;
         g.mode = kEpiSwiglu; g.Y = e.ws.ffh; g.ldy = dm.d_ff;
-        g.planes = xp; g.yplanes = fp;
+        g.m_live = live; g.planes = xp; g.yplanes = fp;
         g.ubias = up_bias; g.ub_ld = ub_ld; g.row_seq = bias_rows;
         launch_wsgemv(&e, s, g);
         // down projection + residual
         WsCall d = ws_base(e, m);
         d.X = e.ws.ffh; d.M = rows; d.K = dm.d_ff; d.W[0] = W[kWd]; d.seg_rows[0] = dm.d_model; d.nseg = 1;
         d.mode = kEpiAdd; d.Y = m.x; d.ldy = dm.d_model; d.ss_out = m.ss;
-        d.planes = fp; d.yplanes = xp; d.ygamma = layer + 1 < dm.n_layers ? W[9 + kAttnNorm] : m.final_norm;
+        d.m_live = live; d.planes = fp; d.yplanes = xp; d.ygamma = layer + 1 < dm.n_layers ? W[9 + kAttnNorm] : m.final_norm;
         d.ubias = out_bias; d.ub_ld = ub_ld; d.row_seq = bias_rows;
         launch_wsgemv(&e, s, d);
         return;

@@ -13,12 +13,19 @@ constexpr size_t kPgSlack = 128 * kPgBlkWords * 2;
 
 // Shape of a launch: 16 MG rows by 64 NG weight rows per workgroup, K in S ranges.
 struct PgPlan {
-    int MG, NG, S, nblk_m, nblk_n;
+    int MG, NG, S, nblk_m, nblk_n, grid;
     size_t part;  // floats of split-K partials (0 without a split)
     size_t cnt;   // arrival counters
 };
-// N: weight rows, counting gate and up together.
-PgPlan pg_plan(int M, int N, int K);
+// K ranges for a number of blocks: up to two workgroups per CU (one with up to 32 rows, 16 MG).
+__host__ __device__ inline int pg_ranges(int blocks, int MG, int K) {
+    const int target = MG <= 2 ? 256 : 512, min_k = MG <= 2 ? 256 : 512;
+    const int s = target / blocks < K / min_k ? target / blocks : K / min_k;
+    return s > 1 ? s : 1;
+}
+// N: weight rows, counting gate and up together.  packed: the rows that hold data may be fewer
+// than M; the kernel then takes blocks and ranges for those (any number may occur).
+PgPlan pg_plan(int M, int N, int K, bool packed = false);
 
 inline int pg_rows(int M) { return (M + 15) / 16 * 16; }
 // bytes of the planes of M rows and K columns

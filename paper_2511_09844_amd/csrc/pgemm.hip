@@ -69,6 +69,7 @@ struct PgArgs {
     const int32_t* in_map;
     int nss;
     float eps;
+    const int32_t* m_live;  // rows that hold data, of M (null: all)
     int M, Mp, K, S, nblk_m, nblk_n, nbs;
     const uint16_t* W[3];
     int pairs;          // pairs of 16-row sub-tiles
@@ -225,8 +226,18 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     const int n = lane & 15, q = lane >> 4;
     // workgroups are dealt to the 8 XCDs in turn, so blocks b, b + 8, ... share an XCD: they take
     // the row blocks of one weight block, whose weights then come from that XCD's L2
-    const int s = blockIdx.x / a.nbs, bb = blockIdx.x % a.nbs;
-    const int r = bb >> 3, mb = r % a.nblk_m, nb = (bb & 7) + 8 * (r / a.nblk_m);
+    // with packed rows, blocks and ranges are those of the rows that hold data
+    int M = a.M, nblk_m = a.nblk_m, nbs = a.nbs, S = a.S;
+    if (a.m_live) {
+        M = *a.m_live;
+        if (M == 0) return;
+        nblk_m = (M + 16 * MG - 1) / (16 * MG);
+        nbs = 8 * nblk_m * ((a.nblk_n + 7) / 8);
+        S = S > 1 ? pg_ranges(nblk_m * a.nblk_n, MG, a.K) : 1;
+    }
+    const int s = blockIdx.x / nbs, bb = blockIdx.x % nbs;
+    if (s >= S) return;
+    const int r = bb >> 3, mb = r % nblk_m, nb = (bb & 7) + 8 * (r / nblk_m);
     if (nb >= a.nblk_n) return;  // grid padding (uniform per workgroup)
     const int m0 = mb * 16 * MG;
     const int P0 = nb * 2 * NG + wave * (NG / 2);       // first pair of this wave
@@ -235,7 +246,7 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     for (int j = 0; j < NG; ++j) wp[j] = pg_row<MODE>(a, min(P0 + j / 2, a.pairs - 1), j & 1, n) + 16 * q;
     // this range's steps of 64 KB columns
     const int nst = a.K / (kPgBlk * KB);
-    const int b0 = nst * s / a.S, b1 = nst * (s + 1) / a.S;
+    const int b0 = nst * s / S, b1 = nst * (s + 1) / S;
 
     pg_u4 w[KB][2][NG];
     pg_u4 xa[NA];
@@ -269,14 +280,14 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     int pos[MG];
 #pragma unroll
     for (int g = 0; g < MG; ++g)
-        pos[g] = MODE == kEpiQkv && kFew ? a.row_pos[min(m0 + 16 * g + n, a.M - 1)] : 0;
+        pos[g] = MODE == kEpiQkv && kFew ? a.row_pos[min(m0 + 16 * g + n, M - 1)] : 0;
     const bool stats = MODE != kEpiAdd && a.ss;
     const int n4s = a.nss / 4;
     pg_f4 sv[RU];
     auto load_ss = [&](int r0, int f0) {
         int src[RU];
 #pragma unroll
-        for (int u = 0; u < RU; ++u) src[u] = min(m0 + wave * RW + r0 + u, a.M - 1);
+        for (int u = 0; u < RU; ++u) src[u] = min(m0 + wave * RW + r0 + u, M - 1);
         if (a.in_map)
 #pragma unroll
             for (int u = 0; u < RU; ++u) src[u] = max(a.in_map[src[u]], 0);
@@ -313,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
         for (int g = 0; g < MG; ++g)
 #pragma unroll
             for (int p = 0; p < NG / 2; ++p)
-                pre[g][p] = pg_pre<MODE>(a, min(P0 + p, a.pairs - 1), min(m0 + 16 * g + n, a.M - 1), pos[g], q);
+                pre[g][p] = pg_pre<MODE>(a, min(P0 + p, a.pairs - 1), min(m0 + 16 * g + n, M - 1), pos[g], q);
     if (stats) {
         if constexpr (kFew) {
             sum_ss(0);
@@ -365,12 +376,12 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
         __syncthreads();
     }
 
-    if (a.S > 1) {
+    if (S > 1) {
         // every range writes its sums through, lane by lane; the last to arrive adds them in range
         // order (see arrive_last)
-        const size_t tile = (size_t)nb * a.nblk_m + mb;
+        const size_t tile = (size_t)nb * nblk_m + mb;
         constexpr int kTile = MG * NG * 4 * 256;  // floats
-        float* pt = a.part + tile * a.S * kTile + (size_t)wave * MG * NG * 256 + lane * 4;
+        float* pt = a.part + tile * S * kTile + (size_t)wave * MG * NG * 256 + lane * 4;
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc(pt + (size_t)s * kTile - lane * 4, 0, MG * NG * 1024, 0x00027000);
 #pragma unroll
@@ -379,7 +390,7 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
             for (int j = 0; j < NG; ++j)
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(pg_u4, acc[g][j]), rs,
                                                        (g * NG + j) * 1024 + lane * 16, 0, 16 /* sc1 */);
-        if (!arrive_last(a.cnt + tile, a.S, &last_s)) return;
+        if (!arrive_last(a.cnt + tile, S, &last_s)) return;
 #pragma unroll
         for (int g = 0; g < MG; ++g)
 #pragma unroll
@@ -387,7 +398,7 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
         // several ranges' sums per round trip, as many as fit 128 registers (loads past S re-read
         // the last range and are not added)
         constexpr int TB = 32 / (MG * NG);
-        for (int t0 = 0; t0 < a.S; t0 += TB) {
+        for (int t0 = 0; t0 < S; t0 += TB) {
             pg_f4 pv[TB][MG][NG];
 #pragma unroll
             for (int t = 0; t < TB; ++t)
@@ -395,20 +406,20 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
                 for (int g = 0; g < MG; ++g)
 #pragma unroll
                     for (int j = 0; j < NG; ++j)
-                        pv[t][g][j] = pg_ld4(pt + (size_t)min(t0 + t, a.S - 1) * kTile + (g * NG + j) * 256);
+                        pv[t][g][j] = pg_ld4(pt + (size_t)min(t0 + t, S - 1) * kTile + (g * NG + j) * 256);
 #pragma unroll
             for (int t = 0; t < TB; ++t)
 #pragma unroll
                 for (int g = 0; g < MG; ++g)
 #pragma unroll
-                    for (int j = 0; j < NG; ++j) acc[g][j] += t0 + t < a.S ? pv[t][g][j] : pg_f4{0.f, 0.f, 0.f, 0.f};
+                    for (int j = 0; j < NG; ++j) acc[g][j] += t0 + t < S ? pv[t][g][j] : pg_f4{0.f, 0.f, 0.f, 0.f};
         }
     }
 #pragma unroll
     for (int g = 0; g < MG; ++g) {
         const int row = m0 + 16 * g + n;
-        const bool valid = row < a.M;
-        const int rr = min(row, a.M - 1);
+        const bool valid = row < M;
+        const int rr = min(row, M - 1);
         const float sc = inv_s[16 * g + n];
 #pragma unroll
         for (int p = 0; p < NG / 2; ++p)
@@ -433,15 +444,13 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
 // 64-row blocks take short K with few columns, where even split 128-row blocks leave workgroups
 // idle (128 rows of O 8B: 28 against 34 us).  S: up to two workgroups per CU, one with up to 32
 // rows (24 rows of gate|up: 55 us unsplit, 60 with S 2; of Q|K|V: 19 with S 4, 23 with S 8).
-PgPlan pg_plan(int M, int N, int K) {
+PgPlan pg_plan(int M, int N, int K, bool packed) {
     PgPlan p{};
     const int rows = pg_rows(M);
     auto blocks = [&](int mg, int ng) { return ((rows + 16 * mg - 1) / (16 * mg)) * ((N + 64 * ng - 1) / (64 * ng)); };
-    int target = 512, min_k = 512;
     p.NG = 2;
     if (rows <= 32 && K % 256 == 0) {
         p.MG = rows <= 16 ? 1 : 2;
-        target = min_k = 256;
     } else if (rows <= 64 || blocks(8, 2) * (K / 512) < 512) {
         p.MG = 4;
     } else {
@@ -450,16 +459,31 @@ PgPlan pg_plan(int M, int N, int K) {
     }
     p.nblk_m = (rows + 16 * p.MG - 1) / (16 * p.MG);
     p.nblk_n = (N + 64 * p.NG - 1) / (64 * p.NG);
-    const int nb = p.nblk_m * p.nblk_n;
-    p.S = std::max(1, std::min(target / nb, K / min_k));
-    p.part = p.S > 1 ? (size_t)nb * p.S * p.MG * p.NG * 1024 : 0;
+    const int nb = p.nblk_m * p.nblk_n, tile = p.MG * p.NG * 1024;
+    p.S = pg_ranges(nb, p.MG, K);
+    p.grid = 8 * p.nblk_m * ((p.nblk_n + 7) / 8) * p.S;
+    if (packed) {
+        // the most any number of row blocks asks for
+        int part = 0;
+        p.S = 1;
+        for (int m = 1; m <= p.nblk_m; ++m) {
+            const int S = pg_ranges(m * p.nblk_n, p.MG, K);
+            p.grid = std::max(p.grid, 8 * m * ((p.nblk_n + 7) / 8) * S);
+            p.S = std::max(p.S, S);
+            if (S > 1) part = std::max(part, m * p.nblk_n * S);
+        }
+        p.part = (size_t)part * tile;
+        p.cnt = part ? nb : 0;
+        return p;
+    }
+    p.part = p.S > 1 ? (size_t)nb * p.S * tile : 0;
     p.cnt = p.S > 1 ? nb : 0;
     return p;
 }
 
 template <int MG, int NG, int KB>
-static void pg_launch(hipStream_t s, ProfEntry* pe, int mode, const PgArgs& a) {
-    const dim3 grid(a.nbs * a.S), blk(256);
+static void pg_launch(hipStream_t s, ProfEntry* pe, int mode, dim3 grid, const PgArgs& a) {
+    const dim3 blk(256);
     hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
     if (mode == kEpiStore) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiStore>), grid, blk, 0, s, ea, eb, 0, a);
     else if (mode == kEpiAdd) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiAdd>), grid, blk, 0, s, ea, eb, 0, a);
@@ -492,8 +516,13 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
         a.W[i] = i < c.nseg ? (const uint16_t*)c.W[i] : nullptr;
         if (i < c.nseg) N += c.seg_rows[i];
     }
-    PgPlan p = pg_plan(c.M, N, c.K);
-    if (p.part > ws.ws_part_n || p.cnt > ws.ws_cnt_n) p.S = 1;  // partials must fit the workspace
+    PgPlan p = pg_plan(c.M, N, c.K, c.m_live != nullptr);
+    a.m_live = c.m_live;
+    if (p.part > ws.ws_part_n || p.cnt > ws.ws_cnt_n) {
+        // partials must fit the workspace
+        p.S = 1;
+        p.grid = 8 * p.nblk_m * ((p.nblk_n + 7) / 8);
+    }
     a.S = p.S; a.nblk_m = p.nblk_m; a.nblk_n = p.nblk_n;
     a.nbs = 8 * p.nblk_m * ((p.nblk_n + 7) / 8);
     if (c.mode == kEpiSwiglu) {
@@ -512,11 +541,11 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
     a.rcos = c.rcos; a.rsin = c.rsin; a.qout = c.qout; a.kc = c.kc; a.vc = c.vc;
     a.cap = c.cap; a.max_batch = c.max_batch; a.layer = c.layer; a.ubias = c.ubias; a.ub_ld = c.ub_ld;
     ProfEntry* pe = prof_slot(e, kProfGemv, (double)N * c.K * 2.0 + (double)c.M * c.K * 4.0 + (double)c.M * N * 4.0);
-    if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, c.mode, a);
-    else if (p.MG == 2) pg_launch<2, 2, 4>(s, pe, c.mode, a);
-    else if (p.MG == 4) pg_launch<4, 2, 2>(s, pe, c.mode, a);
-    else if (p.NG == 2) pg_launch<8, 2, 1>(s, pe, c.mode, a);
-    else pg_launch<8, 4, 1>(s, pe, c.mode, a);
+    if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.MG == 2) pg_launch<2, 2, 4>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.MG == 4) pg_launch<4, 2, 2>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.NG == 2) pg_launch<8, 2, 1>(s, pe, c.mode, dim3(p.grid), a);
+    else pg_launch<8, 4, 1>(s, pe, c.mode, dim3(p.grid), a);
     if (pe) prof_commit(e);
     return true;
 }
