@@ -76,6 +76,7 @@ constexpr int kPaK = 16;                  // key positions per tile
 constexpr int kPaMaxSpans = 16;           // spans per group (one merge batch)
 typedef float pf4 __attribute__((ext_vector_type(4)));
 typedef float pf2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u4_t __attribute__((ext_vector_type(4)));
 
 // Max and sum over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48 hold one column).
 __device__ __forceinline__ float pa_colmax(float v) {
@@ -515,6 +516,9 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
     // spans: outputs [row][head][span][HD], then (max, sum) [row][head][span][2]
     const int rows = a.nseq * a.rps;
     float* const pml = a.part + (size_t)rows * a.H * nspan * HD;
+    const size_t ph0 = (size_t)rbase * a.H * nspan;  // the sequence's first
+    const __amdgpu_buffer_rsrc_t prs =
+        __builtin_amdgcn_make_buffer_rsrc(a.part + ph0 * HD, 0, nrows * a.H * nspan * HD * 4, 0x00027000);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         float w[4], M = -INFINITY, L = 0.f;
@@ -546,8 +550,14 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
                     for (int e = 0; e < VV; ++e) attn_put1(a, vrow[t], h * HD + d + e, x[e]);
                 }
             } else {
+                if constexpr (VV == 4) {
+                    // (one 16-byte write-through store)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, x), prs,
+                                                          (int)(((ph - ph0) * HD + d) * 4), 0, 16);
+                } else {
 #pragma unroll
-                for (int e = 0; e < VV; ++e) store_through(a.part + ph * HD + d + e, x[e]);
+                    for (int e = 0; e < VV; ++e) store_through(a.part + ph * HD + d + e, x[e]);
+                }
             }
         }
         if (nlive > 1 && vok[t] && grp == 0 && wave == 0) {

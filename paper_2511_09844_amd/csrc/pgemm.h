@@ -14,6 +14,7 @@ constexpr size_t kPgSlack = 128 * kPgBlkWords * 2;
 // Shape of a launch: 16 MG rows by 64 NG weight rows per workgroup, K in S ranges.
 struct PgPlan {
     int MG, NG, S, nblk_m, nblk_n, grid;
+    bool skinny;  // k_sgemm takes it (nothing else is set)
     size_t part;  // floats of split-K partials (0 without a split)
     size_t cnt;   // arrival counters
 };

@@ -435,6 +435,108 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     }
 }
 
+// The same projection for up to 16 rows onto few weight rows and short K: a workgroup owns one pair of
+// sub-tiles (32 weight rows) and its four waves take K ranges of it, each streaming weights and
+// planes straight into registers, D blocks of 64 columns ahead, with no LDS and no barrier until
+// the waves' sums meet in LDS.  Against k_pgemm, whose 128-row blocks need K split over workgroups to
+// fill the chip at these sizes, it saves the staging and the hand-off through memory, which are
+// most of a launch this short.
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void k_sgemm(PgArgs a) {
+    constexpr int D = 4, WK = 4;
+    __shared__ __attribute__((aligned(16))) pg_f4 red[WK][2][64];
+    __shared__ float inv_s[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, q = lane >> 4;
+    const int P = blockIdx.x;
+    const uint16_t* const w0 = pg_row<MODE>(a, P, 0, n) + 16 * q;
+    const uint16_t* const w1 = pg_row<MODE>(a, P, 1, n) + 16 * q;
+    const int nkb = a.K / kPgBlk, b0 = nkb * wave / WK, b1 = nkb * (wave + 1) / WK;
+    const uint16_t* const xp = a.planes + n * kPgBlkWords + 16 * q;
+    const size_t xstep = (size_t)a.Mp * kPgBlkWords;
+    // statistics first (see k_pgemm): wave w takes rows w, w + WK, ...
+    constexpr int RU = 16 / WK;
+    const bool stats = MODE != kEpiAdd && a.ss;
+    const int n4s = a.nss / 4;
+    pg_f4 sv[RU];
+    const int row = min(n, a.M - 1);
+    const int pos = MODE == kEpiQkv && wave == 0 ? a.row_pos[row] : 0;
+    auto load_ss = [&](int f0) {
+        const int f = 4 * min(f0 + lane, n4s - 1);
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const int r = min(wave + WK * u, a.M - 1);
+            const int src = a.in_map ? max(a.in_map[r], 0) : r;
+            sv[u] = *(const pg_f4*)(a.ss + (size_t)src * a.nss + f);
+        }
+    };
+    if (stats) load_ss(0);
+    pg_u4 w[D][2][2], x[D][2][2];
+    auto load = [&](int kb, int d) {
+        kb = max(min(kb, b1 - 1), 0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            w[d][h][0] = *(const pg_u4*)(w0 + (size_t)kb * kPgBlk + 8 * h);
+            w[d][h][1] = *(const pg_u4*)(w1 + (size_t)kb * kPgBlk + 8 * h);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) x[d][h][p] = *(const pg_u4*)(xp + kb * xstep + 8 * h + p * kPgBlk);
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(b0 + d, d);
+    PgPre pre = {};
+    if (wave == 0) pre = pg_pre<MODE>(a, P, row, pos, q);
+    if (stats) {
+        float sm[RU], mine = 0.f;
+#pragma unroll
+        for (int u = 0; u < RU; ++u) sm[u] = lane < n4s ? (sv[u].x + sv[u].y) + (sv[u].z + sv[u].w) : 0.f;
+        for (int f0 = 64; f0 < n4s; f0 += 64) {
+            load_ss(f0);
+#pragma unroll
+            for (int u = 0; u < RU; ++u)
+                sm[u] += f0 + lane < n4s ? (sv[u].x + sv[u].y) + (sv[u].z + sv[u].w) : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const float v = wave_sum_dpp(sm[u]);
+            mine = lane == u ? v : mine;
+        }
+        if (lane < RU) inv_s[wave + WK * lane] = rsqrtf(mine / (float)a.K + a.eps);
+    } else if (tid < 16) {
+        inv_s[tid] = 1.0f;
+    }
+    pg_f4 acc[2];
+    acc[0] = acc[1] = pg_f4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = b0; kb < b1; kb += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (kb + d < b1) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf8, w[d][h][j]),
+                                                                            __builtin_bit_cast(pg_bf8, x[d][h][p]),
+                                                                            acc[j], 0, 0, 0);
+            }
+            if (kb + D < b1) load(kb + D + d, d);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) red[wave][j][lane] = acc[j];
+    __syncthreads();
+    if (wave != 0) return;
+    pg_f4 v[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) v[j] = (red[0][j][lane] + red[1][j][lane]) + (red[2][j][lane] + red[3][j][lane]);
+    const float sc = inv_s[n];
+    pg_epilogue<MODE>(a, P, row, n < a.M, pos, q, v[0] * sc, v[1] * sc, pre);
+}
+
 // Shapes from a sweep of tiles and splits over 8 to 2048 rows at the 8B, 70B and drafter widths
 // (weights cycled through more than the last-level cache).  MG: the fewest row groups that hold
 // the rows, up to 128 rows, so that the weights are read once.  NG 4 (128 x 256) halves the LDS
@@ -451,6 +553,11 @@ PgPlan pg_plan(int M, int N, int K, bool packed) {
     p.NG = 2;
     if (rows <= 32 && K % 256 == 0) {
         p.MG = rows <= 16 ? 1 : 2;
+        // k_sgemm where K is short and the pairs do not outnumber the two workgroups per CU: 16 rows
+        // onto 3072 x 2048 in 9.8 us against 11.2, 16384 x 2048 in 18.0 against 19.3, 768 x 768 in
+        // 6.0; longer K streams from too few workgroups (2048 x 8192: 31 us against 15.6)
+        p.skinny = !packed && rows <= 16 && K <= 2048 && N <= 16384;
+        if (p.skinny) return p;
     } else if (rows <= 64 || blocks(8, 2) * (K / 512) < 512) {
         p.MG = 4;
     } else {
@@ -479,6 +586,15 @@ PgPlan pg_plan(int M, int N, int K, bool packed) {
     p.part = p.S > 1 ? (size_t)nb * p.S * tile : 0;
     p.cnt = p.S > 1 ? nb : 0;
     return p;
+}
+
+static void sg_launch(hipStream_t s, ProfEntry* pe, int mode, const PgArgs& a) {
+    const dim3 grid(a.pairs), blk(256);
+    hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
+    if (mode == kEpiStore) hipExtLaunchKernelGGL((k_sgemm<kEpiStore>), grid, blk, 0, s, ea, eb, 0, a);
+    else if (mode == kEpiAdd) hipExtLaunchKernelGGL((k_sgemm<kEpiAdd>), grid, blk, 0, s, ea, eb, 0, a);
+    else if (mode == kEpiSwiglu) hipExtLaunchKernelGGL((k_sgemm<kEpiSwiglu>), grid, blk, 0, s, ea, eb, 0, a);
+    else hipExtLaunchKernelGGL((k_sgemm<kEpiQkv>), grid, blk, 0, s, ea, eb, 0, a);
 }
 
 template <int MG, int NG, int KB>
@@ -541,7 +657,8 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
     a.rcos = c.rcos; a.rsin = c.rsin; a.qout = c.qout; a.kc = c.kc; a.vc = c.vc;
     a.cap = c.cap; a.max_batch = c.max_batch; a.layer = c.layer; a.ubias = c.ubias; a.ub_ld = c.ub_ld;
     ProfEntry* pe = prof_slot(e, kProfGemv, (double)N * c.K * 2.0 + (double)c.M * c.K * 4.0 + (double)c.M * N * 4.0);
-    if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, c.mode, dim3(p.grid), a);
+    if (p.skinny) sg_launch(s, pe, c.mode, a);
+    else if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, c.mode, dim3(p.grid), a);
     else if (p.MG == 2) pg_launch<2, 2, 4>(s, pe, c.mode, dim3(p.grid), a);
     else if (p.MG == 4) pg_launch<4, 2, 2>(s, pe, c.mode, dim3(p.grid), a);
     else if (p.NG == 2) pg_launch<8, 2, 1>(s, pe, c.mode, dim3(p.grid), a);
