@@ -349,31 +349,32 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
 // Blocks of fewer than 16 rows per sequence (decode steps, verify passes): flash attention on fp32
 // matrix cores over packed query vectors.  The rps x G vectors (row, query head) of a sequence
 // and KV head fill the 16 query columns of the products without gaps (rows alone would leave
-// 16 - rps of them empty for every head); a workgroup owns up to 16 NT of them and one span of
-// key tiles, and its 4 waves take the span's 16-key tiles in turn.
+// 16 - rps of them empty for every head); a workgroup owns up to 16 of them and one span of key
+// tiles, and its 4 waves take the span's 16-key tiles in turn.  (Two column tiles per wave read K and V
+// once for 32 vectors but measured slower at every shape: 77 against 72 us for 16 sequences of 8
+// rows, 48 against 43 at the 70B shape; the second workgroup finds them in its XCD's L2.)
 //
 // A wave reads K and V from memory straight in the operand layout, with no LDS and no barrier in
 // the key loop: S^T = K Q^T walks the head dimension as dim = 16 s4 + 4 g + e (lane group g, step
 // 4 s4 + e), so that the four lanes of a key read 64 adjacent bytes per load, and O^T += V^T P^T
 // numbers the output dims as 64 t4 + 4 i + e (tile row i, tile 4 t4 + e), so that the 16 lanes of
-// a key read 256.  An operand register is refilled for the wave's next tile as soon as its products
-// are issued.  The online softmax stays in registers (see k_pattn); the waves' sums are merged
+// a key read 256.  A wave's next tile is requested before the current one is used.  The online softmax stays in registers (see k_pattn); the waves' sums are merged
 // through LDS, and the last live span of a group to arrive merges the spans.
 //
 // Bound: K/V bytes at long contexts, one tile's chain of load, products and softmax at short ones.
 // ---------------------------------------------------------------------------------------------
 constexpr int kVaMaxRows = 15;  // rows per sequence up to which blocks run here
-constexpr int kVaMinTiles = 8;  // key tiles per span at least (two per wave)
+constexpr int kVaMinTiles = 8;  // key tiles per span: two per wave
 
-template <int HD, int NT>
+template <int HD>
 __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan, int span_t) {
     constexpr int QD = HD / 4;                  // S^T steps: head dims per lane group
     constexpr int VD = HD / 16;                 // O^T tiles
     constexpr int VV = VD < 4 ? VD : 4;         // V values per load
-    constexpr int NO = NT * VD * 4 / VV;        // groups of VV adjacent output dims per lane
+    constexpr int NO = VD * 4 / VV;             // groups of VV adjacent output dims per lane
     typedef float vv_t __attribute__((ext_vector_type(VV)));
     __shared__ __attribute__((aligned(16))) float os[4][NO][64 * VV];
-    __shared__ float ms[4][16 * NT], ls[4][16 * NT];
+    __shared__ float ms[4][16], ls[4][16];
     __shared__ int last_flag;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
@@ -381,25 +382,19 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
     // the column groups of one span, which read the same K/V, are 8 workgroups apart: on one XCD
     const int c8 = blockIdx.x / 8, cg = c8 % ncg;
     const int u = (c8 / ncg) * 8 + blockIdx.x % 8;
-    const int sp = u % nspan, kvh = (u / nspan) % a.Hkv, b = u / (nspan * a.Hkv);
-    if (b >= a.nseq) return;  // grid padding
+    // spans in the outer order: in the inner one a span count that is a multiple of 8 put the live
+    // (first) spans of every group on the same few XCDs (4 sequences of 6 rows: 34 against 22 us)
+    const int groups = a.nseq * a.Hkv, sp = u / groups, kvh = u % a.Hkv, b = (u % groups) / a.Hkv;
+    if (sp >= nspan) return;  // grid padding
     int nrows;
     const int rbase = attn_rows(a, b, nrows), nv = nrows * G;
-    // this lane's query vectors (one per column tile) and their positions
-    int vrow[NT], vpos[NT], maxpos = -1;
-    const float* qp[NT];
-    bool vok[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int v = (cg * NT + t) * 16 + col;
-        vok[t] = v < nv;
-        const int vc = vok[t] ? v : 0;
-        vrow[t] = rbase + vc / G;
-        const int p = a.row_pos[vrow[t]];
-        vpos[t] = vok[t] ? p : -1;
-        maxpos = max(maxpos, vpos[t]);
-        qp[t] = a.q + (size_t)vrow[t] * a.q_stride + (size_t)(kvh * G + vc % G) * HD + 4 * grp;
-    }
+    // this lane's query vector and its position
+    const int v = cg * 16 + col;
+    const bool vok = v < nv;
+    const int vrow = rbase + (vok ? v / G : 0), h = kvh * G + (vok ? v % G : 0);
+    const int vpos = vok ? a.row_pos[vrow] : -1;
+    int maxpos = vpos;
+    const float* const qp = a.q + (size_t)vrow * a.q_stride + (size_t)h * HD + 4 * grp;
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) maxpos = max(maxpos, __shfl_xor(maxpos, o, 16));
     maxpos = __builtin_amdgcn_readfirstlane(maxpos);
@@ -410,107 +405,87 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
     const size_t kvoff = (((size_t)a.layer * a.max_batch + b) * a.Hkv + kvh) * (size_t)a.cap * HD;
     const float* kg = a.kc + kvoff + 4 * grp;
     const float* vg = a.vc + kvoff + VV * col;
-    pf4 kf[QD / 4];
-    vv_t vf[4][VD / VV];
+    struct Tile {
+        pf4 k[QD / 4];
+        vv_t v[4][VD / VV];
+    };
     // positions past the last one re-read it (masked in the scores)
-    auto load_k = [&](int kt) {
+    auto load = [&](int kt, Tile& x) {
         const float* p = kg + (size_t)min(kt * 16 + col, maxpos) * HD;
 #pragma unroll
-        for (int s = 0; s < QD / 4; ++s) kf[s] = *(const pf4*)(p + 16 * s);
-    };
-    auto load_v = [&](int kt) {
+        for (int s = 0; s < QD / 4; ++s) x.k[s] = *(const pf4*)(p + 16 * s);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float* p = vg + (size_t)min(kt * 16 + 4 * grp + r, maxpos) * HD;
+            const float* pv = vg + (size_t)min(kt * 16 + 4 * grp + r, maxpos) * HD;
 #pragma unroll
-            for (int t = 0; t < VD / VV; ++t) vf[r][t] = *(const vv_t*)(p + 16 * VV * t);
+            for (int t = 0; t < VD / VV; ++t) x.v[r][t] = *(const vv_t*)(pv + 16 * VV * t);
         }
     };
-    pf4 qf[NT][QD / 4];
+    pf4 qf[QD / 4];
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int s = 0; s < QD / 4; ++s) qf[s] = *(const pf4*)(qp + 16 * s);
+    Tile ta, tb;
+    if (t0 < t1) load(t0, ta);
+    const float qs = vok ? a.scale : 0.f;
 #pragma unroll
-        for (int s = 0; s < QD / 4; ++s) qf[t][s] = *(const pf4*)(qp[t] + 16 * s);
-    if (t0 < t1) {
-        load_k(t0);
-        load_v(t0);
-    }
+    for (int s = 0; s < QD / 4; ++s) qf[s] *= qs;
+    pf4 o[VD];
+    float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const float sc = vok[t] ? a.scale : 0.f;
-#pragma unroll
-        for (int s = 0; s < QD / 4; ++s) qf[t][s] *= sc;
-    }
-    pf4 o[NT][VD];
-    float m_run[NT], l_run[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        m_run[t] = -INFINITY;
-        l_run[t] = 0.f;
-#pragma unroll
-        for (int d = 0; d < VD; ++d) o[t][d] = pf4{0.f, 0.f, 0.f, 0.f};
-    }
-    for (int kt = t0; kt < t1; kt += 4) {
-        pf4 sc[NT][2];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) sc[t][0] = sc[t][1] = pf4{0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < VD; ++d) o[d] = pf4{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](int kt, const Tile& x) {
+        pf4 sc[2] = {pf4{0.f, 0.f, 0.f, 0.f}, pf4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int s = 0; s < QD; ++s)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                sc[t][s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s / 4][s % 4], qf[t][s / 4][s % 4], sc[t][s & 1], 0, 0, 0);
-        const int nx = kt + 4 < t1 ? kt + 4 : kt;
-        load_k(nx);
+            sc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[s / 4][s % 4], qf[s / 4][s % 4], sc[s & 1], 0, 0, 0);
         // online softmax: this lane holds S[its query][key 4 grp + r]
-        float pr[NT][4];
         const int kb = kt * 16 + 4 * grp;
+        float sv[4], pr[4], mx = -INFINITY, sum = 0.f;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            float sv[4], mx = -INFINITY, sum = 0.f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                sv[r] = kb + r <= vpos[t] ? sc[t][0][r] + sc[t][1][r] : -INFINITY;
-                mx = fmaxf(mx, sv[r]);
-            }
-            mx = pa_colmax(mx);
-            const float mnew = fmaxf(m_run[t], mx);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                pr[t][r] = sv[r] == -INFINITY ? 0.f : expf(sv[r] - mnew);
-                sum += pr[t][r];
-            }
-            const float scl = m_run[t] == -INFINITY ? 0.f : expf(m_run[t] - mnew);
-            l_run[t] = l_run[t] * scl + pa_colsum(sum);
-            m_run[t] = mnew;
-#pragma unroll
-            for (int d = 0; d < VD; ++d) o[t][d] *= scl;
+        for (int r = 0; r < 4; ++r) {
+            sv[r] = kb + r <= vpos ? sc[0][r] + sc[1][r] : -INFINITY;
+            mx = fmaxf(mx, sv[r]);
         }
+        mx = pa_colmax(mx);
+        const float mnew = fmaxf(m_run, mx);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            pr[r] = sv[r] == -INFINITY ? 0.f : expf(sv[r] - mnew);
+            sum += pr[r];
+        }
+        const float scl = m_run == -INFINITY ? 0.f : expf(m_run - mnew);
+        l_run = l_run * scl + pa_colsum(sum);
+        m_run = mnew;
+#pragma unroll
+        for (int d = 0; d < VD; ++d) o[d] *= scl;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int d = 0; d < VD; ++d)
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    o[t][d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][d / VV][d % VV], pr[t][r], o[t][d], 0, 0, 0);
-        load_v(nx);
+                o[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[r][d / VV][d % VV], pr[r], o[d], 0, 0, 0);
+    };
+    // (past the last tile the current one is requested again: no branch around the loads)
+    for (int kt = t0; kt < t1; kt += 8) {
+        load(kt + 4 < t1 ? kt + 4 : kt, tb);
+        step(kt, ta);
+        if (kt + 4 >= t1) break;
+        load(kt + 8 < t1 ? kt + 8 : kt, ta);
+        step(kt + 4, tb);
     }
-    // merge the waves: group i = (t, t4, r) of a lane is VV adjacent dims, 16 VV t4 + VV (4 grp + r),
-    // of its query vector t
+    // merge the waves: group i = (t4, r) of a lane is VV adjacent dims, 16 VV t4 + VV (4 grp + r), of
+    // its query vector
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+    for (int t4 = 0; t4 < VD / VV; ++t4)
 #pragma unroll
-        for (int t4 = 0; t4 < VD / VV; ++t4)
+        for (int r = 0; r < 4; ++r) {
+            vv_t x;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                vv_t x;
-#pragma unroll
-                for (int e = 0; e < VV; ++e) x[e] = o[t][VV * t4 + e][r];
-                *(vv_t*)&os[wave][(t * (VD / VV) + t4) * 4 + r][lane * VV] = x;
-            }
-        if (grp == 0) {
-            ms[wave][16 * t + col] = m_run[t];
-            ls[wave][16 * t + col] = l_run[t];
+            for (int e = 0; e < VV; ++e) x[e] = o[VV * t4 + e][r];
+            *(vv_t*)&os[wave][t4 * 4 + r][lane * VV] = x;
         }
+    if (grp == 0) {
+        ms[wave][col] = m_run;
+        ls[wave][col] = l_run;
     }
     __syncthreads();
     // spans: outputs [row][head][span][HD], then (max, sum) [row][head][span][2]
@@ -519,59 +494,52 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
     const size_t ph0 = (size_t)rbase * a.H * nspan;  // the sequence's first
     const __amdgpu_buffer_rsrc_t prs =
         __builtin_amdgcn_make_buffer_rsrc(a.part + ph0 * HD, 0, nrows * a.H * nspan * HD * 4, 0x00027000);
+    float w[4], M = -INFINITY, L = 0.f;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        float w[4], M = -INFINITY, L = 0.f;
+    for (int k = 0; k < 4; ++k) M = fmaxf(M, ms[k][col]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) M = fmaxf(M, ms[k][16 * t + col]);
+    for (int k = 0; k < 4; ++k) {
+        const float m = ms[k][col];
+        w[k] = m == -INFINITY ? 0.f : expf(m - M);
+        L += w[k] * ls[k][col];
+    }
+    const float inv = nlive == 1 ? (L > 0.f ? 1.f / L : 0.f) : 1.f;
+    const size_t ph = ((size_t)vrow * a.H + h) * nspan + sp;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float m = ms[k][16 * t + col];
-            w[k] = m == -INFINITY ? 0.f : expf(m - M);
-            L += w[k] * ls[k][16 * t + col];
-        }
-        const float inv = nlive == 1 ? (L > 0.f ? 1.f / L : 0.f) : 1.f;
-        const int v = (cg * NT + t) * 16 + col, h = kvh * G + (vok[t] ? v % G : 0);
-        const size_t ph = ((size_t)vrow[t] * a.H + h) * nspan + sp;
+    for (int i0 = 0; i0 < NO; i0 += 4) {
+        const int i = i0 + wave;
+        vv_t x = {};
 #pragma unroll
-        for (int i0 = 0; i0 < NO / NT; i0 += 4) {
-            const int i = i0 + wave;
-            vv_t x = {};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) x += *(const vv_t*)&os[k][t * (NO / NT) + i][lane * VV] * w[k];
-            x *= inv;
-            if (!vok[t]) continue;
-            const int d = 16 * VV * (i / 4) + VV * (4 * grp + i % 4);
-            if (nlive == 1) {
-                if constexpr (VV == 4) {
-                    attn_put4(a, vrow[t], h * HD + d, make_float4(x[0], x[1], x[2], x[3]));
-                } else {
-#pragma unroll
-                    for (int e = 0; e < VV; ++e) attn_put1(a, vrow[t], h * HD + d + e, x[e]);
-                }
+        for (int k = 0; k < 4; ++k) x += *(const vv_t*)&os[k][i][lane * VV] * w[k];
+        x *= inv;
+        if (!vok) continue;
+        const int d = 16 * VV * (i / 4) + VV * (4 * grp + i % 4);
+        if (nlive == 1) {
+            if constexpr (VV == 4) {
+                attn_put4(a, vrow, h * HD + d, make_float4(x[0], x[1], x[2], x[3]));
             } else {
-                if constexpr (VV == 4) {
-                    // (one 16-byte write-through store)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, x), prs,
-                                                          (int)(((ph - ph0) * HD + d) * 4), 0, 16);
-                } else {
 #pragma unroll
-                    for (int e = 0; e < VV; ++e) store_through(a.part + ph * HD + d + e, x[e]);
-                }
+                for (int e = 0; e < VV; ++e) attn_put1(a, vrow, h * HD + d + e, x[e]);
             }
+        } else if constexpr (VV == 4) {
+            // (one 16-byte write-through store)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, x), prs, (int)(((ph - ph0) * HD + d) * 4), 0, 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < VV; ++e) store_through(a.part + ph * HD + d + e, x[e]);
         }
-        if (nlive > 1 && vok[t] && grp == 0 && wave == 0) {
-            store_through(pml + ph * 2, M);
-            store_through(pml + ph * 2 + 1, L);
-        }
+    }
+    if (nlive > 1 && vok && grp == 0 && wave == 0) {
+        store_through(pml + ph * 2, M);
+        store_through(pml + ph * 2 + 1, L);
     }
     if (nlive == 1) return;
     if (!arrive_last(a.cnt + (b * a.Hkv + kvh) * ncg + cg, nlive, &last_flag)) return;
     // the last live span merges: a thread per (vector, 4 dims), spans eight per round trip (loads
     // past the last live span re-read it and are not added)
     constexpr int D4 = HD / 4;
-    for (int idx = tid; idx < 16 * NT * D4; idx += 256) {
-        const int v = cg * NT * 16 + idx / D4, d = (idx % D4) * 4;
+    for (int idx = tid; idx < 16 * D4; idx += 256) {
+        const int v = cg * 16 + idx / D4, d = (idx % D4) * 4;
         if (v >= nv) break;
         const int h = kvh * G + v % G;
         const size_t row = (size_t)rbase + v / G, ph = (row * a.H + h) * nspan;
@@ -608,23 +576,27 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
 
 template <int HD>
 static void launch_vattn(Engine& e, hipStream_t s, const AttnArgs& a) {
-    const int nv = a.rps * (a.H / a.Hkv), NT = nv <= 16 ? 1 : 2;
-    const int ncg = (nv + 16 * NT - 1) / (16 * NT), groups = a.nseq * a.Hkv;
-    // Spans for about 2048 workgroups over the whole capacity (those past a sequence's length exit
-    // at once), of at least two key tiles per wave.
-    const int tiles = (a.cap + 15) / 16;
-    int nspan = std::min((tiles + kVaMinTiles - 1) / kVaMinTiles, std::max(1, 2048 / (groups * ncg)));
-    if ((size_t)groups * ncg > e.ws.attn_cnt_n) nspan = 1;
-    const size_t per = (size_t)a.nseq * a.rps * a.H * (HD + 2);  // the partials' room
-    nspan = std::max<int>(1, std::min<size_t>(nspan, e.ws.attn_part_n / per));
-    int span_t = (tiles + nspan - 1) / nspan;
-    span_t = (span_t + 3) / 4 * 4;
-    nspan = (tiles + span_t - 1) / span_t;
+    const int ncg = (a.rps * (a.H / a.Hkv) + 15) / 16, groups = a.nseq * a.Hkv;
+    // Key tiles per span: an eighth of the workgroups that share them, so that capacity-long
+    // sequences come to about 8 x 193 workgroups at the 3081 positions swept; at least two per wave, one
+    // with very few groups, and at most 48 spans to merge.  Measured best or within 5 % of it from 16
+    // groups (2 sequences of 4 rows: 11.1 us with 4 tiles, 13.6 with 8) over 64 (4 of 6: 18.2 with 8,
+    // 20.5 with 4, 22.8 with 16) to 256 (16 of 8: 60.7 with 32, 70.1 with 16, 88.6 with 64).
+    const int tiles = (a.cap + 15) / 16, ng = groups * ncg;
+    int span_t = std::max(ng < 24 ? 4 : kVaMinTiles, ng / 8);
+    span_t = (std::max(span_t, (tiles + 47) / 48) + 3) / 4 * 4;
+    int nspan = (tiles + span_t - 1) / span_t;
+    // the partials' and counters' room
+    const size_t per = (size_t)a.nseq * a.rps * a.H * (HD + 2);
+    if ((size_t)ng > e.ws.attn_cnt_n || per * nspan > e.ws.attn_part_n) {
+        nspan = (size_t)ng > e.ws.attn_cnt_n ? 1 : std::max<int>(1, e.ws.attn_part_n / per);
+        span_t = ((tiles + nspan - 1) / nspan + 3) / 4 * 4;
+        nspan = (tiles + span_t - 1) / span_t;
+    }
     const dim3 grid((groups * nspan + 7) / 8 * 8 * ncg);
     ProfEntry* pe = prof_slot(&e, kProfAttn, 0.0);
     hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
-    if (NT == 1) hipExtLaunchKernelGGL((k_vattn<HD, 1>), grid, dim3(256), 0, s, ea, eb, 0, a, ncg, nspan, span_t);
-    else hipExtLaunchKernelGGL((k_vattn<HD, 2>), grid, dim3(256), 0, s, ea, eb, 0, a, ncg, nspan, span_t);
+    hipExtLaunchKernelGGL((k_vattn<HD>), grid, dim3(256), 0, s, ea, eb, 0, a, ncg, nspan, span_t);
     if (pe) prof_commit(&e);
 }
 
@@ -690,9 +662,10 @@ void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int
     }
 }
 
-// Arrival counters of an attention launch: one per sequence, KV head and 32 query vectors.
+// Arrival counters of an attention launch: one per sequence, KV head and 16 query vectors (more
+// than the blocks of 16 rows that k_pattn counts).
 size_t attn_groups(int rows, int rps, int H, int Hkv) {
-    return (size_t)(rows / rps) * Hkv * ((rps * (H / Hkv) + 31) / 32);
+    return (size_t)(rows / rps) * Hkv * ((rps * (H / Hkv) + 15) / 16);
 }
 
 int attn_nsplit(int cap) { return (cap + kSplit - 1) / kSplit; }
