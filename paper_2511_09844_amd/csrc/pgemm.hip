@@ -13,7 +13,7 @@
 // only, so LDS would add traffic), against all the rows, whose planes all four waves read from
 // LDS.  K goes in steps of KB blocks of 64 columns with two LDS buffers: while step i multiplies,
 // the planes of step i + 1 are on their way into registers, and each weight fragment is
-// requested again for a later step as soon as it has been used.  A row of a block is 256 bytes
+// requested again for a later step (WD steps on) as soon as it has been used.  A row of a block is 256 bytes
 // in LDS, its sixteen 16-byte chunks permuted by chunk ^ (row & 15), so that the sixteen rows of
 // an operand read fall into different banks.
 //
@@ -212,7 +212,7 @@ __device__ __forceinline__ void pg_epilogue(const PgArgs& a, int P, int row, boo
     }
 }
 
-template <int MG, int NG, int KB, int MODE>
+template <int MG, int NG, int KB, int WD, int MODE>
 __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     static_assert(NG % 2 == 0, "sub-tiles come in pairs");
     constexpr int kBlkB = 16 * MG * kPgBlkWords * 2;    // bytes of one 64-column block in LDS
@@ -248,11 +248,11 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     const int nst = a.K / (kPgBlk * KB);
     const int b0 = nst * s / S, b1 = nst * (s + 1) / S;
 
-    pg_u4 w[KB][2][NG];
+    pg_u4 w[WD][KB][2][NG];
     pg_u4 xa[NA];
-    auto load_w = [&](int step, int kb, int h) {
+    auto load_w = [&](int step, int d, int kb, int h) {
 #pragma unroll
-        for (int j = 0; j < NG; ++j) w[kb][h][j] = *(const pg_u4*)(wp[j] + (size_t)(step * KB + kb) * kPgBlk + 8 * h);
+        for (int j = 0; j < NG; ++j) w[d][kb][h][j] = *(const pg_u4*)(wp[j] + (size_t)(step * KB + kb) * kPgBlk + 8 * h);
     };
     // planes: block kb of a step is one run of 16 MG rows of 256 bytes
     const char* const xbase = (const char*)a.planes + (size_t)m0 * kPgBlkWords * 2 + tid * 16;
@@ -317,7 +317,12 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     if (kFew && stats) load_ss(0, 0);
     load_x(b0);
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) { load_w(b0, kb, 0); load_w(b0, kb, 1); }
+    for (int d = 0; d < WD; ++d)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            load_w(min(b0 + d, b1 - 1), d, kb, 0);
+            load_w(min(b0 + d, b1 - 1), d, kb, 1);
+        }
     PgPre pre[kFew ? MG : 1][NG / 2];
     if constexpr (kFew)
 #pragma unroll
@@ -345,10 +350,9 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
         for (int j = 0; j < NG; ++j) acc[g][j] = pg_f4{0.f, 0.f, 0.f, 0.f};
     stage(0);
     __syncthreads();
-    for (int step = b0; step < b1; ++step) {
+    auto run = [&](int step, int d) {
         const int buf = (step - b0) & 1;
-        const int nx = min(step + 1, b1 - 1);
-        load_x(nx);
+        load_x(min(step + 1, b1 - 1));
         const char* const lb = sm + buf * kStageB + n * 256;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
@@ -363,17 +367,26 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
                     const pg_bf8 xl = __builtin_bit_cast(pg_bf8, *(const pg_u4*)(pl + g * 4096));
 #pragma unroll
                     for (int j = 0; j < NG; ++j)
-                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf8, w[kb][h][j]), xh,
+                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf8, w[d][kb][h][j]), xh,
                                                                            acc[g][j], 0, 0, 0);
 #pragma unroll
                     for (int j = 0; j < NG; ++j)
-                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf8, w[kb][h][j]), xl,
+                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pg_bf8, w[d][kb][h][j]), xl,
                                                                            acc[g][j], 0, 0, 0);
                 }
-                load_w(nx, kb, h);
+                load_w(min(step + WD, b1 - 1), d, kb, h);
             }
         stage(buf ^ 1);
         __syncthreads();
+    };
+    if constexpr (WD == 1) {
+        for (int step = b0; step < b1; ++step) run(step, 0);
+    } else {
+        for (int step = b0; step < b1; step += WD) {
+#pragma unroll
+            for (int d = 0; d < WD; ++d)
+                if (step + d < b1) run(step + d, d);
+        }
     }
 
     if (S > 1) {
@@ -544,7 +557,9 @@ __global__ __launch_bounds__(256, 2) void k_sgemm(PgArgs a) {
 // against 269 with NG 2), or K is long enough to split (1024 rows of down: 225 against 252);
 // below that its few blocks and their large partials lose (512 rows of down: 176 against 135).
 // 64-row blocks take short K with few columns, where even split 128-row blocks leave workgroups
-// idle (128 rows of O 8B: 28 against 34 us).  S: up to two workgroups per CU, one with up to 32
+// idle (128 rows of O 8B: 28 against 34 us); with up to 64 rows they take NG 4 where that leaves
+// enough blocks (36 rows of gate|up 8B: 63 against 70 us, 70B 208 against 226, of a vocabulary 392
+// against 478).  S: up to two workgroups per CU, one with up to 32
 // rows (24 rows of gate|up: 55 us unsplit, 60 with S 2; of Q|K|V: 19 with S 4, 23 with S 8).
 PgPlan pg_plan(int M, int N, int K, bool packed) {
     PgPlan p{};
@@ -560,6 +575,7 @@ PgPlan pg_plan(int M, int N, int K, bool packed) {
         if (p.skinny) return p;
     } else if (rows <= 64 || blocks(8, 2) * (K / 512) < 512) {
         p.MG = 4;
+        if (rows <= 64 && blocks(4, 4) >= 96) p.NG = 4;
     } else {
         p.MG = 8;
         if (blocks(8, 4) >= 384 || (K >= 8192 && blocks(8, 4) >= 128)) p.NG = 4;
@@ -597,14 +613,14 @@ static void sg_launch(hipStream_t s, ProfEntry* pe, int mode, const PgArgs& a) {
     else hipExtLaunchKernelGGL((k_sgemm<kEpiQkv>), grid, blk, 0, s, ea, eb, 0, a);
 }
 
-template <int MG, int NG, int KB>
+template <int MG, int NG, int KB, int WD>
 static void pg_launch(hipStream_t s, ProfEntry* pe, int mode, dim3 grid, const PgArgs& a) {
     const dim3 blk(256);
     hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
-    if (mode == kEpiStore) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiStore>), grid, blk, 0, s, ea, eb, 0, a);
-    else if (mode == kEpiAdd) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiAdd>), grid, blk, 0, s, ea, eb, 0, a);
-    else if (mode == kEpiSwiglu) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiSwiglu>), grid, blk, 0, s, ea, eb, 0, a);
-    else hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, kEpiQkv>), grid, blk, 0, s, ea, eb, 0, a);
+    if (mode == kEpiStore) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, WD, kEpiStore>), grid, blk, 0, s, ea, eb, 0, a);
+    else if (mode == kEpiAdd) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, WD, kEpiAdd>), grid, blk, 0, s, ea, eb, 0, a);
+    else if (mode == kEpiSwiglu) hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, WD, kEpiSwiglu>), grid, blk, 0, s, ea, eb, 0, a);
+    else hipExtLaunchKernelGGL((k_pgemm<MG, NG, KB, WD, kEpiQkv>), grid, blk, 0, s, ea, eb, 0, a);
 }
 
 bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
@@ -658,11 +674,12 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
     a.cap = c.cap; a.max_batch = c.max_batch; a.layer = c.layer; a.ubias = c.ubias; a.ub_ld = c.ub_ld;
     ProfEntry* pe = prof_slot(e, kProfGemv, (double)N * c.K * 2.0 + (double)c.M * c.K * 4.0 + (double)c.M * N * 4.0);
     if (p.skinny) sg_launch(s, pe, c.mode, a);
-    else if (p.MG == 1) pg_launch<1, 2, 4>(s, pe, c.mode, dim3(p.grid), a);
-    else if (p.MG == 2) pg_launch<2, 2, 4>(s, pe, c.mode, dim3(p.grid), a);
-    else if (p.MG == 4) pg_launch<4, 2, 2>(s, pe, c.mode, dim3(p.grid), a);
-    else if (p.NG == 2) pg_launch<8, 2, 1>(s, pe, c.mode, dim3(p.grid), a);
-    else pg_launch<8, 4, 1>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.MG == 1) pg_launch<1, 2, 4, 1>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.MG == 2) pg_launch<2, 2, 4, 1>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.MG == 4 && p.NG == 4) pg_launch<4, 4, 1, 2>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.MG == 4) pg_launch<4, 2, 2, 2>(s, pe, c.mode, dim3(p.grid), a);
+    else if (p.NG == 2) pg_launch<8, 2, 1, 2>(s, pe, c.mode, dim3(p.grid), a);
+    else pg_launch<8, 4, 1, 1>(s, pe, c.mode, dim3(p.grid), a);
     if (pe) prof_commit(e);
     return true;
 }
