@@ -131,6 +131,8 @@ __device__ __forceinline__ float mk_wsum(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+constexpr int kMkQG = kMkWaves;  // query vectors per attention unit
+
 // Row plan of the launch, one entry per activation row (position -1: inactive row).
 struct MkRows {
     int pos[kMkMaxRows], seq[kMkMaxRows], tok[kMkMaxRows];
@@ -171,6 +173,20 @@ __device__ __forceinline__ void mk_plan(const MkArgs& a, MkRows& rp) {
     rp.pos[r] = pos;
     rp.seq[r] = b < a.max_batch ? b : 0;
     rp.tok[r] = tok < 0 ? 0 : (tok >= a.vocab ? a.vocab - 1 : tok);
+    // attention: spans per unit and runs per group, from the spans some row of the launch sees
+    static_assert(kMkMaxRows == 16, "the maximum is taken over 16 lanes");
+    int mx = pos;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 16));
+    const int nspan = mx >= 0 ? min(mx, a.cap - 1) / kMkSpan + 1 : 1;
+    const int nq = a.rps * (a.H / a.Hkv), groups = (a.M / a.rps) * a.Hkv * ((nq + kMkQG - 1) / kMkQG);
+    const int runs = max(1, a.G / groups);
+    const int spu = (nspan + runs - 1) / runs, nrun = (nspan + spu - 1) / spu;
+    rp.nl[r] = pos >= 0 ? min(nrun, pos / (kMkSpan * spu) + 1) : 0;
+    if (r == 0) {
+        rp.spu = spu;
+        rp.nrun = nrun;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -741,8 +757,6 @@ __device__ __forceinline__ void mk_gemv(const MkArgs& a, const MkPhase& od, cons
 // read after it.  A cache line holds one row (hd >= 32 floats), so the early reads never bring a
 // line that this launch writes into a cache.
 // ---------------------------------------------------------------------------------------------
-constexpr int kMkQG = kMkWaves;  // query vectors per attention unit
-
 template <int HD>
 struct MkKv {
     static constexpr int F4 = kMkSpan * HD / 4 / kMkThreads;  // float4 of K (and of V) per thread
@@ -756,19 +770,6 @@ struct MkKv {
 struct MkAttnUnit {
     int sp, kvh, sq, qg, q0, nqu, p0, nvalid, nl, newpos;  // sp: run; nvalid: its valid positions
 };
-
-// Spans per unit and runs per group, from the spans some row of the launch sees (one thread, once
-// per launch, after mk_plan).
-__device__ __forceinline__ void mk_attn_plan(const MkArgs& a, MkRows& rp) {
-    int mx = -1;
-    for (int r = 0; r < a.M; ++r) mx = max(mx, rp.pos[r]);
-    const int nspan = mx >= 0 ? min(mx, a.cap - 1) / kMkSpan + 1 : 1;
-    const int nq = a.rps * (a.H / a.Hkv), groups = (a.M / a.rps) * a.Hkv * ((nq + kMkQG - 1) / kMkQG);
-    const int runs = max(1, a.G / groups);
-    rp.spu = (nspan + runs - 1) / runs;
-    rp.nrun = (nspan + rp.spu - 1) / rp.spu;
-    for (int r = 0; r < a.M; ++r) rp.nl[r] = rp.pos[r] >= 0 ? min(rp.nrun, rp.pos[r] / (kMkSpan * rp.spu) + 1) : 0;
-}
 
 // nrun: runs that hold the launch's live spans; unit u of them.
 __device__ __forceinline__ MkAttnUnit mk_attn_unit(const MkArgs& a, const MkRows& rp, int nrun, int spu, int u) {
@@ -1162,8 +1163,6 @@ __global__ __launch_bounds__(kMkThreads) void k_mk(MkArgs a) {
     static_assert(sizeof(MkPhase) % 4 == 0 && kWords <= 64, "phase descriptor larger than one wave");
     mk_plan(a, rp);
     if (threadIdx.x < kWords) ((uint32_t*)&op_lds[0])[threadIdx.x] = mk_ldu((const uint32_t*)&a.prog[0] + threadIdx.x);
-    __syncthreads();
-    if (threadIdx.x == 0) mk_attn_plan(a, rp);
     __syncthreads();
     int gen = (int)a.bar_gen;
     long spins = 0;
