@@ -99,7 +99,7 @@ ROOFLINE_KERNEL = "k_mk"
 
 
 def _kclass(name):
-    for k in ("k_mk", "k_wsgemv", "k_attn"):
+    for k in ("k_mk", "k_wsgemv", "k_pgemm", "k_sgemm", "k_vattn", "k_pattn"):
         if k + "(" in name or k + "<" in name:
             return k
     return "other"

@@ -68,7 +68,7 @@ __device__ __forceinline__ void attn_put4(const AttnArgs& a, size_t row, int c, 
 // runs in registers, with its max and sum taken over the four lane groups of a column by two
 // lane-swap steps, and P never goes through LDS.  With few (sequence, KV head, row block)
 // groups the keys are split into at most 16 spans of span_t tiles (about eight workgroups per
-// compute unit): every span writes an un-normalised partial into k_attn's partial buffer and
+// compute unit): every span writes an un-normalised partial and
 // the last span of a group to arrive merges them in span order, all spans' loads at once.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPaQ = 16;                  // query rows per workgroup

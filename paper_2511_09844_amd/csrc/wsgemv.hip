@@ -1,4 +1,6 @@
-// Weight-streaming projection for bf16 weights and up to 16 activation rows per launch.
+// Weight-streaming projection for bf16 weights and up to 16 fp32 activation rows per launch: the
+// steering projections, and every projection of a static workspace without room for planes (see
+// pgemm.hip for the others).
 //
 //   Y[m][n] (op)= sum_k W[n][k] * xn[m][k],   xn = x (optionally RMS-normalised and scaled by gamma)
 //
@@ -425,6 +427,10 @@ void launch_wsgemv(Engine* e, hipStream_t s, const WsCall& c) {
     // rows that come as planes, and more than one 16-row group, run on the plane kernel
     // (pgemm.hip); up to 16 fp32 rows (the steering projections) save the launch that makes planes
     if ((c.planes || c.M > 16) && launch_pgemm(e, s, c)) return;
+    if (c.planes) {  // there are no fp32 rows to fall back on
+        if (e) e->bad_launch = true;
+        return;
+    }
     for (int r0 = 0; r0 < c.M; r0 += 16) {
         int M = c.M - r0 < 16 ? c.M - r0 : 16;
         WsArgs a{};
