@@ -362,6 +362,8 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
 // through LDS, and the last live span of a group to arrive merges the spans.
 //
 // Bound: K/V bytes at long contexts, one tile's chain of load, products and softmax at short ones.
+// 4 sequences of 6 rows at 201 to 901 positions, 32/8 heads, head dim 128: 18 us (115 with the vector
+// kernel before); 16 of 8 rows at 256 to 2048: 61 us (80 with two heads per tile staged through LDS).
 // ---------------------------------------------------------------------------------------------
 constexpr int kVaMaxRows = 15;  // rows per sequence up to which blocks run here
 constexpr int kVaMinTiles = 8;  // key tiles per span: two per wave
