@@ -10,6 +10,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "attn_part.h"
 #include "device_common.h"
 #include "engine.h"
 #include "pgemm.h"
@@ -490,12 +491,11 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
         ls[wave][col] = l_run;
     }
     __syncthreads();
-    // spans: outputs [row][head][span][HD], then (max, sum) [row][head][span][2]
-    const int rows = a.nseq * a.rps;
-    float* const pml = a.part + (size_t)rows * a.H * nspan * HD;
-    const size_t ph0 = (size_t)rbase * a.H * nspan;  // the sequence's first
+    // spans: outputs and (max, sum) pairs (see attn_part.h)
+    const int rows = a.nseq * a.rps, block = (b * a.Hkv + kvh) * ncg + cg;
+    const size_t ph0 = part_out(rbase, a.H, 0, nspan, 0, HD);  // the sequence's first
     const __amdgpu_buffer_rsrc_t prs =
-        __builtin_amdgcn_make_buffer_rsrc(a.part + ph0 * HD, 0, nrows * a.H * nspan * HD * 4, 0x00027000);
+        __builtin_amdgcn_make_buffer_rsrc(a.part + ph0, 0, nrows * a.H * nspan * HD * 4, 0x00027000);
     float w[4], M = -INFINITY, L = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k) M = fmaxf(M, ms[k][col]);
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
         L += w[k] * ls[k][col];
     }
     const float inv = nlive == 1 ? (L > 0.f ? 1.f / L : 0.f) : 1.f;
-    const size_t ph = ((size_t)vrow * a.H + h) * nspan + sp;
+    const size_t ph = part_out(vrow, a.H, h, nspan, sp, HD);
 #pragma unroll
     for (int i0 = 0; i0 < NO; i0 += 4) {
         const int i = i0 + wave;
@@ -525,18 +525,19 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
             }
         } else if constexpr (VV == 4) {
             // (one 16-byte write-through store)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, x), prs, (int)(((ph - ph0) * HD + d) * 4), 0, 16);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, x), prs, (int)((ph - ph0 + d) * 4), 0, 16);
         } else {
 #pragma unroll
-            for (int e = 0; e < VV; ++e) store_through(a.part + ph * HD + d + e, x[e]);
+            for (int e = 0; e < VV; ++e) store_through(a.part + ph + d + e, x[e]);
         }
     }
     if (nlive > 1 && vok && grp == 0 && wave == 0) {
-        store_through(pml + ph * 2, M);
-        store_through(pml + ph * 2 + 1, L);
+        float* const pml = a.part + part_ml(rows, a.H, HD, block, nspan, sp, col);
+        store_through(pml, M);
+        store_through(pml + 1, L);
     }
     if (nlive == 1) return;
-    if (!arrive_last(a.cnt + (b * a.Hkv + kvh) * ncg + cg, nlive, &last_flag)) return;
+    if (!arrive_last(a.cnt + block, nlive, &last_flag)) return;
     // the last live span merges: a thread per (vector, 4 dims), spans eight per round trip (loads
     // past the last live span re-read it and are not added)
     constexpr int D4 = HD / 4;
@@ -544,7 +545,7 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
         const int v = cg * 16 + idx / D4, d = (idx % D4) * 4;
         if (v >= nv) break;
         const int h = kvh * G + v % G;
-        const size_t row = (size_t)rbase + v / G, ph = (row * a.H + h) * nspan;
+        const size_t row = (size_t)rbase + v / G;
         float M = -INFINITY, L = 0.f;
         pf4 O = {0.f, 0.f, 0.f, 0.f};
         for (int s0 = 0; s0 < nlive; s0 += 8) {
@@ -552,9 +553,9 @@ __global__ __launch_bounds__(256, 2) void k_vattn(AttnArgs a, int ncg, int nspan
             pf2 ml[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const size_t e = ph + min(s0 + k, nlive - 1);
-                ov[k] = *(const pf4*)(a.part + e * HD + d);
-                ml[k] = *(const pf2*)(pml + e * 2);
+                const int s2 = min(s0 + k, nlive - 1);
+                ov[k] = *(const pf4*)(a.part + part_out(row, a.H, h, nspan, s2, HD) + d);
+                ml[k] = *(const pf2*)(a.part + part_ml(rows, a.H, HD, block, nspan, s2, idx / D4));
             }
             float Mn = M;
 #pragma unroll
@@ -589,7 +590,7 @@ static void launch_vattn(Engine& e, hipStream_t s, const AttnArgs& a) {
     span_t = (std::max(span_t, (tiles + 47) / 48) + 3) / 4 * 4;
     int nspan = (tiles + span_t - 1) / span_t;
     // the partials' and counters' room
-    const size_t per = (size_t)a.nseq * a.rps * a.H * (HD + 2);
+    const size_t per = part_floats((size_t)a.nseq * a.rps, a.H, HD, ng);
     if ((size_t)ng > e.ws.attn_cnt_n || per * nspan > e.ws.attn_part_n) {
         nspan = (size_t)ng > e.ws.attn_cnt_n ? 1 : std::max<int>(1, e.ws.attn_part_n / per);
         span_t = ((tiles + nspan - 1) / nspan + 3) / 4 * 4;
