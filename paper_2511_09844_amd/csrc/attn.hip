@@ -30,9 +30,8 @@ struct AttnArgs {
     const int32_t* row_off;  // packed rows: first row of every sequence (its rows: up to the next one's), or null
     int rps, H, Hkv, hd, cap, max_batch, layer;
     int nseq;   // sequences
-    int nsplit; // spans the partials have room for
     float scale;
-    float* part;     // k_pattn: [row][head][nsplit][HD + 2]
+    float* part;     // partials of the spans (see attn_part.h)
     int32_t* cnt;    // one arrival counter per workgroup of the split-free grid
 };
 
@@ -111,15 +110,15 @@ __device__ void pa_span_merge(const AttnArgs& a, int grp_id, int nspan, int span
         const int h = kvh * G + hh;
         float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
         if (qpos[i] >= 0 && nlive > 0) {
-            const float* pp = a.part + (orow * a.H + h) * a.nsplit * (HD + 2);
             float m2[kPaMaxSpans], l2[kPaMaxSpans];
             float4 o2[kPaMaxSpans];
 #pragma unroll
             for (int s2 = 0; s2 < kPaMaxSpans; ++s2) {
-                const float* e2 = pp + (size_t)min(s2, nlive - 1) * (HD + 2);
-                m2[s2] = e2[HD];
-                l2[s2] = e2[HD + 1];
-                o2[s2] = make_float4(e2[d], e2[d + 1], e2[d + 2], e2[d + 3]);
+                const int sp = min(s2, nlive - 1);
+                const pf2 ml = *(const pf2*)(a.part + part_ml((size_t)a.nseq * a.rps, a.H, HD, grp_id * G + hh, nspan, sp, i));
+                m2[s2] = ml[0];
+                l2[s2] = ml[1];
+                o2[s2] = *(const float4*)(a.part + part_out(orow, a.H, h, nspan, sp, HD) + d);
             }
             float M = -INFINITY;
 #pragma unroll
@@ -315,9 +314,9 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
             }
             if (nspan > 1 && grp == 0 && i0 + col < nrows) {
                 // this span's max and sum of the lane's row
-                float* pp = a.part + (((size_t)(rbase + i0 + col) * a.H + h) * a.nsplit + sp) * (HD + 2);
-                store_through(pp + HD, m_run);
-                store_through(pp + HD + 1, l_run);
+                float* pp = a.part + part_ml((size_t)a.nseq * a.rps, a.H, HD, grp_id * G + hh, nspan, sp, col);
+                store_through(pp, m_run);
+                store_through(pp + 1, l_run);
             }
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's rows are in LDS
             __builtin_amdgcn_wave_barrier();
@@ -336,7 +335,7 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
                     const int d = lane + 64 * j;
                     if (i0 + i < nrows && d < HD) {
                         if (nspan == 1) attn_put1(a, orow, h * HD + d, rv[i][j]);
-                        else store_through(a.part + ((orow * a.H + h) * a.nsplit + sp) * (HD + 2) + d, rv[i][j]);
+                        else store_through(a.part + part_out(orow, a.H, h, nspan, sp, HD) + d, rv[i][j]);
                     }
                 }
             }
@@ -612,14 +611,13 @@ static void launch_pattn(Engine& e, hipStream_t s, AttnArgs a) {
     int nspan = 1, span_t = 1;
     if (groups < 256 && (size_t)groups <= e.ws.attn_cnt_n) {
         const int tiles = (a.cap + kPaK - 1) / kPaK;
-        nspan = std::min(std::min(kPaMaxSpans, a.nsplit), std::max(1, 2048 / groups));
+        nspan = std::min(std::min(kPaMaxSpans, attn_nsplit(a.cap)), std::max(1, 2048 / groups));
         // (as many as the partials have room for)
-        const size_t per = (size_t)a.nseq * a.rps * a.H * (a.hd + 2);
+        const size_t per = part_floats((size_t)a.nseq * a.rps, a.H, a.hd, (size_t)groups * (a.H / a.Hkv));
         nspan = std::max<int>(1, std::min<size_t>(nspan, e.ws.attn_part_n / per));
         span_t = (tiles + nspan - 1) / nspan;
         nspan = (tiles + span_t - 1) / span_t;
     }
-    a.nsplit = nspan;
     dim3 grid(groups * nspan);
     ProfEntry* pe = prof_slot(&e, kProfAttn, 0.0);
     hipEvent_t ea = pe ? pe->a : nullptr, eb = pe ? pe->b : nullptr;
@@ -644,7 +642,6 @@ void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int
     a.layer = layer;
     a.nseq = rows / rps;
     a.scale = 1.0f / sqrtf((float)m.hd);
-    a.nsplit = attn_nsplit(e.cap);
     a.part = e.ws.attn_part;
     a.cnt = e.ws.attn_cnt;
     // the kernels read query rows and write output rows as 16-byte vectors

@@ -62,3 +62,17 @@ def test_few_row_spans_share_no_line_between_groups(lib, hd, nseq, rps, Hkv, G):
             values.append((block, lib.out_at(row, H, h, nspan, sp, hd), hd))
             values.append((block, lib.ml_at(rows, H, hd, block, nspan, sp, v % 16), 2))
         _check(values, nspan * lib.floats(rows, H, hd, nseq * Hkv * ncg))
+
+
+@pytest.mark.parametrize("hd", [32, 64, 128])
+@pytest.mark.parametrize("nseq,rps,Hkv,G", [(1, 16, 12, 1), (1, 37, 3, 4), (3, 17, 1, 5)])
+def test_many_row_spans_share_no_line_between_groups(lib, hd, nseq, rps, Hkv, G):
+    # groups of k_pattn: (sequence, KV head, 16 rows)
+    H, rows, nqb = Hkv * G, nseq * rps, (rps + 15) // 16
+    for nspan in (1, 3):
+        values = []
+        for b, kvh, i, g, sp in itertools.product(range(nseq), range(Hkv), range(rps), range(G), range(nspan)):
+            group, row, h = (b * Hkv + kvh) * nqb + i // 16, b * rps + i, kvh * G + g
+            values.append((group, lib.out_at(row, H, h, nspan, sp, hd), hd))
+            values.append((group, lib.ml_at(rows, H, hd, group * G + g, nspan, sp, i % 16), 2))
+        _check(values, nspan * lib.floats(rows, H, hd, nseq * Hkv * nqb * G))
