@@ -28,4 +28,10 @@ SD2_PART_FN size_t part_ml(size_t rows, int H, int hd, size_t block, int nspan, 
 // Floats per span.
 SD2_PART_FN size_t part_floats(size_t rows, int H, int hd, size_t blocks) { return rows * H * hd + blocks * kPartLine; }
 
+// Persistent kernel: floats of an activation row's head, nsplit records of hd + 4 (outputs, max, sum)
+// padded to whole lines (a row's head lies in one group).
+SD2_PART_FN size_t part_row(int nsplit, int hd) {
+    return ((size_t)nsplit * (hd + 4) + kPartLine - 1) / kPartLine * kPartLine;
+}
+
 }  // namespace sd2

@@ -46,7 +46,8 @@ struct MkPhase {
     int32_t* cnt;            // S > 1: arrival counter per tile; ATTN: per (sequence, KV head, query group)
     float* qout;             // Qkv: queries [M][H*hd]; ATTN: query source
     float* aout;             // ATTN: output [M][H*hd]
-    float* apart;            // ATTN: partials [M][H][nsplit][hd+4] (outputs, span max, span sum)
+    float* apart;            // ATTN: partials [M][H][nsplit][hd+4] (outputs, max, sum of a run), a row's head in
+                             // whole lines (see attn_part.h)
     const float* ubias;      // MLP steering, per sequence: SwiGLU, this layer's up-projection bias; Add (down
                              // projection), the bias after the MLP; or null
 };

@@ -26,6 +26,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "attn_part.h"
 #include "device_common.h"
 #include "engine.h"
 #include "mk.h"
@@ -418,14 +419,15 @@ __device__ __forceinline__ void mk_gemv(const MkArgs& a, const MkPhase& od, cons
         // The rows are attention outputs still split into span partials (output, span max, span
         // sum per row, head and span): each thread merges its 4 columns over the spans its row
         // sees, all spans' partials requested at once (up to 16 per round trip), then stages them.
-        const int HD = a.hd, ns = mk_uni(od.nsplit);
+        const int HD = a.hd;
+        const size_t prow = part_row(mk_uni(od.nsplit), HD);
         for (int m = 0; m < M; ++m) {
             const int nl = rp.nl[m];
             float sqm = 0.f;
             for (int c = tid; c < n4 && tid < kNT; c += kNT) {
                 const int kk = k0 + 4 * c, h = kk / HD, d = kk % HD;
                 float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-                const float* pb = oX + ((size_t)m * a.H + h) * ns * (HD + 4);
+                const float* pb = oX + ((size_t)m * a.H + h) * prow;
                 float Mx = -INFINITY, L = 0.f;
                 float4 O = make_float4(0.f, 0.f, 0.f, 0.f);
                 for (int s0 = 0; s0 < nl; s0 += 16) {
@@ -1015,7 +1017,7 @@ __device__ __forceinline__ void mk_attn_t(const MkArgs& a, const MkPhase& od, co
                         const float l = lq[qi];
                         mk_stf(o.aout + (size_t)row * a.H * HD + h * HD + d, l > 0.f ? acc[i] / l : 0.f);
                     } else {
-                        float* pp = o.apart + (((size_t)row * a.H + h) * o.nsplit + sp) * (HD + 4);
+                        float* pp = o.apart + ((size_t)row * a.H + h) * part_row(o.nsplit, HD) + sp * (HD + 4);
                         mk_stf(pp + d, acc[i]);
                         if (d == 0) {
                             mk_stf(pp + HD, mq[qi]);
@@ -1046,7 +1048,7 @@ __device__ __forceinline__ void mk_attn_t(const MkArgs& a, const MkPhase& od, co
             const int row = sq * a.rps + qv / Gq, h = kvh * Gq + qv % Gq;
             float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
             if (rp.pos[row] >= 0) {
-                const float* pb = o.apart + ((size_t)row * a.H + h) * o.nsplit * (HD + 4);
+                const float* pb = o.apart + ((size_t)row * a.H + h) * part_row(o.nsplit, HD);
                 float Mx = -INFINITY, L = 0.f;
                 float4 O = make_float4(0.f, 0.f, 0.f, 0.f);
                 for (int s0 = 0; s0 < nl; s0 += 16) {
@@ -1300,7 +1302,7 @@ bool mk_record(const sd2_config& c, const ModelDev& m, bool verifier, int M, int
         float* xa = ar.take<float>((size_t)M * dm);
         float* hbuf = ar.take<float>((size_t)M * F);
         float* xf = ar.take<float>((size_t)M * dm);
-        float* apart = ar.take<float>((size_t)M * H * nsplit * (hd + 4));
+        float* apart = ar.take<float>((size_t)M * H * part_row(nsplit, hd));
         float* ss = (l == L - 1) ? ar.take<float>((size_t)M * (dm / 16)) : nullptr;
         MkPhase qkv{};
         if (!gemv(kEpiQkv, (H + 2 * Hkv) * hd, dm, Wl[kAttnNorm], true, 1, qkv)) return false;

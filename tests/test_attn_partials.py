@@ -19,6 +19,7 @@ size_t out_at(size_t row, int H, int h, int nspan, int sp, int hd) { return sd2:
 size_t ml_at(size_t rows, int H, int hd, size_t block, int nspan, int sp, int i) {
     return sd2::part_ml(rows, H, hd, block, nspan, sp, i);
 }
+size_t row_floats(int nsplit, int hd) { return sd2::part_row(nsplit, hd); }
 size_t floats(size_t rows, int H, int hd, size_t blocks) { return sd2::part_floats(rows, H, hd, blocks); }
 }
 """
@@ -33,10 +34,11 @@ def lib(tmp_path_factory):
                            os.path.join(ROOT, "paper_2511_09844_amd", "csrc"), str(d / "p.cpp"), "-o", str(so)])
     lib = ctypes.CDLL(str(so))
     sz, i = ctypes.c_size_t, ctypes.c_int
-    lib.out_at.restype = lib.ml_at.restype = lib.floats.restype = sz
+    lib.out_at.restype = lib.ml_at.restype = lib.floats.restype = lib.row_floats.restype = sz
     lib.out_at.argtypes = [sz, i, i, i, i, i]
     lib.ml_at.argtypes = [sz, i, i, sz, i, i, i]
     lib.floats.argtypes = [sz, i, i, sz]
+    lib.row_floats.argtypes = [i, i]
     return lib
 
 
@@ -76,3 +78,11 @@ def test_many_row_spans_share_no_line_between_groups(lib, hd, nseq, rps, Hkv, G)
             values.append((group, lib.out_at(row, H, h, nspan, sp, hd), hd))
             values.append((group, lib.ml_at(rows, H, hd, group * G + g, nspan, sp, i % 16), 2))
         _check(values, nspan * lib.floats(rows, H, hd, nseq * Hkv * nqb * G))
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("nsplit", [2, 3, 9, 13, 24])
+def test_persistent_runs_share_no_line_between_groups(lib, hd, nsplit):
+    # a group holds whole (row, head) pairs: 2 rows x 3 heads, every run live
+    values = [(rh, rh * lib.row_floats(nsplit, hd) + sp * (hd + 4), hd + 2) for rh in range(6) for sp in range(nsplit)]
+    _check(values, 6 * lib.row_floats(nsplit, hd))
