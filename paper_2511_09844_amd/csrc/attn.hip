@@ -365,7 +365,6 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
 // 4 sequences of 6 rows at 201 to 901 positions, 32/8 heads, head dim 128: 18 us (115 with the vector
 // kernel before); 16 of 8 rows at 256 to 2048: 61 us (80 with two heads per tile staged through LDS).
 // ---------------------------------------------------------------------------------------------
-constexpr int kVaMaxRows = 15;  // rows per sequence up to which blocks run here
 constexpr int kVaMinTiles = 8;  // key tiles per span: two per wave
 
 template <int HD>
@@ -590,8 +589,8 @@ static void launch_vattn(Engine& e, hipStream_t s, const AttnArgs& a) {
     int nspan = (tiles + span_t - 1) / span_t;
     // the partials' and counters' room
     const size_t per = part_floats((size_t)a.nseq * a.rps, a.H, HD, ng);
-    if ((size_t)ng > e.ws.attn_cnt_n || per * nspan > e.ws.attn_part_n) {
-        nspan = (size_t)ng > e.ws.attn_cnt_n ? 1 : std::max<int>(1, e.ws.attn_part_n / per);
+    if ((size_t)ng > e.ws.cnt_n || per * nspan > e.ws.attn_part_n) {
+        nspan = (size_t)ng > e.ws.cnt_n ? 1 : std::max<int>(1, e.ws.attn_part_n / per);
         span_t = ((tiles + nspan - 1) / nspan + 3) / 4 * 4;
         nspan = (tiles + span_t - 1) / span_t;
     }
@@ -609,7 +608,7 @@ static void launch_pattn(Engine& e, hipStream_t s, AttnArgs a) {
     // since spans past a sequence's length exit at once (at most 16 spans, within the decode
     // kernel's partial buffer and counters)
     int nspan = 1, span_t = 1;
-    if (groups < 256 && (size_t)groups <= e.ws.attn_cnt_n) {
+    if (groups < kPattnGroups && (size_t)groups <= e.ws.cnt_n) {
         const int tiles = (a.cap + kPaK - 1) / kPaK;
         nspan = std::min(std::min(kPaMaxSpans, attn_nsplit(a.cap)), std::max(1, 2048 / groups));
         // (as many as the partials have room for)
@@ -643,7 +642,7 @@ void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int
     a.nseq = rows / rps;
     a.scale = 1.0f / sqrtf((float)m.hd);
     a.part = e.ws.attn_part;
-    a.cnt = e.ws.attn_cnt;
+    a.cnt = e.ws.cnt;
     // the kernels read query rows and write output rows as 16-byte vectors
     if (a.q_stride % 4 || ((uintptr_t)a.q & 15) || ((uintptr_t)a.out & 15)) {
         e.bad_launch = true;
@@ -662,10 +661,14 @@ void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int
     }
 }
 
-// Arrival counters of an attention launch: one per sequence, KV head and 16 query vectors (more
-// than the blocks of 16 rows that k_pattn counts).
-size_t attn_groups(int rows, int rps, int H, int Hkv) {
-    return (size_t)(rows / rps) * Hkv * ((rps * (H / Hkv) + 15) / 16);
+// Arrival counters of attention launches of up to rps rows per sequence, one per group while the keys
+// are split.  k_vattn: a group per sequence, KV head and 16 query vectors, unsplit from 8 of them per
+// key tile, where a span holds all tiles (see launch_vattn).  k_pattn: per sequence, KV head and 16
+// rows.
+size_t attn_counters(int nseq, int rps, int H, int Hkv, int cap) {
+    const int ng = nseq * Hkv * ((std::min(rps, kVaMaxRows) * (H / Hkv) + 15) / 16);
+    const int groups = rps > kVaMaxRows ? nseq * Hkv * ((rps + kPaQ - 1) / kPaQ) : 0;
+    return std::max(std::min(ng, 8 * ((cap + 15) / 16)), std::min(groups, kPattnGroups));
 }
 
 int attn_nsplit(int cap) { return (cap + kSplit - 1) / kSplit; }

@@ -56,7 +56,9 @@ struct Workspace {
     // row plans
     int32_t* row_pos;       // [maxm]
     int32_t* row_seq;       // [maxm]
-    int32_t* row_off;       // [max_batch + 1] prefill: first row of each sequence's live rows, and their number
+    // [max_batch + 1] prefill: first row of each sequence's live rows, and their number (bf16; in the
+    // sampler's partials, which no prefill uses)
+    int32_t* row_off;
     int32_t* lm_map_d;      // [k][2*max_batch] drafter LM-head output rows per step
     int32_t* steer_map;     // [max_batch]
     int32_t* ident_map;     // [2 max_batch] 0..2 max_batch-1
@@ -80,18 +82,16 @@ struct Workspace {
     int32_t* forced;        // [max_batch][k+2]
     int32_t* forced_on;     // [1]
     // split-K partial tiles of the projection kernel; attention partials per position span
-    // planes of the residual rows (see pgemm.hip), or null: without them (fp32 weights, a static
-    // workspace too small) every projection reads fp32 rows.  With them attn and ffh hold planes
-    // as well, and ffh has ffh_n bytes.
+    // planes of the residual rows (see pgemm.hip); null with fp32 weights, whose projections read fp32
+    // rows.  With them attn and ffh hold planes as well, and ffh has ffh_n bytes.
     uint16_t* planes;
     size_t ffh_n;
     float* ws_part;
-    int32_t* ws_cnt;
-    size_t ws_part_n, ws_cnt_n;  // their capacities (floats, counters)
+    size_t ws_part_n;       // floats of ws_part
     float* attn_part;
-    int32_t* attn_cnt;
+    int32_t* cnt;           // arrival counters of projections and attention, zero between launches
     int32_t* nonfinite;     // set to 1 by the sampler when a logit row it reads holds a NaN or an infinity
-    size_t attn_cnt_n;      // capacity of attn_cnt (counters)
+    size_t cnt_n;           // capacity of cnt (counters)
     size_t attn_part_n;     // capacity of attn_part (floats)
     // MLP steering (null unless cfg.steering == SD2_STEER_MLP)
     float* taps;            // [3][maxm][d_V] verifier residual after the tap blocks (per-operation path)
@@ -158,11 +158,12 @@ void prof_end(Engine* e);
 ProfEntry* prof_slot(Engine* e, int cls, double bytes);
 void prof_commit(Engine* e);
 
-// Workspace forms.  kWsFull: prefill chunks of kPrefillRows.  kWsSmall: of kPrefillRowsSmall (fp32
-// weights, and every configuration whose workspace then fits the static one, so that a handle
-// computes the same in either).  kWsLean: small, and without planes, projections then running 16 fp32
-// rows at a time (a static workspace that holds the configuration only so).
-enum WsForm { kWsFull, kWsSmall, kWsLean };
+// Workspace forms.  kWsFull: prefill chunks of kPrefillRows.  kWsSmall: of kPrefillRowsSmall, for
+// fp32 weights and for every configuration whose workspace then fits the static one, whoever provides
+// it, so that a handle computes the same in either.  Its split-K partials get what the plans ask for
+// as far as the total stays within the static size, and small_part_room() at least, by which the
+// set of configurations that fit is fixed; the plans split K as far as they have room.
+enum WsForm { kWsFull, kWsSmall };
 size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, ModelDev* md, int* maxm,
              MkState* mk = nullptr, WsForm form = kWsFull);
 
@@ -234,7 +235,9 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c);
 
 void launch_attn(Engine& e, hipStream_t s, ModelDev& m, int layer, int rows, int rps, const float* q, int q_stride);
 int attn_nsplit(int cap);
-size_t attn_groups(int rows, int rps, int H, int Hkv);
+size_t attn_counters(int nseq, int rps, int H, int Hkv, int cap);
+constexpr int kVaMaxRows = 15;     // rows per sequence up to which attention runs on k_vattn, above on k_pattn
+constexpr int kPattnGroups = 256;  // groups from which k_pattn leaves the keys unsplit
 void launch_gemv(Engine* e, hipStream_t s, bool bf16, const float* X, const int32_t* in_map, int M, int K,
                  const void* gamma, float eps, const void* const* W, const int* seg_rows, int nseg, int epi, float* Y,
                  int ldy, const int32_t* out_map, const float* ubias = nullptr, int ub_ld = 0,

@@ -96,6 +96,21 @@ int bias_len(const sd2_config& c) {
     return c.steering == SD2_STEER_MLP ? c.drafter.n_layers * c.drafter.d_ff : c.drafter.d_model;
 }
 
+// Floats of partials that the small form holds at least, for N weight rows (gate and up apart) on up
+// to maxm rows: sums of 64-row by 16-column tiles, K halved while the launch has at most 256 blocks
+// of 64 rows by 128 columns (64 of gate and up) and a range keeps 1024 columns (512 for one block of
+// rows).
+size_t small_part_room(int maxm, int N, int K, int subs) {
+    size_t room = 0;
+    for (int nbm = 1; nbm <= (maxm + 63) / 64; ++nbm) {
+        const int nbn = (N / 16 * subs + 7) / 8, blocks = 8 * nbm * ((nbn + 7) / 8), min_k = nbm == 1 ? 512 : 1024;
+        int S = 1;
+        while (blocks * S * 2 <= 512 && K % (S * 2) == 0 && (K / (S * 2)) % 256 == 0 && K / (S * 2) >= min_k) S *= 2;
+        if (S > 1) room = std::max(room, (size_t)nbm * (N / 16) * S * subs * 1024);
+    }
+    return room;
+}
+
 WsForm ws_form(const sd2_config& c) {
     return c.dtype == SD2_F32 || carve(c, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, kWsSmall) <= kStaticWorkspaceBytes
                ? kWsSmall
@@ -141,7 +156,6 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
     w.hcap_ss = cv.take<float>((size_t)B * (c.verifier.d_model / 16));
     w.row_pos = cv.take<int32_t>(maxm);
     w.row_seq = cv.take<int32_t>(maxm);
-    if (c.dtype == SD2_BF16 && form != kWsLean) w.row_off = cv.take<int32_t>(B + 1);
     w.lm_map_d = cv.take<int32_t>((size_t)k * 2 * B);
     w.steer_map = cv.take<int32_t>(B);
     w.ident_map = cv.take<int32_t>(2 * (size_t)B);
@@ -149,7 +163,7 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
     int att = std::max(c.verifier.n_heads * ms[0]->hd, c.drafter.n_heads * ms[1]->hd);
     int ff = std::max(c.verifier.d_ff, c.drafter.d_ff);
     w.qkv = cv.take<float>((size_t)maxm * qkv);
-    const bool planes = c.dtype == SD2_BF16 && form != kWsLean;
+    const bool planes = c.dtype == SD2_BF16;
     w.attn = cv.take<float>(planes ? pg_plane_bytes(maxm, att) / 4 : (size_t)maxm * att);
     w.ffh_n = planes ? pg_plane_bytes(maxm, ff) : 0;
     w.ffh = cv.take<float>(planes ? w.ffh_n / 4 : (size_t)maxm * ff);
@@ -157,6 +171,8 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
     w.logits_d = cv.take<float>((size_t)B * k * V);
     w.hidden_dbg = cv.take<float>((size_t)B * (k + 1) * c.verifier.d_model);
     w.part = cv.take<VPart>((size_t)B * (2 * k + 1) * kVocabChunks);
+    static_assert(kVocabChunks * sizeof(VPart) >= 2 * sizeof(int32_t), "B + 1 offsets fit the sampler's partials");
+    if (planes) w.row_off = (int32_t*)w.part;
     w.lse_v = cv.take<float>((size_t)B * (k + 1));
     w.lse_d = cv.take<float>((size_t)B * k);
     w.argmax_v = cv.take<int32_t>((size_t)B * (k + 1));
@@ -167,9 +183,10 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
     w.own_y = cv.take<int32_t>(B);
     w.forced = cv.take<int32_t>((size_t)B * (k + 2));
     w.forced_on = cv.take<int32_t>(1);
-    // projection split-K partials: the largest tiles*S*256*subs over every projection shape
+    // projection split-K partials (taken last): the largest tiles*S*256*subs over every projection
+    // shape of k_wsgemv, and what the plane kernel asks for
+    size_t pmax = 0, pask = 0, cnt = 1;
     {
-        size_t pmax = 0, pg_cnt = 0;
         const sd2_dims* dd[2] = {&c.verifier, &c.drafter};
         int mmax = std::min(maxm, 16);
         for (int i = 0; i < 2; ++i) {
@@ -209,36 +226,30 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
         for (int i = 0; i < 2 && planes; ++i) {
             const sd2_dims& d = *dd[i];
             int hd = d.d_model / d.n_heads;
-            int shapes[10][2] = {{(d.n_heads + 2 * d.n_kv_heads) * hd, d.d_model},
-                                 {d.d_model, d.n_heads * hd},
-                                 {2 * d.d_ff, d.d_model},
-                                 {d.d_model, d.d_ff},
-                                 {d.vocab, d.d_model},
-                                 {c.drafter.d_model, c.verifier.d_model},
-                                 {mf ? c.verifier.d_model : 0, 3 * c.verifier.d_model},
-                                 {mf ? bias_len(c) : 0, c.verifier.d_model},
-                                 {R, c.drafter.d_model},
-                                 {R ? c.drafter.d_ff : 0, R}};
-            // the plan depends on the rows only through their number of 16-row groups
-            for (int rows = 16; rows <= pg_rows(maxm); rows += 16)
-                for (auto& sh : shapes) {
-                    if (sh[0] <= 0) continue;
-                    for (int packed = 0; packed < 2; ++packed) {
-                        const PgPlan p = pg_plan(rows, sh[0], sh[1], packed);
-                        pmax = std::max(pmax, p.part);
-                        pg_cnt = std::max(pg_cnt, p.cnt);
-                    }
-                }
+            int shapes[10][3] = {{(d.n_heads + 2 * d.n_kv_heads) * hd, d.d_model, 1},
+                                 {d.d_model, d.n_heads * hd, 1},
+                                 {d.d_ff, d.d_model, 2},
+                                 {d.d_model, d.d_ff, 1},
+                                 {d.vocab, d.d_model, 1},
+                                 {c.drafter.d_model, c.verifier.d_model, 1},
+                                 {mf ? c.verifier.d_model : 0, 3 * c.verifier.d_model, 1},
+                                 {mf ? bias_len(c) : 0, c.verifier.d_model, 1},
+                                 {R, c.drafter.d_model, 1},
+                                 {R ? c.drafter.d_ff : 0, R, 1}};
+            for (auto& sh : shapes) {
+                if (sh[0] <= 0) continue;
+                pmax = std::max(pmax, small_part_room(maxm, sh[0], sh[1], sh[2]));
+                // the plan depends on the rows only through their number of 16-row groups
+                for (int rows = 16; rows <= pg_rows(maxm); rows += 16)
+                    for (int packed = 0; packed < 2; ++packed)
+                        pask = std::max(pask, pg_plan(rows, sh[0] * sh[2], sh[1], packed).part);
+            }
         }
-        w.ws_part = cv.take<float>(std::max<size_t>(pmax, 1));
-        w.ws_part_n = std::max<size_t>(pmax, 1);
-        size_t tmax = (size_t)std::max(c.verifier.vocab, c.drafter.vocab) / 16 + 1;
+        cnt = (size_t)std::max(c.verifier.vocab, c.drafter.vocab) / 16 + 1;
         for (int i = 0; i < 2; ++i)
-            tmax = std::max(tmax, (size_t)std::max(dd[i]->d_ff, dd[i]->d_model) / 16 + 1);
-        if (mlp_form(c)) tmax = std::max(tmax, (size_t)bias_len(c) / 16 + 1);
-        tmax = std::max(tmax, pg_cnt);
-        w.ws_cnt = cv.take<int32_t>(tmax);
-        w.ws_cnt_n = tmax;
+            cnt = std::max(cnt, (size_t)std::max(dd[i]->d_ff, dd[i]->d_model) / 16 + 1);
+        if (mlp_form(c)) cnt = std::max(cnt, (size_t)bias_len(c) / 16 + 1);
+        if (pask) cnt = std::max(cnt, (size_t)kPgCounters);
     }
     {
         size_t amax = 0;
@@ -254,21 +265,16 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
         w.attn_part_n = std::max(amax, pn / 4);
         w.attn_part = cv.take<float>(w.attn_part_n);
         w.planes = planes ? (uint16_t*)w.attn_part : nullptr;
-        // arrival counters: the largest split-free grid of any launch shape
-        size_t gmax = 1;
+        // arrival counters of attention launches that split their keys
         for (int i = 0; i < 2; ++i) {
             const sd2_dims& d = *dd[i];
-            gmax = std::max(gmax, attn_groups(2 * B, 2, d.n_heads, d.n_kv_heads));
-            gmax = std::max(gmax, attn_groups(B, 1, d.n_heads, d.n_kv_heads));
-            gmax = std::max(gmax, attn_groups(B * (c.k + 1), c.k + 1, d.n_heads, d.n_kv_heads));
-            for (int nseq = 1; nseq <= B; ++nseq) {
-                int rps = std::max(1, kPrefillRowsSmall / nseq);
-                gmax = std::max(gmax, attn_groups(nseq * rps, rps, d.n_heads, d.n_kv_heads));
-            }
+            for (int nseq = 1; nseq <= B; ++nseq)
+                for (int rps : {2, c.k + 1, (form == kWsFull ? kPrefillRows : kPrefillRowsSmall) / nseq})
+                    cnt = std::max(cnt, attn_counters(nseq, rps, d.n_heads, d.n_kv_heads, cap));
         }
-        w.attn_cnt = cv.take<int32_t>(gmax);
+        w.cnt_n = cnt;
+        w.cnt = cv.take<int32_t>(cnt);
         w.nonfinite = cv.take<int32_t>(4);
-        w.attn_cnt_n = gmax;
     }
     if (mlp_form(c)) {
         const size_t dV = c.verifier.d_model;
@@ -307,9 +313,14 @@ size_t carve(const sd2_config& c, char* base, Workspace* ws, ModelDev* mv, Model
             st.cnt = cv.take<int32_t>(mk_counter_ints(c));
             st.dummy = cv.take<uint16_t>(512);
             st.ones = cv.take<uint16_t>(kMkMaxKR);
-            st.trace = cv.take<int64_t>((size_t)kMkMaxLaunch * kMkTracePhases);
+            st.trace = cv.take<int64_t>((size_t)(k + 1) * kMkTracePhases);
         }
         if (mk) *mk = st;
+    }
+    {
+        const size_t off = align_up(cv.off), left = off < kStaticWorkspaceBytes ? (kStaticWorkspaceBytes - off) / 4 : 0;
+        w.ws_part_n = std::max<size_t>({1, pmax, form == kWsSmall ? std::min(pask, left) : pask});
+        w.ws_part = cv.take<float>(w.ws_part_n);
     }
     if (ws) *ws = w;
     return align_up(cv.off);
@@ -543,12 +554,8 @@ static sd2_status create_impl(const sd2_config* cfg, const sd2_weights* verifier
     const bool unsteered = cfg->steering == SD2_STEER_NONE;
     if (!unsteered && !aligned16(w_steer)) return SD2_ERR_INVALID_ARG;
     if (!workspace || ((uintptr_t)workspace % kAlign) != 0) return SD2_ERR_INVALID_ARG;
-    size_t need = sd2_workspace_bytes(cfg);
-    WsForm form = ws_form(*cfg);
-    if (slot && need > workspace_bytes) {
-        form = kWsLean;
-        need = carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, form);
-    }
+    const WsForm form = ws_form(*cfg);
+    const size_t need = carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, form);
     if (workspace_bytes < need) return SD2_ERR_INVALID_ARG;
     // the kernels are built for gfx950 with XNACK (page-fault replay) off, MI355X's default mode
     {
@@ -692,8 +699,7 @@ sd2_status sd2_create_noalloc(const sd2_config* cfg, const sd2_weights* verifier
     if (!out) return SD2_ERR_INVALID_ARG;
     *out = nullptr;
     if (!config_ok(cfg) || mlp_form(*cfg)) return SD2_ERR_INVALID_ARG;
-    if (carve(*cfg, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, kWsLean) > kStaticWorkspaceBytes)
-        return SD2_ERR_CAPACITY;
+    if (sd2_workspace_bytes(cfg) > kStaticWorkspaceBytes) return SD2_ERR_CAPACITY;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return SD2_ERR_HIP;
     if (dev < 0 || dev >= kStaticMaxDevices) return SD2_ERR_UNSUPPORTED;
@@ -910,6 +916,10 @@ sd2_status sd2_debug_read(sd2_handle_t h, int32_t what, void* dst_host, size_t b
     }
     hipError_t err = hipStreamSynchronize(e->stream);
     if (err != hipSuccess) return hip_fail(e, err, "hipStreamSynchronize");
+    if (what == SD2_DBG_TRACE) {  // the workspace holds the launches of a round, k + 1
+        memset(dst_host, 0, bytes);
+        want = sizeof(int64_t) * (size_t)(k + 1) * kMkTracePhases;
+    }
     if (what == SD2_DBG_STATE) {
         int32_t* out = (int32_t*)dst_host;
         const int32_t* cols[5] = {e->ws.t, e->ws.len_v, e->ws.len_d, e->ws.produced, e->ws.done};

@@ -449,7 +449,7 @@ __global__ __launch_bounds__(128) void k_rope_append(RopeArgs a) {
 static WsCall ws_base(Engine& e, ModelDev& m) {
     WsCall c{};
     c.part = e.ws.ws_part;
-    c.cnt = e.ws.ws_cnt;
+    c.cnt = e.ws.cnt;
     c.eps = m.dm.rms_eps;
     c.nss = m.dm.d_model / 16;
     return c;
@@ -464,11 +464,11 @@ void launch_layer(hipStream_t s, Engine& e, ModelDev& m, int layer, int rows, in
     const void* const* W = m.layer + (size_t)layer * 9;
     int hd = m.hd, H = dm.n_heads, Hkv = dm.n_kv_heads;
     if (e.bf16) {
-        // Every operand passes as planes where the workspace has them: the residual's with the
-        // gain of the norm that reads it next, the attention's and the MLP's as they are.
+        // Every operand passes as planes: the residual's with the gain of the norm that reads it next,
+        // the attention's and the MLP's as they are.
         uint16_t* const xp = e.ws.planes;
-        uint16_t* const ap = xp ? (uint16_t*)e.ws.attn : nullptr;
-        uint16_t* const fp = xp ? (uint16_t*)e.ws.ffh : nullptr;
+        uint16_t* const ap = (uint16_t*)e.ws.attn;
+        uint16_t* const fp = (uint16_t*)e.ws.ffh;
         const int32_t* const live = e.live_off ? e.live_off + e.batch : nullptr;
         // Q|K|V with the attention RMSNorm as prologue, RoPE and the cache append as epilogue
         WsCall c = ws_base(e, m);

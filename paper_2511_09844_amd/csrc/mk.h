@@ -107,7 +107,7 @@ struct MkState {
     const float* tap_x[3]; // verifier launch: residual rows after the steering tap blocks (h, m, l)
     float* final_x;       // verifier launch: final residual rows [M][d_V]
     float* final_ss;      //   and their 16-column sums of squares
-    int64_t* trace;       // [kMkMaxLaunch][kMkTracePhases] phase end times of the last profiled round
+    int64_t* trace;       // [k + 1][kMkTracePhases] phase end times of the last profiled round
 };
 
 struct Engine;

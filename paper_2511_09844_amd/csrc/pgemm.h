@@ -8,29 +8,34 @@ namespace sd2 {
 
 constexpr int kPgBlk = 64;            // columns of one block of the activation planes
 constexpr int kPgBlkWords = 2 * kPgBlk;  // its bf16 words per row: 64 hi, then 64 lo
-// bytes read past the last row of the planes by the last row block (never used)
-constexpr size_t kPgSlack = 128 * kPgBlkWords * 2;
+// The last row block reads up to 112 rows (28 KB) past the end of the planes, never used: the
+// workspace holds more than that behind every plane buffer.
 
 // Shape of a launch: 16 MG rows by 64 NG weight rows per workgroup, K in S ranges.
 struct PgPlan {
     int MG, NG, S, nblk_m, nblk_n, grid;
     bool skinny;  // k_sgemm takes it (nothing else is set)
+    int units;    // block partials the workspace has room for
     size_t part;  // floats of split-K partials (0 without a split)
-    size_t cnt;   // arrival counters
 };
-// K ranges for a number of blocks: up to two workgroups per CU (one with up to 32 rows, 16 MG).
-__host__ __device__ inline int pg_ranges(int blocks, int MG, int K) {
-    const int target = MG <= 2 ? 256 : 512, min_k = MG <= 2 ? 256 : 512;
+// Arrival counters: one per block of a split launch, of which two ranges each come to kPgUnits at most.
+constexpr int kPgUnits = 512, kPgCounters = kPgUnits / 2;
+// K ranges for a number of blocks: up to two workgroups per CU (one with up to 32 rows, 16 MG), and
+// no more block partials than `units`.
+__host__ __device__ inline int pg_ranges(int blocks, int MG, int K, int units) {
+    const int want = MG <= 2 ? kPgUnits / 2 : kPgUnits, min_k = MG <= 2 ? 256 : 512;
+    const int target = want < units ? want : units;
     const int s = target / blocks < K / min_k ? target / blocks : K / min_k;
     return s > 1 ? s : 1;
 }
 // N: weight rows, counting gate and up together.  packed: the rows that hold data may be fewer
-// than M; the kernel then takes blocks and ranges for those (any number may occur).
-PgPlan pg_plan(int M, int N, int K, bool packed = false);
+// than M; the kernel then takes blocks and ranges for those (any number may occur).  room: floats of
+// partials that the workspace holds.
+PgPlan pg_plan(int M, int N, int K, bool packed = false, size_t room = SIZE_MAX);
 
 inline int pg_rows(int M) { return (M + 15) / 16 * 16; }
 // bytes of the planes of M rows and K columns
-inline size_t pg_plane_bytes(int M, int K) { return (size_t)pg_rows(M) * K * 4 + kPgSlack; }
+inline size_t pg_plane_bytes(int M, int K) { return (size_t)pg_rows(M) * K * 4; }
 
 #ifdef __HIPCC__
 typedef __bf16 pg_bf2 __attribute__((ext_vector_type(2)));

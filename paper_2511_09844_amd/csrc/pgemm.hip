@@ -75,7 +75,7 @@ struct PgArgs {
     int nss;
     float eps;
     const int32_t* m_live;  // rows that hold data, of M (null: all)
-    int M, Mp, K, S, nblk_m, nblk_n, nbs;
+    int M, Mp, K, S, nblk_m, nblk_n, nbs, units;
     const uint16_t* W[3];
     int pairs;          // pairs of 16-row sub-tiles
     int tiles;          // 16-column tiles of the output (store, add, SwiGLU)
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
         if (M == 0) return;
         nblk_m = (M + 16 * MG - 1) / (16 * MG);
         nbs = 8 * nblk_m * ((a.nblk_n + 7) / 8);
-        S = S > 1 ? pg_ranges(nblk_m * a.nblk_n, MG, a.K) : 1;
+        S = S > 1 ? pg_ranges(nblk_m * a.nblk_n, MG, a.K, a.units) : 1;
     }
     const int s = blockIdx.x / nbs, bb = blockIdx.x % nbs;
     if (s >= S) return;
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(256, 2) void k_sgemm(PgArgs a) {
 // enough blocks (36 rows of gate|up 8B: 63 against 70 us, 70B 208 against 226, of a vocabulary 392
 // against 478).  S: up to two workgroups per CU, one with up to 32
 // rows (24 rows of gate|up: 55 us unsplit, 60 with S 2; of Q|K|V: 19 with S 4, 23 with S 8).
-PgPlan pg_plan(int M, int N, int K, bool packed) {
+PgPlan pg_plan(int M, int N, int K, bool packed, size_t room) {
     PgPlan p{};
     const int rows = pg_rows(M);
     auto blocks = [&](int mg, int ng) { return ((rows + 16 * mg - 1) / (16 * mg)) * ((N + 64 * ng - 1) / (64 * ng)); };
@@ -588,24 +588,23 @@ PgPlan pg_plan(int M, int N, int K, bool packed) {
     p.nblk_m = (rows + 16 * p.MG - 1) / (16 * p.MG);
     p.nblk_n = (N + 64 * p.NG - 1) / (64 * p.NG);
     const int nb = p.nblk_m * p.nblk_n, tile = p.MG * p.NG * 1024;
-    p.S = pg_ranges(nb, p.MG, K);
+    p.units = (int)std::min<size_t>(room / tile, kPgUnits);
+    p.S = pg_ranges(nb, p.MG, K, p.units);
     p.grid = 8 * p.nblk_m * ((p.nblk_n + 7) / 8) * p.S;
     if (packed) {
         // the most any number of row blocks asks for
         int part = 0;
         p.S = 1;
         for (int m = 1; m <= p.nblk_m; ++m) {
-            const int S = pg_ranges(m * p.nblk_n, p.MG, K);
+            const int S = pg_ranges(m * p.nblk_n, p.MG, K, p.units);
             p.grid = std::max(p.grid, 8 * m * ((p.nblk_n + 7) / 8) * S);
             p.S = std::max(p.S, S);
             if (S > 1) part = std::max(part, m * p.nblk_n * S);
         }
         p.part = (size_t)part * tile;
-        p.cnt = part ? nb : 0;
         return p;
     }
     p.part = p.S > 1 ? (size_t)nb * p.S * tile : 0;
-    p.cnt = p.S > 1 ? nb : 0;
     return p;
 }
 
@@ -636,7 +635,7 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
     a.planes = c.planes;
     if (!a.planes) {
         // the MLP's planes are free outside a layer
-        if (!ws.planes || c.M > e->maxm || pg_plane_bytes(c.M, c.K) > ws.ffh_n) return false;
+        if (c.M > e->maxm || pg_plane_bytes(c.M, c.K) > ws.ffh_n) return false;
         PlaneArgs x{};
         x.X = c.X; x.in_map = c.in_map; x.Mp = a.Mp; x.K = c.K; x.gamma = (const uint16_t*)c.gamma;
         x.planes = (uint16_t*)ws.ffh;
@@ -653,13 +652,8 @@ bool launch_pgemm(Engine* e, hipStream_t s, const WsCall& c) {
         a.W[i] = i < c.nseg ? (const uint16_t*)c.W[i] : nullptr;
         if (i < c.nseg) N += c.seg_rows[i];
     }
-    PgPlan p = pg_plan(c.M, N, c.K, c.m_live != nullptr);
-    a.m_live = c.m_live;
-    if (p.part > ws.ws_part_n || p.cnt > ws.ws_cnt_n) {
-        // partials must fit the workspace
-        p.S = 1;
-        p.grid = 8 * p.nblk_m * ((p.nblk_n + 7) / 8);
-    }
+    const PgPlan p = pg_plan(c.M, N, c.K, c.m_live != nullptr, ws.ws_part_n);
+    a.m_live = c.m_live; a.units = p.units;
     a.S = p.S; a.nblk_m = p.nblk_m; a.nblk_n = p.nblk_n;
     a.nbs = 8 * p.nblk_m * ((p.nblk_n + 7) / 8);
     if (c.mode == kEpiSwiglu) {

@@ -7,6 +7,7 @@ import re
 import pytest
 
 import sd2_inputs as si
+from sd2_inputs.configs import Dims, Workload
 from paper_2511_09844_amd import binding as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -134,6 +135,27 @@ def test_create_noalloc_argument_errors_without_gpu():
     c = B.config_of(si.TINY, steering=B.STEER_MLP)
     assert lib.sd2_create_noalloc(ctypes.byref(c), None, None, None, None, ctypes.byref(h)) == -1
     assert lib.sd2_create_noalloc(ctypes.byref(B.config_of(si.TINY)), None, None, None, None, None) == -1
+
+
+def test_create_noalloc_takes_what_the_static_array_holds():
+    """Refused for capacity exactly where sd2_workspace_bytes exceeds the array, before any device call.
+    The set is fixed: workspaces of 23 to 62 MiB with their least room for split-K partials are taken
+    (and report at most the array, whatever the plans would use), larger ones refused."""
+    lib = B.load()
+    h = B.P()
+
+    def one(d, ff, batch, prompt):
+        return Workload("w", Dims(1, d, d // 64, d // 128, ff, 1008), Dims(1, d // 2, d // 128, d // 128, ff, 1008), "bf16",
+                        4, batch, (prompt, prompt), 20, 1.0)
+
+    taken = [one(1024, 2048, 4, 128), one(1024, 4096, 1, 512), one(1536, 3072, 1, 512), one(2048, 4096, 1, 128),
+             one(2048, 4096, 4, 128), one(2048, 4096, 5, 100), si.SMALL, si.SMALL.with_(prompt=(256, 256))]
+    for wl, fits in [(w, True) for w in taken] + [(one(2048, 4096, 1, 512), False),
+                                                  (si.SMALL.with_(prompt=(384, 384)), False)]:
+        c = B.config_of(wl)
+        assert (lib.sd2_workspace_bytes(ctypes.byref(c)) <= (64 << 20)) == fits, wl
+        rc = lib.sd2_create_noalloc(ctypes.byref(c), None, None, None, None, ctypes.byref(h))
+        assert (rc != -2) == fits, (wl, rc)
 
 
 def test_train_loss_scratch_sizes_without_gpu():

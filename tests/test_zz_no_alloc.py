@@ -13,6 +13,7 @@ import torch
 
 import sd2_inputs as si
 from oracle_fixtures import MK2
+from sd2_inputs.configs import Dims, Workload
 
 pytestmark = pytest.mark.gpu
 
@@ -56,9 +57,24 @@ def _side_by_side(wl, max_rounds=200):
 
 
 def test_noalloc_matches_caller_workspace_twice_second_smaller():
-    r1, p1 = _side_by_side(MK2)                               # 19.9 MiB, persistent path, 2 sequences
-    r2, p2 = _side_by_side(si.TINY.with_(new_tokens=16))      # 6.1 MiB, f32, per-operation path
+    r1, p1 = _side_by_side(MK2)                               # 31.7 MiB, persistent path, 2 sequences
+    r2, p2 = _side_by_side(si.TINY.with_(new_tokens=16))      # 5.9 MiB, f32, per-operation path
     assert r1 > 0 and r2 > 0 and p1 == 1 and p2 == 0
+
+
+@pytest.mark.parametrize("wl,path", [
+    # split-K partials with less room than the plans ask for: ragged prompts, 20 verify rows
+    (Workload("partials", Dims(1, 2048, 32, 16, 4096, 1008, 5e5), Dims(1, 1024, 16, 8, 4096, 1008, 5e5), "bf16", 4, 4,
+              (17, 128), 10, 1.0, 211), 0),
+    # one prompt of 512 rows
+    (Workload("partials1", Dims(1, 1024, 16, 8, 4096, 1008, 5e5), Dims(1, 512, 8, 8, 4096, 1008, 5e5), "bf16", 4, 1,
+              (513, 513), 10, 1.0, 213), 1)], ids=["ragged", "long"])
+def test_noalloc_matches_where_partials_fill_the_static_array(wl, path):
+    # exact against the caller's workspace (tokens, counts, logits), and both against the oracle
+    from gpu_harness import parity_run
+    rounds, got = _side_by_side(wl)
+    assert rounds > 0 and got == path
+    assert parity_run(wl, expect_path=path).pinned > 0
 
 
 def test_noalloc_one_live_handle_per_device_and_size_limit():
