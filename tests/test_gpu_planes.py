@@ -43,8 +43,20 @@ def test_few_row_attention_at_tile_and_span_edges(n, k):
     _run(batch=2, k=k, prompt=(n, n), new_tokens=k + 1, seed=70 + n)
 
 
-def test_few_row_attention_head_dim_128_one_head_per_kv_head():
-    _run(verifier=Dims(1, 1024, 8, 8, 1024, 1008, 5e5), batch=2, k=16, prompt=(250, 300), new_tokens=8, seed=91)
+# head dim 128 and one query head per KV head in both models
+VER128 = Dims(1, 1024, 8, 8, 1280, 1008, 5e5)
+DRF128 = Dims(1, 512, 4, 4, 768, 1008, 5e5)
+
+
+@pytest.mark.parametrize("k", [4, 14])
+def test_few_row_attention_head_dim_128_one_head_per_kv_head(k):
+    # 5 and 15 verify rows, 1 and 2 drafter rows: column tiles that rows alone leave partly empty
+    _run(verifier=VER128, drafter=DRF128, batch=2, k=k, prompt=(250, 300), new_tokens=8, seed=91)
+
+
+def test_many_row_attention_head_dim_128_verify_rows():
+    # 17 verify rows, one more than a row block, over several spans
+    _run(verifier=VER128, drafter=DRF128, batch=2, k=16, prompt=(250, 300), new_tokens=8, seed=91)
 
 
 def test_packed_prefill_ragged():
