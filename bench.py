@@ -94,7 +94,7 @@ def cpu_baseline(wl, wv, wd, ws, toks, lens, budget_s):
 # ---------------------------------------------------------------------------------------------
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_mk_8b-bf16-b1_traffic.json")
 TRAFFIC_SOURCES = ("paper_2511_09844_amd/csrc/mk.hip", "paper_2511_09844_amd/csrc/mk.h",
-                   "paper_2511_09844_amd/csrc/device_common.h")
+                   "paper_2511_09844_amd/csrc/device_common.h", "paper_2511_09844_amd/csrc/attn_part.h")
 ROOFLINE_KERNEL = "k_mk"
 
 

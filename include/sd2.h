@@ -125,7 +125,10 @@ typedef struct {
     const void* w_cu;      /* SD2_STEER_MLP_COND: U [L_D * d_ff_D][R], rows l*d_ff_D .. the U_l block */
 } sd2_mlp_steering;
 
-/* Bytes of device workspace sd2_create needs for cfg (0 if cfg is invalid). */
+/* Bytes of device workspace sd2_create needs for cfg (0 if cfg is invalid).  K/V caches and logits
+   grow with the configuration; above SD2_NOALLOC_WORKSPACE_BYTES prefill runs chunks of 2048 rows
+   (512 up to it), whose activations and partial sums take most of the rest: 707 MiB for the
+   8B / 1B pair of the benchmark (one sequence, 774 positions), 242 MiB of it K/V. */
 size_t sd2_workspace_bytes(const sd2_config* cfg);
 
 /*

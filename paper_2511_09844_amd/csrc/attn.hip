@@ -358,10 +358,13 @@ __global__ __launch_bounds__(256) void k_pattn(AttnArgs a, int nspan, int span_t
 // the key loop: S^T = K Q^T walks the head dimension as dim = 16 s4 + 4 g + e (lane group g, step
 // 4 s4 + e), so that the four lanes of a key read 64 adjacent bytes per load, and O^T += V^T P^T
 // numbers the output dims as 64 t4 + 4 i + e (tile row i, tile 4 t4 + e), so that the 16 lanes of
-// a key read 256.  A wave's next tile is requested before the current one is used.  The online softmax stays in registers (see k_pattn); the waves' sums are merged
+// a key read 256.  The online softmax stays in registers (see k_pattn); the waves' sums are merged
 // through LDS, and the last live span of a group to arrive merges the spans.
 //
-// Bound: K/V bytes at long contexts, one tile's chain of load, products and softmax at short ones.
+// Bound: a tile's chain of loads, products and softmax.  The loop names a wave's next tile before it
+// uses the current one, but nothing in it writes memory, and the compiler sinks the loads to their
+// uses: at head dim 128 a tile's 16 loads are waited for one or two at a time among its 64 products
+// (145 VGPRs; two tiles, the queries and the outputs would need 192).
 // 4 sequences of 6 rows at 201 to 901 positions, 32/8 heads, head dim 128: 18 us (115 with the vector
 // kernel before); 16 of 8 rows at 256 to 2048: 61 us (80 with two heads per tile staged through LDS).
 // ---------------------------------------------------------------------------------------------
@@ -582,7 +585,9 @@ static void launch_vattn(Engine& e, hipStream_t s, const AttnArgs& a) {
     // sequences come to about 8 x 193 workgroups at the 3081 positions swept; at least two per wave, one
     // with very few groups, and at most 48 spans to merge.  Measured best or within 5 % of it from 16
     // groups (2 sequences of 4 rows: 11.1 us with 4 tiles, 13.6 with 8) over 64 (4 of 6: 18.2 with 8,
-    // 20.5 with 4, 22.8 with 16) to 256 (16 of 8: 60.7 with 32, 70.1 with 16, 88.6 with 64).
+    // 20.5 with 4, 22.8 with 16) to 256 (16 of 8: 60.7 with 32, 70.1 with 16, 88.6 with 64).  Large
+    // ragged batches pull either way: a round of 128 sequences of 6 rows, d 2048 and 4 layers, takes 5.2 ms
+    // with one of 5000 positions among 100s (4.5 with 8 tiles), 6.7 with lengths spread to 3000 (7.0).
     const int tiles = (a.cap + 15) / 16, ng = groups * ncg;
     int span_t = std::max(ng < 24 ? 4 : kVaMinTiles, ng / 8);
     span_t = (std::max(span_t, (tiles + 47) / 48) + 3) / 4 * 4;

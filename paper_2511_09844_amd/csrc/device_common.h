@@ -30,20 +30,21 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// The same sum with DPP steps (quad permutes, row mirrors, row broadcasts), every lane active: no
-// LDS round trips; uniform.
+// The same sum through DPP row operations (no LDS round trips), every lane active: pairs, quads, half
+// rows and rows by swaps and mirrors, then rows 0-3 folded into row 3 by the row broadcasts; lane
+// 63's result is returned to every lane.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ float dpp_f32(float old, float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v),
                                                                  CTRL, ROWS, 0xf, false));
 }
 __device__ __forceinline__ float wave_sum_dpp(float v) {
-    v += dpp_f32<0xB1, 0xf>(0.f, v);
-    v += dpp_f32<0x4E, 0xf>(0.f, v);
-    v += dpp_f32<0x141, 0xf>(0.f, v);
-    v += dpp_f32<0x140, 0xf>(0.f, v);
-    v += dpp_f32<0x142, 0xa>(0.f, v);
-    v += dpp_f32<0x143, 0xc>(0.f, v);
+    v += dpp_f32<0xB1, 0xf>(0.f, v);   // quad_perm [1,0,3,2]
+    v += dpp_f32<0x4E, 0xf>(0.f, v);   // quad_perm [2,3,0,1]
+    v += dpp_f32<0x141, 0xf>(0.f, v);  // row_half_mirror
+    v += dpp_f32<0x140, 0xf>(0.f, v);  // row_mirror
+    v += dpp_f32<0x142, 0xa>(0.f, v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_f32<0x143, 0xc>(0.f, v);  // row_bcast:31 into rows 2 and 3
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
@@ -123,8 +124,9 @@ __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
 //   - every workgroup stores its partial with device-scope (write-through) stores and waits
 //     until they have completed, then counts itself in with a device-scope atomic;
 //   - the workgroup that counts in last reads all partials with ordinary loads.  Those lines
-//     are read by nobody else during the kernel, so no stale copy of them can sit in the
-//     reader's caches; the caches are invalidated at every kernel start.
+//     are read by nobody else during the kernel (no 128-byte line holds partials of two groups),
+//     so no stale copy of them can sit in the reader's caches; the caches are invalidated at every
+//     kernel start.
 // The last workgroup also resets the counter for the next launch.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void store_through(float* p, float v) {

@@ -26,7 +26,7 @@ enum MkX : int32_t { kMkXBuf = 0, kMkXEmbed = 1, kMkXAttn = 2 };
 // each unit is a tile times a 512-column slice per wave, wpu waves per tile (gate|up: a tile is
 // 16 features with a gate and an up sub-tile when subs == 2, else 8 gate + 8 up rows).  ATTN:
 // causal GQA attention of the launch's rows over the cache of layer `layer`, in units of
-// (sequence, KV head, group of up to 8 query vectors, 64-position span).
+// (sequence, KV head, group of up to 8 query vectors, run of 64-position spans).
 struct MkPhase {
     int32_t op, mode, K, tiles, S, KR, wpu, subs, nseg, xsrc, res_embed, ldy;
     int32_t seg_tiles[3];

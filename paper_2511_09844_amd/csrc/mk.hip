@@ -105,30 +105,14 @@ __device__ __forceinline__ T mk_uni(const T& v) {
     return r;
 }
 
-// Wave-wide max / sum through DPP row operations (no LDS round trips): pairs, quads, half rows
-// and rows by swaps and mirrors, then rows 0-3 folded into row 3 by the row broadcasts; the
-// result of lane 63 is returned to every lane.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float mk_dpp(float old, float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v),
-                                                                 CTRL, ROWS, 0xf, false));
-}
+// Wave-wide max through DPP row operations, as wave_sum_dpp.
 __device__ __forceinline__ float mk_wmax(float v) {
-    v = fmaxf(v, mk_dpp<0xB1, 0xf>(v, v));   // quad_perm [1,0,3,2]
-    v = fmaxf(v, mk_dpp<0x4E, 0xf>(v, v));   // quad_perm [2,3,0,1]
-    v = fmaxf(v, mk_dpp<0x141, 0xf>(v, v));  // row_half_mirror
-    v = fmaxf(v, mk_dpp<0x140, 0xf>(v, v));  // row_mirror
-    v = fmaxf(v, mk_dpp<0x142, 0xa>(v, v));  // row_bcast:15 into rows 1 and 3
-    v = fmaxf(v, mk_dpp<0x143, 0xc>(v, v));  // row_bcast:31 into rows 2 and 3
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-__device__ __forceinline__ float mk_wsum(float v) {
-    v += mk_dpp<0xB1, 0xf>(0.f, v);
-    v += mk_dpp<0x4E, 0xf>(0.f, v);
-    v += mk_dpp<0x141, 0xf>(0.f, v);
-    v += mk_dpp<0x140, 0xf>(0.f, v);
-    v += mk_dpp<0x142, 0xa>(0.f, v);
-    v += mk_dpp<0x143, 0xc>(0.f, v);
+    v = fmaxf(v, dpp_f32<0xB1, 0xf>(v, v));
+    v = fmaxf(v, dpp_f32<0x4E, 0xf>(v, v));
+    v = fmaxf(v, dpp_f32<0x141, 0xf>(v, v));
+    v = fmaxf(v, dpp_f32<0x140, 0xf>(v, v));
+    v = fmaxf(v, dpp_f32<0x142, 0xa>(v, v));
+    v = fmaxf(v, dpp_f32<0x143, 0xc>(v, v));
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
@@ -453,7 +437,7 @@ __device__ __forceinline__ void mk_gemv(const MkArgs& a, const MkPhase& od, cons
                 *(uint2*)(xl + (size_t)m * ldk + 4 * c) = make_uint2(__builtin_bit_cast(uint32_t, l0), __builtin_bit_cast(uint32_t, l1));
                 sqm += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
             }
-            sqm = mk_wsum(sqm);
+            sqm = wave_sum_dpp(sqm);
             if (lane == 0 && wave < kNW) ssq[m * kNW + wave] = sqm;
         }
     } else {
@@ -517,7 +501,7 @@ __device__ __forceinline__ void mk_gemv(const MkArgs& a, const MkPhase& od, cons
             // the rows' wave sums are independent DPP chains
     #pragma unroll
             for (int mm = 0; mm < 8; ++mm)
-                if (m0 + mm < M) sq[mm] = mk_wsum(sq[mm]);
+                if (m0 + mm < M) sq[mm] = wave_sum_dpp(sq[mm]);
     #pragma unroll
             for (int mm = 0; mm < 8; ++mm)
                 if (m0 + mm < M && lane == 0 && wave < kNW) ssq[(m0 + mm) * kNW + wave] = sq[mm];
@@ -963,7 +947,7 @@ __device__ __forceinline__ void mk_attn_t(const MkArgs& a, const MkPhase& od, co
                     const float pr = v == -INFINITY ? 0.f : expf(v - mx);
                     // the sums so far, at the new maximum (nothing seen yet: nothing to scale)
                     const float cr = FIRST || m_run == -INFINITY ? 0.f : expf(m_run - mx);
-                    l_run = FIRST ? mk_wsum(pr) : l_run * cr + mk_wsum(pr);
+                    l_run = FIRST ? wave_sum_dpp(pr) : l_run * cr + wave_sum_dpp(pr);
                     m_run = mx;
                     ps[wave * kMkSpan + lane] = pr;  // [query][position]
                     if (lane == 0) {

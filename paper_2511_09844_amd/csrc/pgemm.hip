@@ -11,11 +11,13 @@
 // A workgroup of four waves owns 16 MG rows and 64 NG weight rows: each wave holds 16 NG weight
 // rows of its own, whose fragments it loads straight into registers (a weight is read by one wave
 // only, so LDS would add traffic), against all the rows, whose planes all four waves read from
-// LDS.  K goes in steps of KB blocks of 64 columns with two LDS buffers: while step i multiplies,
-// the planes of step i + 1 are on their way into registers, and each weight fragment is
-// requested again for a later step (WD steps on) as soon as it has been used.  A row of a block is 256 bytes
-// in LDS, its sixteen 16-byte chunks permuted by chunk ^ (row & 15), so that the sixteen rows of
-// an operand read fall into different banks.
+// LDS.  K goes in steps of KB blocks of 64 columns with two LDS buffers; step i requests the planes of
+// step i + 1 and each weight fragment of a later step (WD steps on).  As compiled these loads stand at
+// the end of the step, among its last products: the planes are waited for there, and with WD 1 the
+// weights at the start of the next step, so a step shows a good part of a memory round trip that only
+// the CU's other workgroup covers.  A row of a block is 256 bytes in LDS, its sixteen 16-byte chunks
+// permuted by chunk ^ (row & 15), so that the sixteen rows of an operand read fall into different
+// banks.
 //
 // The weights are the A operand of v_mfma_f32_16x16x32_bf16 and the activations the B operand, so
 // a lane ends with four consecutive output columns of one row: the epilogues (store, residual add
@@ -279,7 +281,8 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(PgArgs a) {
     // statistics (4 MG rows of partial sums of squares per wave, all in flight together), the planes
     // and the weights of the first step, and what the epilogue reads; the sums are added while the
     // weights are on their way.  With more rows the statistics would fill the registers: they follow
-    // the weights, eight rows in flight, and the epilogue reads its inputs itself.
+    // the weights, eight rows in flight, and the epilogue reads its inputs itself, in a round trip or
+    // more for each row group and pair.
     constexpr bool kFew = MG <= 2;
     constexpr int RW = 4 * MG, RU = RW < 8 ? RW : 8;
     int pos[MG];
@@ -556,7 +559,7 @@ __global__ __launch_bounds__(256, 2) void k_sgemm(PgArgs a) {
 }
 
 // Shapes from a sweep of tiles and splits over 8 to 2048 rows at the 8B, 70B and drafter widths
-// (weights cycled through more than the last-level cache).  MG: the fewest row groups that hold
+// (weights cycled through more than the last-level cache; loads as compiled, see above).  MG: the fewest row groups that hold
 // the rows, up to 128 rows, so that the weights are read once.  NG 4 (128 x 256) halves the LDS
 // reads per product and wins wherever its grid fills the chip (512 rows of gate|up 8B: 209 us
 // against 269 with NG 2), or K is long enough to split (1024 rows of down: 225 against 252);
